@@ -261,7 +261,13 @@ int hdg_get_update_tile(const hdg_ctx *ctx, int n);
  *    (pivots chosen among rows 0..n-1), the elimination carried through the
  *    trace rows and the [B | R_qu] columns.  Afterwards rows 0..n-1 hold U (upper
  *    triangle of the n x n block) and L^{-1} P [B | R_qu]; rows n.. hold
- *    [S^K | -g^K].
+ *    [S^K | -g^K].  Where an element's gradient rows have the structure of
+ *    eq. hdg-grad (one mass matrix M in every field, the same coupling to u_c and
+ *    uh_c for every component, checked entry by entry), the gradient is
+ *    eliminated with M itself as the block factor: U's first 15 N_p rows are then
+ *    scaled so that their diagonal blocks are identities (L holds M there), and
+ *    the pivots of the remaining 5 N_p columns are chosen among the conserved
+ *    rows.  Any other system takes the LU of all n columns.
  *  HDG_MIXED_FAST: as HDG_FP64 but in FP32 (an FP32 copy of the systems in the
  *    workspace); S^K and g^K carry the FP32 rounding; rows 0..n-1 of E are then
  *    overwritten with the FP32 factors converted to FP64 (for the recovery).

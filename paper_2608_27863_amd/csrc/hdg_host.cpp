@@ -298,6 +298,8 @@ int hdg_create(const hdg_mesh_desc *m, const hdg_phys *phys, hdg_ctx **out) {
     ctx->tloc_off.assign(ne + 1, 0);
     ctx->m32_off.assign(ne + 1, 0);
     ctx->x_off.assign(ne + 1, 0);
+    ctx->kred_off.assign(ne + 1, 0);
+    ctx->aux_off.assign(ne + 1, 0);
     ctx->vgeo_off.assign(ne + 1, 0);
     ctx->fgeo_off.assign(6 * ne + 1, 0);
     ctx->toff.assign(7 * ne, 0);
@@ -339,6 +341,8 @@ int hdg_create(const hdg_mesh_desc *m, const hdg_phys *phys, hdg_ctx **out) {
         ctx->tloc_off[e + 1] = ctx->tloc_off[e] + f;
         ctx->m32_off[e + 1] = ctx->m32_off[e] + (int64_t)n * hdg::e_ld(n, f);
         ctx->x_off[e + 1] = ctx->x_off[e] + (int64_t)n * hdg::x_ld(f);
+        ctx->kred_off[e + 1] = ctx->kred_off[e] + hdg::red_k_size(Np, f);
+        ctx->aux_off[e + 1] = ctx->aux_off[e] + hdg::red_aux_size(Np, f);
     }
     for (int F = 0; F < nf; ++F) ctx->max_b = std::max(ctx->max_b, trace_size(ctx->face_p[F]));
     // ---- tables and geometry
@@ -517,6 +521,8 @@ int hdg_create(const hdg_mesh_desc *m, const hdg_phys *phys, hdg_ctx **out) {
     UP(ctx->tloc_off, tloc_off);
     UP(ctx->m32_off, m32_off);
     UP(ctx->x_off, x_off);
+    UP(ctx->kred_off, kred_off);
+    UP(ctx->aux_off, aux_off);
     UP(ctx->vgeo_off, vgeo_off);
     UP(ctx->fgeo_off, fgeo_off);
     UP(vgeo, vgeo);
@@ -605,7 +611,7 @@ int hdg_workspace_size(const hdg_ctx *ctx, int op, int prec, int e0, int ne, siz
             return HDG_OK;
         case 1:  // hdg_condense
             if (!chunk_ok(ctx, e0, ne)) return HDG_ERR_INVALID_ARGUMENT;
-            *bytes = (prec == HDG_FP64)    ? round256(hdg::bordered_lu_work(ctx, ne))
+            *bytes = (prec == HDG_FP64)    ? hdg::condense_fp64_work_bytes(ctx, e0, ne)
                      : (prec == HDG_MIXED) ? hdg::condense_mixed_work_bytes(ctx, e0, ne)
                                            : hdg::condense_fast_work_bytes(ctx, e0, ne);
             return HDG_OK;
@@ -643,8 +649,9 @@ int hdg_local_residual_jacobian(hdg_ctx *ctx, int e0, int ne, const double *Q, c
                                                  (hipStream_t)stream));
 }
 
-int hdg_condense(hdg_ctx *ctx, int prec, int refine_steps, int e0, int ne, double *E, double *SK, int *info,
-                 void *work, size_t work_bytes, void *stream) {
+// formed: E was written by hdg_local_residual_jacobian in this same call
+static int condense_any(hdg_ctx *ctx, int prec, int refine_steps, int e0, int ne, bool formed, double *E, double *SK,
+                        int *info, void *work, size_t work_bytes, void *stream) {
     if (!chunk_ok(ctx, e0, ne) || !E || !SK || !info) return HDG_ERR_INVALID_ARGUMENT;
     if (prec != HDG_FP64 && prec != HDG_MIXED && prec != HDG_MIXED_FAST) return HDG_ERR_INVALID_ARGUMENT;
     if (prec == HDG_MIXED && (refine_steps < 1 || refine_steps > 8)) return HDG_ERR_INVALID_ARGUMENT;
@@ -652,10 +659,15 @@ int hdg_condense(hdg_ctx *ctx, int prec, int refine_steps, int e0, int ne, doubl
     hdg_workspace_size(ctx, 1, prec, e0, ne, &need);
     if (!work || work_bytes < need) return HDG_ERR_WORKSPACE;
     if (prec == HDG_FP64)
-        return dev_status(hdg::launch_condense_fp64(ctx, e0, ne, E, SK, info, work, (hipStream_t)stream));
+        return dev_status(hdg::launch_condense_fp64(ctx, e0, ne, formed, E, SK, info, work, (hipStream_t)stream));
     if (prec == HDG_MIXED_FAST)
         return dev_status(hdg::launch_condense_fast(ctx, e0, ne, E, SK, info, work, (hipStream_t)stream));
     return dev_status(hdg::launch_condense_mixed(ctx, e0, ne, refine_steps, E, SK, info, work, (hipStream_t)stream));
+}
+
+int hdg_condense(hdg_ctx *ctx, int prec, int refine_steps, int e0, int ne, double *E, double *SK, int *info,
+                 void *work, size_t work_bytes, void *stream) {
+    return condense_any(ctx, prec, refine_steps, e0, ne, false, E, SK, info, work, work_bytes, stream);
 }
 
 int hdg_assemble_trace(hdg_ctx *ctx, const double *SK, double *S_bsr, double *g, void *stream) {
@@ -858,7 +870,7 @@ static int newton_enqueue(hdg_ctx *ctx, const hdg_newton_args *a, void *stream) 
         if ((rc = hdg_local_residual_jacobian(ctx, e0, ne, a->Q, a->U, a->Un, a->Uhat, a->nu, a->Ub, Ek(e0),
                                               a->qp_work, a->qp_work_bytes, stream)))
             return rc;
-        if ((rc = hdg_condense(ctx, a->prec, a->refine_steps, e0, ne, Ek(e0), a->SK, a->info, a->cond_work,
+        if ((rc = condense_any(ctx, a->prec, a->refine_steps, e0, ne, true, Ek(e0), a->SK, a->info, a->cond_work,
                                a->cond_work_bytes, stream)))
             return rc;
     }

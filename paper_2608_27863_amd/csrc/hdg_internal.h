@@ -56,6 +56,8 @@ struct DevMesh {
     const int64_t *tloc_off;   // [n_elem+1] prefix sums of f_e (element-local trace vectors)
     const int64_t *m32_off;    // [n_elem+1] FP32 interior systems [A | B R_qu] (n x e_ld floats)
     const int64_t *x_off;      // [n_elem+1] X = A^{-1}[B | R_qu] (n x x_ld doubles)
+    const int64_t *kred_off;   // [n_elem+1] reduced systems K' (red_k_size)
+    const int64_t *aux_off;    // [n_elem+1] their auxiliary regions (red_aux_size)
     const int64_t *vgeo_off;   // [n_elem+1]  volume geometry: [10][Nq] = W, G00..G22 (G = J^{-1})
     const int64_t *fgeo_off;   // [n_elem*6+1] face geometry: [4][Nqf] = w N_x, w N_y, w N_z, w |N|
     const double *vgeo;
@@ -93,6 +95,33 @@ __host__ __device__ inline int asm_pad(int f) { return (f + 3) & ~3; }
 // Row stride of X (doubles): f + 1 rounded up to a multiple of 8.
 __host__ __device__ inline int64_t x_ld(int f) { return ((int64_t)(f + 1) + 7) / 8 * 8; }
 
+// Reduced system K' of an element (the gradient unknowns eliminated, k_reduce.hip):
+// red_n + f rows of stride e_ld(red_n, f), red_n = 5 N_p rounded up to a multiple
+// of 4 with decoupled identity unknowns (so that every column offset allows
+// 16-byte accesses), and its auxiliary region Y | M^{-1} | residual parts.
+// Sizes in doubles, multiples of 16 (128-byte lines).
+__host__ __device__ inline int red_n(int Np) { return (5 * Np + 3) & ~3; }
+__host__ __device__ inline int red_ldy(int Np, int w) { return (Np + w + 5 + 7) / 8 * 8; }
+__host__ __device__ inline int red_ldm(int Np) { return (Np + 15) / 16 * 16; }
+inline int64_t red_k_size(int Np, int f) { return ((int64_t)(red_n(Np) + f) * e_ld(red_n(Np), f) + 15) / 16 * 16; }
+inline int64_t red_aux_size(int Np, int f) {
+    return ((int64_t)3 * Np * red_ldy(Np, f / 5) + (int64_t)Np * red_ldm(Np) + 5 * (red_n(Np) + f) + 15) / 16 * 16;
+}
+// Buffers of a chunk's reduced systems: element e's K' at K + k_off[e] - k_off[e0],
+// its auxiliary region at aux + aux_off[e] - aux_off[e0]; sel[e - e0] = 1 if the
+// element is condensed this way, 0 if by the dense LU of all its columns.
+struct RedBuf {
+    double *K, *aux;
+    int *sel;
+    const int64_t *k_off, *aux_off;
+};
+// Mark at the start of an element's first trace row (columns 0 .. 3, which hold
+// nothing after the condensation): its gradient rows are [I | Y_j | r].
+constexpr int kRedMarkN = 4;
+__host__ __device__ inline unsigned long long red_mark(int i) {
+    return 0x3FE5A3C96D1B7E42ull ^ ((unsigned long long)(i + 1) * 0x0009E3779B97F4A7ull);
+}
+
 }  // namespace hdg
 
 struct hdg_ctx {
@@ -108,7 +137,7 @@ struct hdg_ctx {
     bool face_cols_aligned = true, asm_cols_aligned64 = true, asm_cols_aligned32 = true;
     std::vector<int> elem_p, face_p, elem_face, face_elem, face_bc, toff, elem_n, elem_f;
     std::vector<int64_t> node_off, face_off, E_off, SK_off, asm_off, qp_off, vgeo_off, fgeo_off, asmsys_off,
-        tloc_off, m32_off, x_off;
+        tloc_off, m32_off, x_off, kred_off, aux_off;
     std::vector<int64_t> bsr_row_ptr64, bsr_col64, bsr_val_off;
     std::vector<int> bsr_row_ptr, bsr_col;
     hdg::DevMesh dm{};
@@ -121,15 +150,22 @@ namespace hdg {
 int launch_element_system(const hdg_ctx *ctx, int e0, int ne, const double *Q, const double *U,
                           const double *Un, const double *Uhat, const double *nu, const double *Ub,
                           double *E, double *qp, hipStream_t s);
-int launch_condense_fp64(const hdg_ctx *ctx, int e0, int ne, double *E, double *SK, int *info,
+// formed: the systems come straight from launch_element_system (no structure check)
+int launch_condense_fp64(const hdg_ctx *ctx, int e0, int ne, bool formed, double *E, double *SK, int *info,
                          void *work, hipStream_t s);
+size_t condense_fp64_work_bytes(const hdg_ctx *ctx, int e0, int ne);
+// gradient elimination (k_reduce.hip)
+void launch_red_init(int ne, bool structured, int *info, int *sel, hipStream_t s);
+int launch_red_eliminate(const hdg_ctx *ctx, const RedBuf &rb, int e0, int ne, bool checked, bool write, double *E,
+                         int *info, hipStream_t s);
+int launch_red_writeback(const hdg_ctx *ctx, const RedBuf &rb, int e0, int ne, double *E, double *SK, hipStream_t s);
+int launch_red_clear_mark(const hdg_ctx *ctx, int e0, int ne, const int *sel, double *E, hipStream_t s);
 int launch_condense_mixed(const hdg_ctx *ctx, int e0, int ne, int refine, double *E, double *SK,
                           int *info, void *work, hipStream_t s);
 size_t condense_mixed_work_bytes(const hdg_ctx *ctx, int e0, int ne);
 int launch_condense_fast(const hdg_ctx *ctx, int e0, int ne, double *E, double *SK, int *info, void *work,
                          hipStream_t s);
 size_t condense_fast_work_bytes(const hdg_ctx *ctx, int e0, int ne);
-size_t bordered_lu_work(const hdg_ctx *ctx, int ne);
 int run_asm_inversion(const hdg_ctx *ctx, int prec, void *sys, int *info, void *work, hipStream_t s);
 int launch_assemble(const hdg_ctx *ctx, const double *SK, double *S, double *g, hipStream_t s);
 int launch_matvec(const hdg_ctx *ctx, const double *S, const double *x, double *y, hipStream_t s);

@@ -110,26 +110,43 @@ struct ElemDims {
 };
 // Systems factored here: mode 0 = element systems (n = 20 N_p, f = f_e, all
 // n + f rows); mode 1 = Schwarz inversion systems [S_r | I] (n = f = f_r rounded up
-// to a multiple of 4, n rows); mode 2 = FP32 interior rows [A | B R_qu] (n rows).
+// to a multiple of 4, n rows); mode 2 = FP32 interior rows [A | B R_qu] (n rows);
+// mode 3 = reduced systems K' (n = red_n, all n + f rows); mode 4 = the first red_n
+// rows of K' in FP32.  With sel, only the elements with sel[e - e0] == want are
+// factored: the others have n = 0, past which every kernel returns at once.
 struct SysDesc {
     int mode;
     const int64_t *off;  // [n_elem+1] offsets (elements) of the systems
+    const int *sel = nullptr;
+    int e0 = 0, want = 0;
 };
 __device__ inline ElemDims elem_dims(const DevMesh &dm, const SysDesc &sd, int e) {
     ElemDims d;
+    if (sd.sel && sd.sel[e - sd.e0] != sd.want) {
+        d.n = d.f = d.mrows = d.ncols = 0;
+        d.ld = 0;
+        return d;
+    }
     if (sd.mode != 1) {
         const int p = dm.elem_p[e];
-        d.n = 20 * (p + 1) * (p + 1) * (p + 1);
+        const int Np = (p + 1) * (p + 1) * (p + 1);
+        d.n = (sd.mode >= 3) ? red_n(Np) : 20 * Np;
         d.f = dm.toff[7 * e + 6];
     } else {
         // Schwarz system padded with decoupled unknowns to a multiple of 4
         d.n = asm_pad(dm.toff[7 * e + 6]);
         d.f = d.n;
     }
-    d.mrows = (sd.mode == 0) ? d.n + d.f : d.n;
+    d.mrows = (sd.mode == 0 || sd.mode == 3) ? d.n + d.f : d.n;
     d.ncols = d.n + d.f + 1;
     d.ld = e_ld(d.n, d.f);
     return d;
+}
+
+// Columns of the element system eliminated before the factored system's first one.
+__device__ inline int red_before(const DevMesh &dm, const SysDesc &sd, int e) {
+    const int p1 = dm.elem_p[e] + 1;
+    return sd.mode >= 3 ? 15 * p1 * p1 * p1 : 0;
 }
 
 template <typename T> __device__ inline void argmax_combine(T &v, int &r, T v2, int r2) {
@@ -333,7 +350,7 @@ __global__ void __launch_bounds__(kPT, sizeof(T) == 4 ? 4 : 2) k_panel(DevMesh d
             const bool bad = !(bv > T(0)) || !(bv < T(INFINITY)) || pr == INT_MAX;
             if (bad) {
                 pr = k;
-                if (info_k == 0) info_k = k + 1;
+                if (info_k == 0) info_k = k + 1 + red_before(dm, sd, e);
             }
             if (tid == 0) s_piv[j0 + jj] = pr;
             // exchange rows k and pr through LDS
@@ -1294,7 +1311,7 @@ __global__ void __launch_bounds__(256) k_extract(DevMesh dm, SysDesc sd, int e0,
     const ElemDims dd = elem_dims(dm, sd, e);
     const int f = dd.f;
     const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;  // i: row of S, j: column (0..f)
-    if (i0 >= f || j0 > f) return;
+    if (i0 >= f || j0 > f) return;  // (f = 0 where the element is not selected)
     const T *E = Ebase + (sd.off[e] - sd.off[e0]);
     double *out = SK + dm.SK_off[e];
     __shared__ double tile[32][33];
@@ -1755,7 +1772,7 @@ static int update_tile_rows(const hdg_ctx *ctx, int n) {
 // included when maxf_rows > 0).  ws: per-element workspace of a pair of
 // 128-column blocks, or with `persist` one per block (ws strides hold all of
 // them).  maxc: most columns of a system; maxrhs: most columns right of the n
-// pivot columns.
+// pivot columns; TMr: rows of the trailing update's tiles.
 //
 // The blocks go in pairs (A at K0, B at K0 + 128) so that the columns beyond
 // the pair receive one update with K = 256 instead of two with K = 128, which
@@ -1765,9 +1782,8 @@ static int update_tile_rows(const hdg_ctx *ctx, int n) {
 //   columns (A's update applied to B's gathered rows); far update, K = 256.
 template <typename T, int TAG>
 static int run_lu(const hdg_ctx *ctx, const SysDesc &sd, int e0, int ne, T *E, int *info, WS<T> ws, bool persist,
-                  int maxn, int maxm, int maxc, int maxrhs, int maxf_rows, hipStream_t s) {
+                  int maxn, int maxm, int maxc, int maxrhs, int maxf_rows, int TMr, hipStream_t s) {
     const DevMesh &dm = ctx->dm;
-    hipLaunchKernelGGL(k_zero_int, dim3((ne + 255) / 256), dim3(256), 0, s, info + e0, ne);
     const int R = (maxn + kPT - 1) / kPT;
     if (R > 5) return (int)hipErrorInvalidValue;
     auto block_ws_of = [&](int bi) {
@@ -1777,7 +1793,6 @@ static int run_lu(const hdg_ctx *ctx, const SysDesc &sd, int e0, int ne, T *E, i
         wb.i += (int64_t)slot * kWsInt;
         return wb;
     };
-    const int TMr = update_tile_rows(ctx, maxn);
     auto update = [&](int k0, int KW, int CB, int CW, int rows, int cols) {
         if (rows <= 0 || cols <= 0) return;
         const int tm = (rows + TMr - 1) / TMr, tn = (cols + kTN - 1) / kTN;
@@ -1853,24 +1868,92 @@ static void chunk_max(const hdg_ctx *ctx, int e0, int ne, int *maxn, int *maxf) 
     }
 }
 
-int launch_condense_fp64(const hdg_ctx *ctx, int e0, int ne, double *E, double *SK, int *info, void *work,
-                         hipStream_t s) {
-    int maxn, maxf, maxm = 0;
-    chunk_max(ctx, e0, ne, &maxn, &maxf);
-    for (int e = e0; e < e0 + ne; ++e) maxm = std::max(maxm, ctx->elem_n[e] + ctx->elem_f[e]);
-    const SysDesc sd{0, ctx->dm.E_off};
-    WS<double> ws{(double *)work, (int *)((char *)work + sizeof(double) * (size_t)ne * 2 * kWsDbl), 2 * kWsDbl,
-                  2 * kWsInt};
-    int err = run_lu<double, 0>(ctx, sd, e0, ne, E, info, ws, false, maxn, maxm, maxm + 1, maxf + 1, maxf, s);
-    if (err) return err;
-    hipLaunchKernelGGL(k_extract<double>, dim3((maxf + 1 + 31) / 32, (maxf + 31) / 32, ne), dim3(256), 0, s,
-                       ctx->dm, sd, e0, (const double *)E, SK);
-    return (int)hipGetLastError();
+static void zero_info(int *info, int ne, hipStream_t s) {
+    hipLaunchKernelGGL(k_zero_int, dim3((ne + 255) / 256), dim3(256), 0, s, info, ne);
 }
 
-size_t bordered_lu_work(const hdg_ctx *ctx, int ne) {
-    (void)ctx;
-    return 2 * (sizeof(double) * (size_t)ne * kWsDbl + sizeof(int) * (size_t)ne * kWsInt);
+// FP64 condensation in pieces of at most kPieceBytes of workspace, so that a
+// call over a whole mesh needs no more (285 elements at p = 4: more than one
+// panel workgroup per CU).  An element takes its K' and auxiliary region, two
+// blocks' LU records and a flag.
+constexpr int64_t kPieceBytes = (int64_t)9 << 29;  // 4.5 GiB
+static int64_t fp64_elem_bytes(const hdg_ctx *ctx, int e) {
+    return 8 * (ctx->kred_off[e + 1] - ctx->kred_off[e] + ctx->aux_off[e + 1] - ctx->aux_off[e] + 2 * kWsDbl) +
+           4 * (2 * kWsInt + 1);
+}
+constexpr int64_t kPieceRound = 5 * 256;
+
+size_t condense_fp64_work_bytes(const hdg_ctx *ctx, int e0, int ne) {
+    int64_t total = 0, most = 0;
+    for (int e = e0; e < e0 + ne; ++e) {
+        const int64_t b = fp64_elem_bytes(ctx, e);
+        total += b;
+        most = std::max(most, b);
+    }
+    return (size_t)((std::min(total, std::max(most, kPieceBytes)) + kPieceRound + 255) / 256 * 256);
+}
+
+static size_t r256(size_t b) { return (b + 255) / 256 * 256; }
+
+// One piece: the gradient unknowns of every element whose system has the
+// structure of k_reduce.hip are eliminated through the mass matrix and the
+// reduced system is factored; the others (none, where the systems were just
+// formed) take the dense LU in place.
+static int condense_piece(const hdg_ctx *ctx, int e0, int ne, bool formed, double *E, double *SK, int *info, void *work,
+                          hipStream_t s) {
+    int maxn = 0, maxf = 0, maxm = 0, maxu = 0, maxr = 0;
+    for (int e = e0; e < e0 + ne; ++e) {
+        maxn = std::max(maxn, ctx->elem_n[e]);
+        maxf = std::max(maxf, ctx->elem_f[e]);
+        maxm = std::max(maxm, ctx->elem_n[e] + ctx->elem_f[e]);
+        const int nu = red_n(ctx->elem_n[e] / 20);
+        maxu = std::max(maxu, nu);
+        maxr = std::max(maxr, nu + ctx->elem_f[e]);
+    }
+    char *p = (char *)work;
+    auto take = [&](size_t bytes) {
+        char *at = p;
+        p += r256(bytes);
+        return at;
+    };
+    RedBuf rb;
+    rb.k_off = ctx->dm.kred_off;
+    rb.aux_off = ctx->dm.aux_off;
+    rb.K = (double *)take(8 * (size_t)(ctx->kred_off[e0 + ne] - ctx->kred_off[e0]));
+    rb.aux = (double *)take(8 * (size_t)(ctx->aux_off[e0 + ne] - ctx->aux_off[e0]));
+    WS<double> ws;
+    ws.d = (double *)take(8 * (size_t)ne * 2 * kWsDbl);
+    ws.i = (int *)take(4 * (size_t)ne * 2 * kWsInt);
+    rb.sel = (int *)take(4 * (size_t)ne);
+    ws.ds = 2 * kWsDbl;
+    ws.is = 2 * kWsInt;
+    const int TMr = update_tile_rows(ctx, maxn);  // the element systems' setting, reduced or not
+    launch_red_init(ne, true, info + e0, rb.sel, s);
+    int err = launch_red_eliminate(ctx, rb, e0, ne, formed, true, E, info, s);
+    if (err) return err;
+    const SysDesc sr{3, rb.k_off, rb.sel, e0, 1};
+    if ((err = run_lu<double, 0>(ctx, sr, e0, ne, rb.K, info, ws, false, maxu, maxr, maxr + 1, maxf + 1, maxf, TMr, s)))
+        return err;
+    if ((err = launch_red_writeback(ctx, rb, e0, ne, E, SK, s))) return err;
+    if (formed) return 0;
+    const SysDesc sd{0, ctx->dm.E_off, rb.sel, e0, 0};
+    if ((err = run_lu<double, 0>(ctx, sd, e0, ne, E, info, ws, false, maxn, maxm, maxm + 1, maxf + 1, maxf, TMr, s))) return err;
+    hipLaunchKernelGGL(k_extract<double>, dim3((maxf + 1 + 31) / 32, (maxf + 31) / 32, ne), dim3(256), 0, s,
+                       ctx->dm, sd, e0, (const double *)E, SK);
+    return launch_red_clear_mark(ctx, e0, ne, rb.sel, E, s);
+}
+
+int launch_condense_fp64(const hdg_ctx *ctx, int e0, int ne, bool formed, double *E, double *SK, int *info, void *work,
+                         hipStream_t s) {
+    for (int a = e0; a < e0 + ne;) {
+        int b = a;
+        int64_t bytes = 0;
+        while (b < e0 + ne && (b == a || bytes + fp64_elem_bytes(ctx, b) <= kPieceBytes)) bytes += fp64_elem_bytes(ctx, b++);
+        const int err = condense_piece(ctx, a, b - a, formed, E + (ctx->E_off[a] - ctx->E_off[e0]), SK, info, work, s);
+        if (err) return err;
+        a = b;
+    }
+    return (int)hipGetLastError();
 }
 
 template <typename T> static WS<T> block_ws(WS<T> ws, int k0) {
@@ -1940,12 +2023,14 @@ int run_asm_inversion(const hdg_ctx *ctx, int prec, void *sys, int *info, void *
     int *wi = (int *)((char *)iwork + ((es * (size_t)ne * nblk * kWsDbl + 255) / 256 * 256));
     if (prec == HDG_FP64) {
         WS<double> ws{(double *)iwork, wi, (int64_t)nblk * kWsDbl, (int64_t)nblk * kWsInt};
-        int err = run_lu<double, 1>(ctx, sd, 0, ne, (double *)sys, info, ws, true, m, m, 2 * m + 1, m + 1, 0, s);
+        zero_info(info, ne, s);
+        int err = run_lu<double, 1>(ctx, sd, 0, ne, (double *)sys, info, ws, true, m, m, 2 * m + 1, m + 1, 0, update_tile_rows(ctx, m), s);
         if (err) return err;
         run_back_solve<double, 1>(ctx, sd, 0, ne, (double *)sys, ws, m, m + 1, s);
     } else {
         WS<float> ws{(float *)iwork, wi, (int64_t)nblk * kWsDbl, (int64_t)nblk * kWsInt};
-        int err = run_lu<float, 3>(ctx, sd, 0, ne, (float *)sys, info, ws, true, m, m, 2 * m + 1, m + 1, 0, s);
+        zero_info(info, ne, s);
+        int err = run_lu<float, 3>(ctx, sd, 0, ne, (float *)sys, info, ws, true, m, m, 2 * m + 1, m + 1, 0, update_tile_rows(ctx, m), s);
         if (err) return err;
         run_back_solve<float, 3>(ctx, sd, 0, ne, (float *)sys, ws, m, m + 1, s);
     }
@@ -1958,7 +2043,6 @@ struct MixedLayout {
     size_t m_off, x_off, wd_off, wi_off, total;
     int nblk;
 };
-static size_t r256(size_t b) { return (b + 255) / 256 * 256; }
 static MixedLayout mixed_layout(const hdg_ctx *ctx, int e0, int ne) {
     int maxn, maxf;
     chunk_max(ctx, e0, ne, &maxn, &maxf);
@@ -2015,11 +2099,14 @@ int launch_condense_fast(const hdg_ctx *ctx, int e0, int ne, double *E, double *
     WS<float> ws{wd, wi, 2 * kWsDbl, 2 * kWsInt};
     const dim3 grid(64, ne);
     hipLaunchKernelGGL(k_full_to32, grid, dim3(256), 0, s, ctx->dm, e0, (const double *)E, F);
-    int err = run_lu<float, 4>(ctx, sd, e0, ne, F, info, ws, false, maxn, maxm, maxm + 1, maxf + 1, maxf, s);
+    const int TMr = update_tile_rows(ctx, maxn);
+    zero_info(info + e0, ne, s);
+    int err = run_lu<float, 4>(ctx, sd, e0, ne, F, info, ws, false, maxn, maxm, maxm + 1, maxf + 1, maxf, TMr, s);
     if (err) return err;
     hipLaunchKernelGGL(k_extract<float>, dim3((maxf + 1 + 31) / 32, (maxf + 31) / 32, ne), dim3(256), 0, s,
                        ctx->dm, sd, e0, (const float *)F, SK);
     hipLaunchKernelGGL(k_interior_to64, grid, dim3(256), 0, s, ctx->dm, e0, (const float *)F, E);
+    if ((err = launch_red_clear_mark(ctx, e0, ne, nullptr, E, s))) return err;
     return (int)hipGetLastError();
 }
 
@@ -2042,7 +2129,9 @@ int launch_condense_mixed(const hdg_ctx *ctx, int e0, int ne, int refine, double
     const dim3 elem_grid(64, ne);
     hipLaunchKernelGGL(k_to32, elem_grid, dim3(256), 0, s, dm, e0, (const double *)E, M);
     // FP32 LU of A with the forward substitution of [B | R_qu] carried along, then X_0
-    int err = run_lu<float, 2>(ctx, sd, e0, ne, M, info, ws, true, maxn, maxn, maxn + maxf + 1, maxf + 1, 0, s);
+    const int TMr = update_tile_rows(ctx, maxn);
+    zero_info(info + e0, ne, s);
+    int err = run_lu<float, 2>(ctx, sd, e0, ne, M, info, ws, true, maxn, maxn, maxn + maxf + 1, maxf + 1, 0, TMr, s);
     if (err) return err;
     back_solve();
     hipLaunchKernelGGL(k_xupdate<0>, elem_grid, dim3(256), 0, s, dm, e0, (const float *)M, X, E);

@@ -679,13 +679,20 @@ __global__ void __launch_bounds__(kRT) k_recover(DevMesh dm, int e0, int backsub
         for (int t = threadIdx.x; t < len; t += blockDim.x) sd[to[lf] + t] = dUhat[dm.face_off[F] + t];
     }
     __syncthreads();
+    // the form of the gradient rows (uniform): [I | Y_j | r] under the mark, then only
+    // the conserved rows have a triangle to solve with
+    bool reduced = backsub != 0;
+    if (backsub)
+        for (int i = 0; i < kRedMarkN; ++i)
+            reduced &= (unsigned long long)__double_as_longlong(E[(int64_t)n * ld + i]) == red_mark(i);
+    const int lo = reduced ? 15 * Np : 0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     auto wave_sum = [&](double v) {
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
         return v;
     };
     // y = Y_r + Y_B dUh, kRQ rows per wave at a time
-    for (int i = kRQ * wave; i < n; i += kRQ * kRW) {
+    for (int i = lo + kRQ * wave; i < n; i += kRQ * kRW) {
         double acc[kRQ];
 #pragma unroll
         for (int q = 0; q < kRQ; ++q) acc[q] = 0.0;
@@ -722,8 +729,8 @@ __global__ void __launch_bounds__(kRT) k_recover(DevMesh dm, int e0, int backsub
         // left-looking by 64-row blocks from the bottom: a block's rows first take
         // the solved part, y[r] -= U[r][i1:n] x[i1:n] (one dot product per row,
         // kRQ rows per wave), then wave 0 solves the diagonal block
-        for (int i1 = n; i1 > 0; i1 -= kRB) {
-            const int i0 = max(0, i1 - kRB), nb = i1 - i0;
+        for (int i1 = n; i1 > lo; i1 -= kRB) {
+            const int i0 = max(lo, i1 - kRB), nb = i1 - i0;
             for (int r = i0 + kRQ * wave; r < i1; r += kRQ * kRW) {
                 double acc[kRQ];
 #pragma unroll
@@ -771,6 +778,38 @@ __global__ void __launch_bounds__(kRT) k_recover(DevMesh dm, int e0, int backsub
             }
             __syncthreads();
         }
+    }
+    if (reduced) {
+        // q_(c,j) = r_(c,j) + H_j dUh_c - G_j u_c: rows of component 0 serve all five
+        // components, one wave per (j, node)
+        const int w = f / 5;
+        for (int r = wave; r < 3 * Np; r += kRW) {
+            const double *row = E + (int64_t)r * ld;
+            double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+            for (int k = lane; k < Np; k += 64) {
+                const double g = row[15 * Np + k];
+#pragma unroll
+                for (int c = 0; c < 5; ++c) acc[c] -= g * sy[(15 + c) * Np + k];
+            }
+            for (int t = lane; t < w; t += 64) {
+                int lf = 0;
+                while (5 * t >= to[lf + 1]) ++lf;
+                const int nfp = (to[lf + 1] - to[lf]) / 5, a = to[lf] + t - to[lf] / 5;
+                const double h = row[n + a];
+#pragma unroll
+                for (int c = 0; c < 5; ++c) acc[c] += h * sd[a + c * nfp];
+            }
+#pragma unroll
+            for (int c = 0; c < 5; ++c) acc[c] = wave_sum(acc[c]);
+            const int j = r / Np, i = r % Np;
+#pragma unroll
+            for (int c = 0; c < 5; ++c)
+                if (lane == c) {
+                    const int q = (3 * c + j) * Np + i;
+                    sy[q] = acc[c] + E[(int64_t)q * ld + n + f];
+                }
+        }
+        __syncthreads();
     }
     double *out = dQU + 20 * dm.node_off[e];
     for (int i = threadIdx.x; i < n; i += blockDim.x) out[i] = -sy[i];
