@@ -274,7 +274,10 @@ int hdg_get_update_tile(const hdg_ctx *ctx, int n);
  *  HDG_MIXED: A is factorised in FP32 in the workspace, X = A^{-1}[B | R_qu] is
  *    refined `refine_steps` (>= 1) times with FP64 residuals [B|R_qu] - A X, S^K
  *    and g^K are formed with FP64 products; X is then stored in place of
- *    [B | R_qu] (rows 0..n-1, columns n..n+f).
+ *    [B | R_qu] (rows 0..n-1, columns n..n+f).  Where the gradient rows have the
+ *    structure above, the gradient is first eliminated in FP64, the FP32
+ *    factorisation and the refinement take the remaining 5 N_p columns, and the
+ *    gradient rows of X follow from them in FP64.
  * SK (all elements, element e at SK_off[e]) receives [S^K | g^K].
  * info[e] (device, all elements) = 0, or k+1 if the k-th pivot was zero or
  * not finite (the element's outputs are then undefined; the other elements'

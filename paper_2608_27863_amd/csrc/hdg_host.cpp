@@ -300,6 +300,9 @@ int hdg_create(const hdg_mesh_desc *m, const hdg_phys *phys, hdg_ctx **out) {
     ctx->x_off.assign(ne + 1, 0);
     ctx->kred_off.assign(ne + 1, 0);
     ctx->aux_off.assign(ne + 1, 0);
+    ctx->mk_off.assign(ne + 1, 0);
+    ctx->m32r_off.assign(ne + 1, 0);
+    ctx->maux_off.assign(ne + 1, 0);
     ctx->vgeo_off.assign(ne + 1, 0);
     ctx->fgeo_off.assign(6 * ne + 1, 0);
     ctx->toff.assign(7 * ne, 0);
@@ -339,7 +342,11 @@ int hdg_create(const hdg_mesh_desc *m, const hdg_phys *phys, hdg_ctx **out) {
         const int fe = hdg::asm_pad(f);  // Schwarz system size
         ctx->asmsys_off[e + 1] = ctx->asmsys_off[e] + (int64_t)fe * hdg::e_ld(fe, fe);
         ctx->tloc_off[e + 1] = ctx->tloc_off[e] + f;
-        ctx->m32_off[e + 1] = ctx->m32_off[e] + (int64_t)n * hdg::e_ld(n, f);
+        const int64_t ksz = hdg::red_k_size(Np, f);
+        ctx->m32_off[e + 1] = ctx->m32_off[e] + (std::max((int64_t)n * hdg::e_ld(n, f), 3 * ksz) + 31) / 32 * 32;
+        ctx->mk_off[e] = ctx->m32_off[e] / 2;
+        ctx->m32r_off[e] = ctx->m32_off[e] + 2 * ksz;
+        ctx->maux_off[e] = ctx->x_off[e] + ((int64_t)hdg::red_n(Np) * hdg::x_ld(f) + 15) / 16 * 16;
         ctx->x_off[e + 1] = ctx->x_off[e] + (int64_t)n * hdg::x_ld(f);
         ctx->kred_off[e + 1] = ctx->kred_off[e] + hdg::red_k_size(Np, f);
         ctx->aux_off[e + 1] = ctx->aux_off[e] + hdg::red_aux_size(Np, f);
@@ -523,6 +530,9 @@ int hdg_create(const hdg_mesh_desc *m, const hdg_phys *phys, hdg_ctx **out) {
     UP(ctx->x_off, x_off);
     UP(ctx->kred_off, kred_off);
     UP(ctx->aux_off, aux_off);
+    UP(ctx->mk_off, mk_off);
+    UP(ctx->m32r_off, m32r_off);
+    UP(ctx->maux_off, maux_off);
     UP(ctx->vgeo_off, vgeo_off);
     UP(ctx->fgeo_off, fgeo_off);
     UP(vgeo, vgeo);
@@ -662,7 +672,7 @@ static int condense_any(hdg_ctx *ctx, int prec, int refine_steps, int e0, int ne
         return dev_status(hdg::launch_condense_fp64(ctx, e0, ne, formed, E, SK, info, work, (hipStream_t)stream));
     if (prec == HDG_MIXED_FAST)
         return dev_status(hdg::launch_condense_fast(ctx, e0, ne, E, SK, info, work, (hipStream_t)stream));
-    return dev_status(hdg::launch_condense_mixed(ctx, e0, ne, refine_steps, E, SK, info, work, (hipStream_t)stream));
+    return dev_status(hdg::launch_condense_mixed(ctx, e0, ne, refine_steps, formed, E, SK, info, work, (hipStream_t)stream));
 }
 
 int hdg_condense(hdg_ctx *ctx, int prec, int refine_steps, int e0, int ne, double *E, double *SK, int *info,

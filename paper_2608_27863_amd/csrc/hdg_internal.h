@@ -54,10 +54,15 @@ struct DevMesh {
     const int64_t *qp_off;     // [n_elem+1]
     const int64_t *asmsys_off; // [n_elem+1] Schwarz inversion systems [S_r | I] (m x ld entries, m = asm_pad(f))
     const int64_t *tloc_off;   // [n_elem+1] prefix sums of f_e (element-local trace vectors)
-    const int64_t *m32_off;    // [n_elem+1] FP32 interior systems [A | B R_qu] (n x e_ld floats)
+    const int64_t *m32_off;    // [n_elem+1] FP32 interior systems [A | B R_qu] (n x e_ld floats, or K' and its
+                               // interior rows in FP32 where that is more)
     const int64_t *x_off;      // [n_elem+1] X = A^{-1}[B | R_qu] (n x x_ld doubles)
     const int64_t *kred_off;   // [n_elem+1] reduced systems K' (red_k_size)
     const int64_t *aux_off;    // [n_elem+1] their auxiliary regions (red_aux_size)
+    // the mixed path's reduced systems inside the element's other regions
+    const int64_t *mk_off;     // [n_elem+1] K', doubles: m32_off / 2
+    const int64_t *m32r_off;   // [n_elem+1] its interior rows in FP32, floats
+    const int64_t *maux_off;   // [n_elem+1] auxiliary regions, doubles: in the X region
     const int64_t *vgeo_off;   // [n_elem+1]  volume geometry: [10][Nq] = W, G00..G22 (G = J^{-1})
     const int64_t *fgeo_off;   // [n_elem*6+1] face geometry: [4][Nqf] = w N_x, w N_y, w N_z, w |N|
     const double *vgeo;
@@ -137,7 +142,8 @@ struct hdg_ctx {
     bool face_cols_aligned = true, asm_cols_aligned64 = true, asm_cols_aligned32 = true;
     std::vector<int> elem_p, face_p, elem_face, face_elem, face_bc, toff, elem_n, elem_f;
     std::vector<int64_t> node_off, face_off, E_off, SK_off, asm_off, qp_off, vgeo_off, fgeo_off, asmsys_off,
-        tloc_off, m32_off, x_off, kred_off, aux_off;
+        tloc_off, m32_off, x_off, kred_off, aux_off, mk_off,
+        m32r_off, maux_off;
     std::vector<int64_t> bsr_row_ptr64, bsr_col64, bsr_val_off;
     std::vector<int> bsr_row_ptr, bsr_col;
     hdg::DevMesh dm{};
@@ -159,8 +165,9 @@ void launch_red_init(int ne, bool structured, int *info, int *sel, hipStream_t s
 int launch_red_eliminate(const hdg_ctx *ctx, const RedBuf &rb, int e0, int ne, bool checked, bool write, double *E,
                          int *info, hipStream_t s);
 int launch_red_writeback(const hdg_ctx *ctx, const RedBuf &rb, int e0, int ne, double *E, double *SK, hipStream_t s);
+int launch_red_xq(const hdg_ctx *ctx, const RedBuf &rb, int e0, int ne, const double *Xu, double *E, hipStream_t s);
 int launch_red_clear_mark(const hdg_ctx *ctx, int e0, int ne, const int *sel, double *E, hipStream_t s);
-int launch_condense_mixed(const hdg_ctx *ctx, int e0, int ne, int refine, double *E, double *SK,
+int launch_condense_mixed(const hdg_ctx *ctx, int e0, int ne, int refine, bool formed, double *E, double *SK,
                           int *info, void *work, hipStream_t s);
 size_t condense_mixed_work_bytes(const hdg_ctx *ctx, int e0, int ne);
 int launch_condense_fast(const hdg_ctx *ctx, int e0, int ne, double *E, double *SK, int *info, void *work,

@@ -1,6 +1,12 @@
 // Static condensation of the element systems (eqs. local-elimination,
 // schur-trace), in FP64 and in mixed precision.
 //
+// Where an element's gradient rows have the structure of eq. hdg-grad, k_reduce.hip
+// first eliminates them through the mass matrix, and what follows runs on the
+// reduced system K' of 5 N_p interior rows and f trace rows; any other system is
+// taken as it is.  8^3 elements at p = 4: whole Newton step 352.8 -> 105.6 ms (FP64);
+// p = 3, mixed: 73.3 -> 30.3 ms.
+//
 // FP64.  E^K = [[A B R_qu],[C D R_uh]] (row-major) is reduced by a right-looking
 // blocked LU with partial pivoting over the first n columns, pivots taken
 // among the interior rows 0..n-1 only, the elimination carried through the
@@ -1525,23 +1531,33 @@ __global__ void __launch_bounds__(256, 2) k_lbsolve(DevMesh dm, SysDesc sd, int 
 }
 
 // ---------------------------------------------------- mixed precision only
-__device__ inline void mixed_dims(const DevMesh &dm, int e, int &n, int &f, int64_t &ld, int64_t &ldx) {
-    const int p = dm.elem_p[e];
-    n = 20 * (p + 1) * (p + 1) * (p + 1);
+// The FP64 systems of the mixed path: element systems (red = 0) or reduced systems
+// K' (red = 1, n = red_n), those of the elements with sel[e - e0] == red.
+struct MixSys {
+    int red;
+    const int *sel;
+    const int64_t *off;    // [n_elem+1] FP64 systems
+    const int64_t *m_off;  // [n_elem+1] their interior rows in FP32
+};
+__device__ inline bool mixed_dims(const DevMesh &dm, const MixSys &ms, int e, int e0, int &n, int &f, int64_t &ld,
+                                  int64_t &ldx) {
+    const int p = dm.elem_p[e], Np = (p + 1) * (p + 1) * (p + 1);
+    n = ms.red ? red_n(Np) : 20 * Np;
     f = dm.toff[7 * e + 6];
     ld = e_ld(n, f);
     ldx = x_ld(f);
+    return ms.sel[e - e0] == ms.red;
 }
 
 // FP32 copy of the interior rows [A | B R_qu] (padding columns included).
-__global__ void __launch_bounds__(256) k_to32(DevMesh dm, int e0, const double *__restrict__ Ebase,
+__global__ void __launch_bounds__(256) k_to32(DevMesh dm, MixSys ms, int e0, const double *__restrict__ Ebase,
                                               float *__restrict__ Mbase) {
     const int e = e0 + blockIdx.y;
     int n, f;
     int64_t ld, ldx;
-    mixed_dims(dm, e, n, f, ld, ldx);
-    const MF<double>::v2 *E = (const MF<double>::v2 *)(Ebase + (dm.E_off[e] - dm.E_off[e0]));
-    MF<float>::v2 *M = (MF<float>::v2 *)(Mbase + (dm.m32_off[e] - dm.m32_off[e0]));
+    if (!mixed_dims(dm, ms, e, e0, n, f, ld, ldx)) return;
+    const MF<double>::v2 *E = (const MF<double>::v2 *)(Ebase + (ms.off[e] - ms.off[e0]));
+    MF<float>::v2 *M = (MF<float>::v2 *)(Mbase + (ms.m_off[e] - ms.m_off[e0]));
     const int64_t total = (int64_t)n * ld / 2;
     for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
         const MF<double>::v2 v = E[i];
@@ -1550,25 +1566,29 @@ __global__ void __launch_bounds__(256) k_to32(DevMesh dm, int e0, const double *
 }
 
 // X (FP64, n x x_ld) = the right-hand columns of the FP32 system (MODE 0), or
-// X += them (MODE 1), or X += them and X is also written into E's [B | R_qu]
-// columns (MODE 2, the last refinement step).
+// X += them (MODE 1), or X += them and X is also written into the [B | R_qu]
+// columns of the element system Ebase (MODE 2, the last refinement step; the
+// conserved rows where X belongs to a reduced system).
 template <int MODE>
-__global__ void __launch_bounds__(256) k_xupdate(DevMesh dm, int e0, const float *__restrict__ Mbase,
+__global__ void __launch_bounds__(256) k_xupdate(DevMesh dm, MixSys ms, int e0, const float *__restrict__ Mbase,
                                                  double *__restrict__ Xbase, double *__restrict__ Ebase) {
     const int e = e0 + blockIdx.y;
     int n, f;
     int64_t ld, ldx;
-    mixed_dims(dm, e, n, f, ld, ldx);
-    const float *M = Mbase + (dm.m32_off[e] - dm.m32_off[e0]);
+    if (!mixed_dims(dm, ms, e, e0, n, f, ld, ldx)) return;
+    const int p1 = dm.elem_p[e] + 1, nn = 20 * p1 * p1 * p1;
+    const int rbeg = ms.red ? nn / 4 * 3 : 0, rows = nn - rbeg;  // E's rows that X belongs to
+    const int64_t lde = e_ld(nn, f);
+    const float *M = Mbase + (ms.m_off[e] - ms.m_off[e0]);
     double *X = Xbase + (dm.x_off[e] - dm.x_off[e0]);
-    double *E = Ebase + (dm.E_off[e] - dm.E_off[e0]);
+    double *E = Ebase + (dm.E_off[e] - dm.E_off[e0]) + rbeg * lde + nn;
     for (int r = blockIdx.x; r < n; r += gridDim.x)
         for (int c = threadIdx.x; c < ldx; c += 256) {
             const double m = (c <= f) ? (double)M[(int64_t)r * ld + n + c] : 0.0;
             const int64_t i = (int64_t)r * ldx + c;
             const double x = (MODE == 0) ? m : X[i] + m;
             X[i] = x;
-            if (MODE == 2 && c <= f) E[(int64_t)r * ld + n + c] = x;
+            if (MODE == 2 && c <= f && r < rows) E[(int64_t)r * lde + c] = x;
         }
 }
 
@@ -1592,7 +1612,7 @@ __device__ inline unsigned a_field_mask(int fr) {
 //   OP 1 (Schur complement): [S^K | -g^K] = [D | R_uh] - C X over rows n..n+f-1,
 //        written to SK column-major with the last column negated.
 template <int OP>
-__global__ void __launch_bounds__(256, 2) k_gemm64(DevMesh dm, int e0, int ne, int tiles_m, int tiles_n,
+__global__ void __launch_bounds__(256, 2) k_gemm64(DevMesh dm, MixSys ms, int e0, int ne, int tiles_m, int tiles_n,
                                                    const double *__restrict__ Ebase, const double *__restrict__ Xbase,
                                                    float *__restrict__ Mbase, double *__restrict__ SK) {
     typedef UpdCfg<double> C;
@@ -1603,12 +1623,12 @@ __global__ void __launch_bounds__(256, 2) k_gemm64(DevMesh dm, int e0, int ne, i
     const int e = e0 + el;
     int n, f;
     int64_t ld, ldx;
-    mixed_dims(dm, e, n, f, ld, ldx);
+    if (!mixed_dims(dm, ms, e, e0, n, f, ld, ldx)) return;
     const int Mrows = (OP == 0) ? n : f, N = f + 1, K = n;
     const int r0 = (t / tiles_n) * kTM, c0 = (t % tiles_n) * kTN;
     if (r0 >= Mrows || c0 >= N) return;
     const int arow0 = (OP == 0) ? 0 : n;
-    const double *E = Ebase + (dm.E_off[e] - dm.E_off[e0]);
+    const double *E = Ebase + (ms.off[e] - ms.off[e0]);
     const double *X = Xbase + (dm.x_off[e] - dm.x_off[e0]);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = (wave >> 1) * 64, wc = (wave & 1) * 64;
@@ -1652,10 +1672,11 @@ __global__ void __launch_bounds__(256, 2) k_gemm64(DevMesh dm, int e0, int ne, i
             *(v16 *)&sB[buf][C::KPQ * q + bk][bc] = b;
         }
     };
-    // K chunks this tile needs
-    const int Np = n / 20;
+    // K chunks this tile needs (a reduced system has no zero blocks to skip)
+    const bool skip = OP == 0 && !ms.red;
+    const int Np = (n + 19) / 20;
     unsigned rmask = 0xFFFFFu;
-    if (OP == 0) {
+    if (skip) {
         rmask = 0;
         const int fr1 = (min(r0 + kTM, Mrows) - 1) / Np;
         for (int fr = r0 / Np; fr <= fr1; ++fr) rmask |= a_field_mask(fr);
@@ -1678,7 +1699,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm64(DevMesh dm, int e0, int ne, i
     for (int bi = 0; bi < 4; ++bi) {
         const int lo = r0 + wr + 16 * bi, hi = min(lo + 15, Mrows - 1);
         bmask[bi] = 0;
-        if (OP != 0) bmask[bi] = 0xFFFFFu;
+        if (!skip) bmask[bi] = 0xFFFFFu;
         else if (lo < Mrows)
             for (int fr = lo / Np; fr <= hi / Np; ++fr) bmask[bi] |= a_field_mask(fr);
     }
@@ -1747,7 +1768,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm64(DevMesh dm, int e0, int ne, i
                 if (c >= N) continue;
                 const double v = cv[j][bj] - acc[bi][bj][j];
                 if (OP == 0) {
-                    float *M = Mbase + (dm.m32_off[e] - dm.m32_off[e0]);
+                    float *M = Mbase + (ms.m_off[e] - ms.m_off[e0]);
                     M[(int64_t)r * ld + n + c] = (float)v;
                 } else {
                     SK[dm.SK_off[e] + (int64_t)c * f + r] = (c == f) ? -v : v;
@@ -1979,7 +2000,7 @@ static void run_back_solve(const hdg_ctx *ctx, const SysDesc &sd, int e0, int ne
 // recorded permutations and the pairing of the blocks as the factorisation did.
 template <typename T, int TAG>
 static void run_forward_solve(const hdg_ctx *ctx, const SysDesc &sd, int e0, int ne, T *E, WS<T> ws, int maxn,
-                              int rhs_cols, hipStream_t s) {
+                              int rhs_cols, int TMr, hipStream_t s) {
     const DevMesh &dm = ctx->dm;
     const int tn = (rhs_cols + kTN - 1) / kTN;
     const int tiles = (rhs_cols + kBC - 1) / kBC;
@@ -1991,7 +2012,6 @@ static void run_forward_solve(const hdg_ctx *ctx, const SysDesc &sd, int e0, int
                                K0 + kNBO, 1, 0, 0, tiles, E, block_ws(ws, K0 + kNBO));
         const int rows = maxn - K0 - 2 * kNBO;
         if (rows > 0) {
-            const int TMr = update_tile_rows(ctx, maxn);
             const int tm = (rows + TMr - 1) / TMr;
             if (TMr == 256)
                 hipLaunchKernelGGL((k_update<T, TAG, kRangeFwd, 256>), dim3(xcd_grid(ne, tm * tn)), dim3(512), 0, s, dm,
@@ -2038,9 +2058,9 @@ int run_asm_inversion(const hdg_ctx *ctx, int prec, void *sys, int *info, void *
 }
 
 // ---------------------------------------------------------------- mixed path
-// Workspace of a chunk: FP32 systems | X (FP64) | per-block LU records (FP32 values, ints).
+// Workspace of a chunk: FP32 systems | X (FP64) | per-block LU records (FP32 values, ints) | flags.
 struct MixedLayout {
-    size_t m_off, x_off, wd_off, wi_off, total;
+    size_t m_off, x_off, wd_off, wi_off, sel_off, total;
     int nblk;
 };
 static MixedLayout mixed_layout(const hdg_ctx *ctx, int e0, int ne) {
@@ -2052,7 +2072,8 @@ static MixedLayout mixed_layout(const hdg_ctx *ctx, int e0, int ne) {
     L.x_off = L.m_off + r256(sizeof(float) * (size_t)(ctx->m32_off[e0 + ne] - ctx->m32_off[e0]));
     L.wd_off = L.x_off + r256(sizeof(double) * (size_t)(ctx->x_off[e0 + ne] - ctx->x_off[e0]));
     L.wi_off = L.wd_off + r256(sizeof(float) * (size_t)ne * L.nblk * kWsDbl);
-    L.total = L.wi_off + r256(sizeof(int) * (size_t)ne * L.nblk * kWsInt);
+    L.sel_off = L.wi_off + r256(sizeof(int) * (size_t)ne * L.nblk * kWsInt);
+    L.total = L.sel_off + r256(sizeof(int) * (size_t)ne);
     return L;
 }
 
@@ -2110,48 +2131,64 @@ int launch_condense_fast(const hdg_ctx *ctx, int e0, int ne, double *E, double *
     return (int)hipGetLastError();
 }
 
-int launch_condense_mixed(const hdg_ctx *ctx, int e0, int ne, int refine, double *E, double *SK, int *info,
+// The elements with the structure of k_reduce.hip go through their reduced
+// systems: the FP32 factorisation and the refinement then have 5 N_p columns, and
+// the gradient rows of X follow in FP64 from the conserved ones.  K' and its FP32
+// interior rows lie in the element's own FP32 region (m32_off is sized for
+// either), its X and auxiliary region in the element's X region.
+int launch_condense_mixed(const hdg_ctx *ctx, int e0, int ne, int refine, bool formed, double *E, double *SK, int *info,
                           void *work, hipStream_t s) {
     const DevMesh &dm = ctx->dm;
-    int maxn, maxf;
+    int maxn, maxf, maxu = 0;
     chunk_max(ctx, e0, ne, &maxn, &maxf);
+    for (int e = e0; e < e0 + ne; ++e) maxu = std::max(maxu, red_n(ctx->elem_n[e] / 20));
     const MixedLayout L = mixed_layout(ctx, e0, ne);
     char *wb = (char *)work;
     float *M = (float *)(wb + L.m_off);
     double *X = (double *)(wb + L.x_off);
+    int *sel = (int *)(wb + L.sel_off);
     WS<float> ws{(float *)(wb + L.wd_off), (int *)(wb + L.wi_off), (int64_t)L.nblk * kWsDbl,
                  (int64_t)L.nblk * kWsInt};
-    const SysDesc sd{2, dm.m32_off};
-    const int rhs_cols = maxf + 1;
-    auto back_solve = [&]() { run_back_solve<float, 2>(ctx, sd, e0, ne, M, ws, maxn, rhs_cols, s); };
-    auto forward_solve = [&]() { run_forward_solve<float, 2>(ctx, sd, e0, ne, M, ws, maxn, rhs_cols, s); };
-    const int tn = (rhs_cols + kTN - 1) / kTN;
+    const int rhs_cols = maxf + 1, tn = (rhs_cols + kTN - 1) / kTN, TMr = update_tile_rows(ctx, maxn);
     const dim3 elem_grid(64, ne);
-    hipLaunchKernelGGL(k_to32, elem_grid, dim3(256), 0, s, dm, e0, (const double *)E, M);
-    // FP32 LU of A with the forward substitution of [B | R_qu] carried along, then X_0
-    const int TMr = update_tile_rows(ctx, maxn);
-    zero_info(info + e0, ne, s);
-    int err = run_lu<float, 2>(ctx, sd, e0, ne, M, info, ws, true, maxn, maxn, maxn + maxf + 1, maxf + 1, 0, TMr, s);
+    // FP32 LU of the interior with the forward substitution of [B | R] carried along,
+    // X_0, the refinement steps, then [S^K | g^K]
+    auto solve = [&](const MixSys &ms, const SysDesc &sd, const double *sys, float *M32, int nmax) -> int {
+        hipLaunchKernelGGL(k_to32, elem_grid, dim3(256), 0, s, dm, ms, e0, sys, M32);
+        const int err =
+            run_lu<float, 2>(ctx, sd, e0, ne, M32, info, ws, true, nmax, nmax, nmax + maxf + 1, maxf + 1, 0, TMr, s);
+        if (err) return err;
+        run_back_solve<float, 2>(ctx, sd, e0, ne, M32, ws, nmax, rhs_cols, s);
+        hipLaunchKernelGGL(k_xupdate<0>, elem_grid, dim3(256), 0, s, dm, ms, e0, (const float *)M32, X, E);
+        const int tm_r = (nmax + kTM - 1) / kTM;
+        for (int it = 0; it < refine; ++it) {
+            // R = [B | R] - A X in FP64 (into the FP32 right-hand columns), d = A^{-1} R, X += d
+            hipLaunchKernelGGL(k_gemm64<0>, dim3(xcd_grid(ne, tm_r * tn)), dim3(256), 0, s, dm, ms, e0, ne, tm_r, tn,
+                               sys, (const double *)X, M32, SK);
+            run_forward_solve<float, 2>(ctx, sd, e0, ne, M32, ws, nmax, rhs_cols, TMr, s);
+            run_back_solve<float, 2>(ctx, sd, e0, ne, M32, ws, nmax, rhs_cols, s);
+            if (it + 1 < refine)
+                hipLaunchKernelGGL(k_xupdate<1>, elem_grid, dim3(256), 0, s, dm, ms, e0, (const float *)M32, X, E);
+            else
+                hipLaunchKernelGGL(k_xupdate<2>, elem_grid, dim3(256), 0, s, dm, ms, e0, (const float *)M32, X, E);
+        }
+        // [S^K | -g^K] = [D | R_uh] - C X (FP64), stored as [S^K | g^K]
+        const int tm_s = (maxf + kTM - 1) / kTM;
+        hipLaunchKernelGGL(k_gemm64<1>, dim3(xcd_grid(ne, tm_s * tn)), dim3(256), 0, s, dm, ms, e0, ne, tm_s, tn, sys,
+                           (const double *)X, M32, SK);
+        return (int)hipGetLastError();
+    };
+    launch_red_init(ne, true, info + e0, sel, s);
+    // bases of element e0's regions, offsets relative to it
+    const RedBuf rb{(double *)M, X + (ctx->maux_off[e0] - ctx->x_off[e0]), sel, dm.mk_off, dm.maux_off};
+    int err = launch_red_eliminate(ctx, rb, e0, ne, formed, false, E, info, s);
     if (err) return err;
-    back_solve();
-    hipLaunchKernelGGL(k_xupdate<0>, elem_grid, dim3(256), 0, s, dm, e0, (const float *)M, X, E);
-    const int tm_r = (maxn + kTM - 1) / kTM;
-    for (int it = 0; it < refine; ++it) {
-        // R = [B | R_qu] - A X in FP64 (into the FP32 right-hand columns), d = A^{-1} R, X += d
-        hipLaunchKernelGGL(k_gemm64<0>, dim3(xcd_grid(ne, tm_r * tn)), dim3(256), 0, s, dm, e0, ne, tm_r, tn,
-                           (const double *)E, (const double *)X, M, SK);
-        forward_solve();
-        back_solve();
-        if (it + 1 < refine)
-            hipLaunchKernelGGL(k_xupdate<1>, elem_grid, dim3(256), 0, s, dm, e0, (const float *)M, X, E);
-        else
-            hipLaunchKernelGGL(k_xupdate<2>, elem_grid, dim3(256), 0, s, dm, e0, (const float *)M, X, E);
-    }
-    // [S^K | -g^K] = [D | R_uh] - C X (FP64), stored as [S^K | g^K]
-    const int tm_s = (maxf + kTM - 1) / kTM;
-    hipLaunchKernelGGL(k_gemm64<1>, dim3(xcd_grid(ne, tm_s * tn)), dim3(256), 0, s, dm, e0, ne, tm_s, tn,
-                       (const double *)E, (const double *)X, M, SK);
-    return (int)hipGetLastError();
+    float *M32r = M + (ctx->m32r_off[e0] - ctx->m32_off[e0]);
+    const SysDesc sr{4, dm.m32r_off, sel, e0, 1}, sd{2, dm.m32_off, sel, e0, 0};
+    if ((err = solve(MixSys{1, sel, dm.mk_off, dm.m32r_off}, sr, rb.K, M32r, maxu))) return err;
+    if ((err = launch_red_xq(ctx, rb, e0, ne, X, E, s))) return err;
+    if (formed) return 0;
+    return solve(MixSys{0, sel, dm.E_off, dm.m32_off}, sd, E, M, maxn);
 }
 
 }  // namespace hdg

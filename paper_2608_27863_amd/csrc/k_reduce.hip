@@ -634,6 +634,73 @@ __global__ void __launch_bounds__(256) k_wb_trace(DevMesh dm, RedBuf rb, int e0,
         E[threadIdx.x] = __longlong_as_double((long long)red_mark(threadIdx.x));
 }
 
+// Gradient rows of X = A^{-1} [B | R] from the conserved ones (mixed path), into
+// the right-hand columns of E: X_(c,j) = [H part of Y_j at uh_c | r] - Y_j,G X_u_c.
+// Tiles over the 3 N_p rows of one component c and the f + 1 columns.  Xu: the
+// conserved rows, stride x_ld, element e at x_off[e].
+template <int P, int WR, int WC, int BR, int BC>
+__global__ void __launch_bounds__(256, 2) k_xq(DevMesh dm, RedBuf rb, int e0, int ne, int tiles_r, int tiles_n,
+                                               const double *__restrict__ Xbase, double *__restrict__ Ebase) {
+    constexpr int p1 = P + 1, Np = p1 * p1 * p1;
+    typedef Tile<WR, WC, BR, BC> T;
+    int el, t;
+    if (!xcd_item(ne, 5 * tiles_r * tiles_n, el, t)) return;
+    const int e = e0 + el;
+    if (dm.elem_p[e] != P || !rb.sel[el]) return;
+    const int *to = dm.toff + 7 * e;
+    const int f = to[6], w = f / 5, n = 20 * Np;
+    const int c0 = (t % tiles_n) * T::TN, r0 = (t / tiles_n) % tiles_r * T::TM, c = t / tiles_n / tiles_r;
+    if (c0 > f || r0 >= 3 * Np) return;  // uniform per block
+    const int64_t ld = e_ld(n, f), ldx = x_ld(f);
+    double *E = Ebase + (dm.E_off[e] - dm.E_off[e0]) + (int64_t)3 * c * Np * ld + n;
+    const double *X = Xbase + (dm.x_off[e] - dm.x_off[e0]) + (int64_t)c * Np * ldx;
+    const Aux ax = aux_of(rb, e, e0, Np, w);
+    __shared__ __attribute__((aligned(16))) typename T::Smem sm;
+    __shared__ int scol[T::TN];  // column of Y that each column starts from (-1: none)
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < T::TN; i += 256) {
+        const int col = c0 + i;
+        int y = -1;
+        if (col == f) {
+            y = Np + w + c;
+        } else if (col < f) {
+            int lf = 0;
+            while (col >= to[lf + 1]) ++lf;
+            const int nfp = (to[lf + 1] - to[lf]) / 5, k = col - to[lf] - c * nfp;
+            if (k >= 0 && k < nfp) y = Np + to[lf] / 5 + k;
+        }
+        scol[i] = y;
+    }
+    __syncthreads();
+    const int wr = (wave / WC) * 16 * BR, wc = (wave % WC) * 16 * BC;
+    acc_t acc[BR][BC];
+#pragma unroll
+    for (int b = 0; b < BR; ++b)
+#pragma unroll
+        for (int h = 0; h < BC; ++h) {
+            const int y = scol[wc + 16 * h + (lane & 15)];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = r0 + wr + 16 * b + rowof(lane, q);
+                acc[b][h][q] = (y >= 0 && r < 3 * Np) ? ax.Y[(int64_t)r * ax.ldy + y] : 0.0;
+            }
+        }
+    const int rl = 3 * Np - 1 - r0;
+    T::product(
+        Np, [&](int r, int k) { return ax.Y + (int64_t)(r0 + min(r, rl)) * ax.ldy + k; },
+        [&](int r) { return r <= rl; }, [&](int k, int h) { return X + (int64_t)k * ldx + min(c0 + h, f); },
+        [&](int h) { return c0 + h <= f; }, (1u << BR) - 1u, true, sm, acc);
+#pragma unroll
+    for (int b = 0; b < BR; ++b)
+#pragma unroll
+        for (int h = 0; h < BC; ++h)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = r0 + wr + 16 * b + rowof(lane, q), col = c0 + wc + 16 * h + (lane & 15);
+                if (r < 3 * Np && col <= f) __builtin_nontemporal_store(acc[b][h][q], E + (int64_t)r * ld + col);
+            }
+}
+
 // A densely factored element (every element without sel) must not carry the mark.
 __global__ void __launch_bounds__(256) k_clear_mark(DevMesh dm, int e0, int ne, const int *__restrict__ sel,
                                                     double *__restrict__ Ebase) {
@@ -726,6 +793,21 @@ int launch_red_writeback(const hdg_ctx *ctx, const RedBuf &rb, int e0, int ne, d
     }
     hipLaunchKernelGGL(k_wb_rows, dim3((nu + 3) / 4, ne), dim3(256), 0, s, ctx->dm, rb, e0, E);
     hipLaunchKernelGGL(k_wb_trace, dim3((f + 1 + 31) / 32, (f + 31) / 32, ne), dim3(256), 0, s, ctx->dm, rb, e0, E, SK);
+    return (int)hipGetLastError();
+}
+
+int launch_red_xq(const hdg_ctx *ctx, const RedBuf &rb, int e0, int ne, const double *Xu, double *E, hipStream_t s) {
+    int maxf[kMaxP + 1], maxb[kMaxP + 1];
+    const unsigned deg = degrees_of(ctx, e0, ne, maxf, maxb);
+    auto go = [&](auto kernel, int p, int TM) {
+        const int Np = (p + 1) * (p + 1) * (p + 1), tr = (3 * Np + TM - 1) / TM, tn = (maxf[p] + 1 + 127) / 128;
+        hipLaunchKernelGGL(kernel, dim3(xcd_grid(ne, 5 * tr * tn)), dim3(256), 0, s, ctx->dm, rb, e0, ne, tr, tn, Xu, E);
+    };
+    // 128 columns; rows: 24, 81, 192, 375 for p = 1 .. 4
+    if (deg & 2u) go(k_xq<1, 1, 4, 2, 2>, 1, 32);
+    if (deg & 4u) go(k_xq<2, 2, 2, 3, 4>, 2, 96);
+    if (deg & 8u) go(k_xq<3, 1, 4, 4, 2>, 3, 64);
+    if (deg & 16u) go(k_xq<4, 2, 2, 4, 4>, 4, 128);
     return (int)hipGetLastError();
 }
 

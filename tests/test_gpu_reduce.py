@@ -142,3 +142,38 @@ def test_workspace_is_bounded_and_pieces_agree():
     whole, part = ctx.workspace_size(1), ctx.workspace_size(1, e0=100, ne=100)
     assert part < whole <= (9 << 29) + 4096
     assert ctx.workspace_size(1, e0=0, ne=300) == whole
+
+
+@pytest.mark.parametrize("p,walls,chunk", [(1, False, 5), (2, True, None), (3, True, 7), (4, False, 12),
+                                           ((1, 2, 3, 4), True, 5)])
+def test_mixed_routes_agree(p, walls, chunk):
+    """HDG_MIXED: S^K and g^K of both routes within its 1e-10 of an FP64 solve, and the
+    X stored for the recovery within what the route through all columns leaves, or 1e-11."""
+    import torch
+    from paper_2608_27863_amd import hdg, pipeline
+    wl = _workload(p, walls)
+    print(f"[reduce] mixed, p={p} walls={walls} chunk={chunk}", flush=True)
+    st = pipeline.NewtonStep(wl, prec=hdg.HDG_MIXED, chunk=chunk)
+    ctx = st.ctx
+    st.residual_jacobian()
+    E0 = st.E.clone()
+    E1 = E0.clone()
+    for e in range(ctx.n_elem):
+        E1[int(ctx.layout["E_off"][e]) + int(ctx.layout["elem_n"][e]) // 20] = 1e-290
+    out = [_condensed(st, E) for E in (E0, E1)]
+    host = E0.cpu().numpy()
+    for e in range(ctx.n_elem):
+        if e not in (0, 5, ctx.n_elem - 1):
+            continue
+        n = int(ctx.layout["elem_n"][e])
+        Ev, _ = e_view(ctx, host, e)
+        X = np.linalg.solve(Ev[:n, :n], Ev[:n, n:])
+        R = Ev[n:, n:] - Ev[n:, :n] @ X
+        err = []
+        for SK, fact in out:
+            S, g = sk_view(ctx, SK, e)
+            assert rel_err(S, R[:, :-1]) <= 1e-10 and rel_err(g, -R[:, -1]) <= 1e-10
+            err.append(rel_err(e_view(ctx, fact, e)[0][:n, n:], X))
+        print(f"  element {e}: X {err[0]:.2e} (all columns: {err[1]:.2e})")
+        assert err[0] <= max(err[1], 1e-11)
+    torch.cuda.synchronize()
