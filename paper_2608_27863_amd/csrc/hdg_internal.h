@@ -76,6 +76,7 @@ struct DevMesh {
     const int *blk_src;        // [n][3]: elem, local face a (row), local face b (col)
     const int *face_src_ptr;   // [n_face+1] elements touching each face
     const int *face_src;       // [n][2]: elem, local face
+    const int *gsrc;           // [2 N_uh]: entries of the element-local trace vectors that meet in a trace unknown
     const int *asm_blk;        // [n_elem][36]: bsr block index of (face a, face b)
     // artificial-viscosity smoothing: element corners grouped into vertex
     // classes (vertices identified through every two-sided face, periodic

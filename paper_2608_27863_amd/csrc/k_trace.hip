@@ -14,7 +14,7 @@ namespace hdg {
 namespace {
 
 typedef double v2d __attribute__((ext_vector_type(2)));
-
+constexpr int kCUs = 256;  // compute units of the chip
 
 // ------------------------------------------------------------------ assembly
 __global__ void __launch_bounds__(256) k_assemble_blocks(DevMesh dm, const double *__restrict__ SK,
@@ -131,6 +131,64 @@ __global__ void __launch_bounds__(256) k_matvec(DevMesh dm, const double *__rest
                 }
                 for (; j <= jhi; j += W) acc += sp[j * bF + i - p0] * xs[j];
             }
+        }
+    }
+    sred[tid] = acc;
+    __syncthreads();
+    if (tid < bF) {
+        double v = 0.0;
+        for (int ww = 0; ww < W; ++ww) v += sred[ww * bF + tid];
+        y[dm.face_off[F] + tid] = v;
+    }
+}
+
+// The same product for few face rows, where k_matvec's one workgroup of 256
+// threads per row leaves most of the chip idle and passes its pieces through LDS
+// one after another: 1024 threads, thread (i, w) straight from memory, whose
+// consecutive lanes are consecutive entries of the block, four columns in flight.
+constexpr int kMvFewThreads = 1024;
+__global__ void __launch_bounds__(kMvFewThreads) k_matvec_few(DevMesh dm, const double *__restrict__ S,
+                                                              const double *__restrict__ x, double *__restrict__ y) {
+    const int F = blockIdx.x;
+    const int bF = (int)(dm.face_off[F + 1] - dm.face_off[F]);
+    const int k0 = dm.bsr_row_ptr[F], nk = dm.bsr_row_ptr[F + 1] - k0;
+    const int tid = threadIdx.x;
+    __shared__ double sx[kMaxRowBlocks * 125];
+    __shared__ int sxo[kMaxRowBlocks + 1];
+    __shared__ int64_t svo[kMaxRowBlocks], sfo[kMaxRowBlocks];
+    __shared__ double sred[kMvFewThreads];
+    if (tid < nk) {
+        const int G = dm.bsr_col[k0 + tid];
+        sfo[tid] = dm.face_off[G];
+        svo[tid] = dm.bsr_val_off[k0 + tid];
+        sxo[tid + 1] = (int)(dm.face_off[G + 1] - dm.face_off[G]);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        sxo[0] = 0;
+        for (int q = 0; q < nk; ++q) sxo[q + 1] += sxo[q];
+    }
+    __syncthreads();
+    for (int q = tid >> 6; q < nk; q += kMvFewThreads / 64)
+        for (int t = tid & 63; t < sxo[q + 1] - sxo[q]; t += 64) sx[sxo[q] + t] = x[sfo[q] + t];
+    __syncthreads();
+    const int W = kMvFewThreads / bF;
+    const int i = tid % bF, w = tid / bF;
+    double acc = 0.0;
+    if (w < W) {
+        // columns of the whole row, 0 .. sxo[nk] - 1, block by block
+        int q = 0;
+        for (int c0 = w; c0 < sxo[nk]; c0 += 4 * W) {
+            double v[4], xv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int c = min(c0 + u * W, sxo[nk] - 1);  // past the end: the last column, times zero
+                while (c >= sxo[q + 1]) ++q;
+                v[u] = S[svo[q] + (int64_t)(c - sxo[q]) * bF + i];
+                xv[u] = (c0 + u * W < sxo[nk]) ? sx[c] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc += v[u] * xv[u];
         }
     }
     sred[tid] = acc;
@@ -329,6 +387,46 @@ __global__ void __launch_bounds__(256) k_asm_local_elem(DevMesh dm, const T *__r
         if (tid + 256 * q < f) z[tid + 256 * q] = acc[q];
 }
 
+// The same product for few elements: one workgroup per (element, 64 rows), its
+// eight waves taking every eighth column, eight loads in flight each; the eight
+// partial sums of a row are added in order.  With a workgroup per element, 27
+// elements at p = 2 keep 27 CUs busy for 49 us.
+constexpr int kFewRows = 64, kFewWaves = 8;
+template <typename T>
+__global__ void __launch_bounds__(64 * kFewWaves) k_asm_local_few(DevMesh dm, const T *__restrict__ Sinv,
+                                                                  const double *__restrict__ r, double *__restrict__ zloc) {
+    const int e = blockIdx.x, tid = threadIdx.x;
+    const int *to = dm.toff + 7 * e;
+    const int f = to[6], i = blockIdx.y * kFewRows + (tid & 63), wave = tid >> 6;
+    if ((int)blockIdx.y * kFewRows >= f) return;  // uniform per block
+    __shared__ double sy[750];
+    __shared__ double sred[kFewWaves][kFewRows];
+    for (int lf = 0; lf < 6; ++lf) {
+        const int F = dm.elem_face[6 * e + lf];
+        const int len = to[lf + 1] - to[lf];
+        for (int t = tid; t < len; t += 64 * kFewWaves) sy[to[lf] + t] = r[dm.face_off[F] + t];
+    }
+    __syncthreads();
+    const T *M = Sinv + dm.asm_off[e] + min(i, f - 1);
+    double acc = 0.0;
+    for (int j = wave; j < f; j += 8 * kFewWaves) {
+        T a[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) a[q] = M[(int64_t)min(j + q * kFewWaves, f - 1) * f];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (j + q * kFewWaves < f) acc += (double)a[q] * sy[j + q * kFewWaves];
+    }
+    sred[wave][tid & 63] = acc;
+    __syncthreads();
+    if (wave == 0 && i < f) {
+        double v = 0.0;
+#pragma unroll
+        for (int q = 0; q < kFewWaves; ++q) v += sred[q][tid];
+        zloc[dm.tloc_off[e] + i] = v;
+    }
+}
+
 __global__ void __launch_bounds__(128) k_asm_gather(DevMesh dm, const double *__restrict__ zloc, double *__restrict__ z) {
     const int F = blockIdx.x;
     const int bF = (int)(dm.face_off[F + 1] - dm.face_off[F]);
@@ -410,55 +508,226 @@ __global__ void __launch_bounds__(256) k_sub_multi(const double *__restrict__ V,
     }
 }
 
-// dst = src / *nrm  (0 if the norm is 0)
-__global__ void __launch_bounds__(256) k_scale_inv(const double *__restrict__ src, const double *__restrict__ nrm_sq,
-                                                   double *__restrict__ dst, int64_t N) {
-    const double nr = sqrt(*nrm_sq);
-    const double s = (nr > 0.0) ? 1.0 / nr : 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x)
-        dst[i] = src[i] * s;
-}
+// --- one Arnoldi step's vector work in four launches.  Each of nb workgroups owns
+// one slice of the vectors.  k_arn_dot forms w = sum_r R_r^T zloc_r on its slice and
+// its part of V^T w; k_arn_sub (twice: classical Gram-Schmidt applied twice) adds
+// the parts of all slices up, redundantly in every workgroup, subtracts V h from w
+// and forms its part of the next V^T w (or of ||w||^2); k_arn_next normalises w into
+// the next vector and updates the rotations.  All sums have a fixed order.  Bound
+// by latency on small systems (a launch is 4 us, and a chain of 14 of them was
+// most of an iteration: with the matvec and Schwarz kernels for few rows a 4^3 p = 2
+// step went 6.68 -> 3.75 ms), by HBM on large ones (V read three times a step;
+// GMRES(30) on 10^3 elements at p = 2 7.67 -> 5.56 ms).
+constexpr int kArnThreads = 1024, kArnWaves = kArnThreads / 64, kArnBlocks = kCUs, kArnTile = 1024;
 
-// Start of the cycle: gam[0] = beta = ||r0||, hist[0] = beta.
-__global__ void k_gmres_start(const double *__restrict__ nrm_sq, double *__restrict__ gam, double *__restrict__ hist, int m) {
-    const double b = sqrt(*nrm_sq);
-    for (int i = 0; i <= m; ++i) gam[i] = 0.0;
-    gam[0] = b;
-    hist[0] = b;
+struct Slice {
+    int64_t i0, i1;
+};
+__device__ inline Slice arn_slice(int64_t N) {
+    const int64_t len = ((N + gridDim.x - 1) / gridDim.x + 15) / 16 * 16;
+    Slice s;
+    s.i0 = min(N, (int64_t)blockIdx.x * len);
+    s.i1 = min(N, s.i0 + len);
+    return s;
 }
-
-// Column j of H (length j+2, column-major ld m+1): fold in the norm, apply
-// the previous rotations, form the new one, update gam and the history.
-__global__ void k_givens(double *__restrict__ H, int m, int j, const double *__restrict__ nrm_sq,
-                         double *__restrict__ cs, double *__restrict__ sn, double *__restrict__ gam,
-                         double *__restrict__ hist) {
-    double *h = H + (int64_t)j * (m + 1);
-    h[j + 1] = sqrt(*nrm_sq);
-    for (int i = 0; i < j; ++i) {
-        const double t = cs[i] * h[i] + sn[i] * h[i + 1];
-        h[i + 1] = -sn[i] * h[i] + cs[i] * h[i + 1];
-        h[i] = t;
+// sacc[v] += V[v][i0 .. i0+n) . sw[0 .. n) for v < nv (nv = 0: sacc[0] += sw . sw), one
+// wave per vector.
+__device__ inline void arn_dots(const double *__restrict__ V, int nv, int64_t N, int64_t i0, int n, const double *sw,
+                                double *sacc) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int v = wave; v < max(nv, 1); v += kArnWaves) {
+        const double *p = V + (int64_t)v * N + i0;
+        double a = 0.0;
+        if (nv > 0) {
+            int i = lane;
+            for (; i + 3 * 64 < n; i += 4 * 64) {
+                double x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = p[i + 64 * u];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) a += x[u] * sw[i + 64 * u];
+            }
+            for (; i < n; i += 64) a += p[i] * sw[i];
+        } else {
+            for (int i = lane; i < n; i += 64) a += sw[i] * sw[i];
+        }
+        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
+        if (lane == 0) sacc[v] += a;
     }
-    const double a = h[j], b = h[j + 1];
-    const double den = hypot(a, b);
-    double c = 1.0, s = 0.0;
-    if (den > 0.0) { c = a / den; s = b / den; }
-    cs[j] = c;
-    sn[j] = s;
-    h[j] = den;
-    h[j + 1] = 0.0;
-    gam[j + 1] = -s * gam[j];
-    gam[j] = c * gam[j];
-    hist[j + 1] = fabs(gam[j + 1]);
+}
+// sh[v] = sum over the nb slices of part[v * nb + b], one wave per vector.
+__device__ inline void arn_total(const double *__restrict__ part, int nv, int nb, double *sh) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int v = wave; v < nv; v += kArnWaves) {
+        double a = 0.0;
+        for (int b = lane; b < nb; b += 64) a += part[(int64_t)v * nb + b];
+        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
+        if (lane == 0) sh[v] = a;
+    }
 }
 
-// y = R^{-1} gam (upper triangular m x m part of H); skips zero pivots
-__global__ void k_upper_solve(const double *__restrict__ H, int m, const double *__restrict__ gam, double *__restrict__ y) {
+// gsrc[2 i], gsrc[2 i + 1]: entries of zloc that add up to trace unknown i (-1: none)
+__global__ void __launch_bounds__(kArnThreads) k_arn_dot(const int *__restrict__ gsrc, const double *__restrict__ zloc,
+                                                         const double *__restrict__ V, int nv, int64_t N,
+                                                         double *__restrict__ w, double *__restrict__ part) {
+    __shared__ double sw[kArnTile], sacc[256];
+    const int tid = threadIdx.x;
+    const Slice sl = arn_slice(N);
+    for (int v = tid; v < max(nv, 1); v += kArnThreads) sacc[v] = 0.0;
+    for (int64_t t0 = sl.i0; t0 < sl.i1; t0 += kArnTile) {
+        const int n = (int)min((int64_t)kArnTile, sl.i1 - t0);
+        __syncthreads();
+        if (tid < n) {
+            const int a = gsrc[2 * (t0 + tid)], b = gsrc[2 * (t0 + tid) + 1];
+            double x = zloc[a];
+            if (b >= 0) x += zloc[b];
+            sw[tid] = x;
+            w[t0 + tid] = x;
+        }
+        __syncthreads();
+        arn_dots(V, nv, N, t0, n, sw, sacc);
+    }
+    __syncthreads();
+    for (int v = tid; v < max(nv, 1); v += kArnThreads) part[(int64_t)v * gridDim.x + blockIdx.x] = sacc[v];
+}
+
+// h = the totals of `part`; w -= V h; part_out = V^T w (norm = 0) or ||w||^2 (norm = 1);
+// hj = h (accumulate = 0) or hj + h.
+__global__ void __launch_bounds__(kArnThreads) k_arn_sub(const double *__restrict__ V, int nv, int64_t N,
+                                                         const double *__restrict__ part, double *__restrict__ part_out,
+                                                         double *__restrict__ w, double *__restrict__ hj,
+                                                         int accumulate, int norm) {
+    __shared__ double sw[kArnTile], sacc[256], sh[256], sred[kArnThreads];
+    const int tid = threadIdx.x;
+    const Slice sl = arn_slice(N);
+    arn_total(part, nv, gridDim.x, sh);
+    const int no = norm ? 1 : nv;
+    for (int v = tid; v < no; v += kArnThreads) sacc[v] = 0.0;
+    __syncthreads();
+    if (blockIdx.x == 0)
+        for (int v = tid; v < nv; v += kArnThreads) hj[v] = accumulate ? hj[v] + sh[v] : sh[v];
+    // a tile of ts entries, the vectors spread over kArnThreads / ts groups of threads
+    int ts = 64;
+    while (ts < kArnTile && ts < sl.i1 - sl.i0) ts *= 2;
+    const int G = kArnThreads / ts, g = tid / ts, ti = tid & (ts - 1);
+    for (int64_t t0 = sl.i0; t0 < sl.i1; t0 += ts) {
+        const int n = (int)min((int64_t)ts, sl.i1 - t0);
+        double a = 0.0;
+        if (ti < n) {
+            const double *p = V + t0 + ti;
+            int v = g;
+            for (; v + 7 * G < nv; v += 8 * G) {
+                double x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = p[(int64_t)(v + u * G) * N];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) a += x[u] * sh[v + u * G];
+            }
+            for (; v < nv; v += G) a += p[(int64_t)v * N] * sh[v];
+        }
+        sred[tid] = a;
+        __syncthreads();
+        if (tid < n) {
+            double x = w[t0 + tid];
+            for (int q = 0; q < G; ++q) x -= sred[q * ts + tid];
+            w[t0 + tid] = x;
+            sw[tid] = x;
+        }
+        __syncthreads();
+        arn_dots(V, norm ? 0 : nv, N, t0, n, sw, sacc);
+        __syncthreads();
+    }
+    for (int v = tid; v < no; v += kArnThreads) part_out[(int64_t)v * gridDim.x + blockIdx.x] = sacc[v];
+}
+
+// v_next = w / ||w|| (0 if the norm is 0); the last workgroup's first wave also
+// folds the norm into column j of H (length j+2, column-major ld m+1), applies the
+// previous rotations, forms the new one and updates gam and the history.  j < 0:
+// the start of the cycle, gam[0] = hist[0] = beta = ||r0||.
+__global__ void __launch_bounds__(kArnThreads) k_arn_next(const double *__restrict__ w, int64_t N,
+                                                          const double *__restrict__ part, double *__restrict__ vnext,
+                                                          double *__restrict__ H, int m, int j, double *__restrict__ cs,
+                                                          double *__restrict__ sn, double *__restrict__ gam,
+                                                          double *__restrict__ hist) {
+    __shared__ double snrm[1];
+    __shared__ double sc[201], ss[201], shc[202];
+    const int tid = threadIdx.x;
+    arn_total(part, 1, gridDim.x, snrm);
+    const bool last = blockIdx.x == gridDim.x - 1;
+    if (last && j >= 0) {
+        for (int i = tid; i <= j; i += kArnThreads) {
+            sc[i] = (i < j) ? cs[i] : 0.0;
+            ss[i] = (i < j) ? sn[i] : 0.0;
+            shc[i] = H[(int64_t)j * (m + 1) + i];
+        }
+    }
+    __syncthreads();
+    const double nr = sqrt(snrm[0]);
+    const double s = (nr > 0.0) ? 1.0 / nr : 0.0;
+    const Slice sl = arn_slice(N);
+    for (int64_t i = sl.i0 + tid; i < sl.i1; i += kArnThreads) vnext[i] = w[i] * s;
+    if (!last) return;
+    if (j < 0) {
+        for (int i = tid; i <= m; i += kArnThreads) gam[i] = (i == 0) ? nr : 0.0;
+        if (tid == 0) hist[0] = nr;
+        return;
+    }
+    if (tid == 0) {
+        // the column stays in registers and LDS; only the final values go out
+        double a = shc[0];
+        for (int i = 0; i < j; ++i) {
+            const double b = shc[i + 1];
+            shc[i] = sc[i] * a + ss[i] * b;
+            a = -ss[i] * a + sc[i] * b;
+        }
+        const double b = nr, den = hypot(a, b);
+        double c = 1.0, sv = 0.0;
+        if (den > 0.0) { c = a / den; sv = b / den; }
+        cs[j] = c;
+        sn[j] = sv;
+        shc[j] = den;
+        shc[j + 1] = 0.0;
+        const double gj = gam[j];
+        gam[j + 1] = -sv * gj;
+        gam[j] = c * gj;
+        hist[j + 1] = fabs(-sv * gj);
+    }
+    __syncthreads();
+    for (int i = tid; i <= j + 1; i += kArnThreads) H[(int64_t)j * (m + 1) + i] = shc[i];
+}
+
+// y = R^{-1} gam (upper triangular m x m part of H); skips zero pivots.  One wave:
+// y[i] is taken off the right-hand sides of all rows above at once, column i of R
+// read with consecutive lanes (m <= 200: four rows per lane).
+__global__ void __launch_bounds__(64) k_upper_solve(const double *__restrict__ H, int m, const double *__restrict__ gam,
+                                                    double *__restrict__ y) {
+    const int lane = threadIdx.x;
+    double r[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) r[q] = (lane + 64 * q < m) ? gam[lane + 64 * q] : 0.0;
+    double col[4], nxt[4];
+    auto load = [&](int i, double (&c)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c[q] = (i >= 0 && lane + 64 * q <= i) ? H[(int64_t)i * (m + 1) + lane + 64 * q] : 0.0;
+    };
+    load(m - 1, nxt);
     for (int i = m - 1; i >= 0; --i) {
-        double s = gam[i];
-        for (int k = i + 1; k < m; ++k) s -= H[(int64_t)k * (m + 1) + i] * y[k];
-        const double d = H[(int64_t)i * (m + 1) + i];
-        y[i] = (d != 0.0) ? s / d : 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) col[q] = nxt[q];
+        load(i - 1, nxt);
+        double ri = 0.0, d = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (i / 64 == q) {
+                ri = r[q];
+                d = col[q];
+            }
+        ri = __shfl(ri, i & 63);
+        d = __shfl(d, i & 63);
+        const double yi = (d != 0.0) ? ri / d : 0.0;
+        if (lane == 0) y[i] = yi;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r[q] -= col[q] * yi;  // rows above i (rows from i on are done)
     }
 }
 
@@ -851,7 +1120,14 @@ int launch_assemble(const hdg_ctx *ctx, const double *SK, double *S, double *g, 
 }
 
 int launch_matvec(const hdg_ctx *ctx, const double *S, const double *x, double *y, hipStream_t s) {
-    hipLaunchKernelGGL(k_matvec, dim3(ctx->n_face), dim3(256), 0, s, ctx->dm, S, x, y);
+    // the direct kernel while its workgroups cover the chip at most twice over, and for
+    // blocks up to 45 x 45, whose 16 KB fill half of k_matvec's LDS piece: p = 2, 81 faces
+    // 19.3 -> 9.2 us, 5184 faces 218 -> 172 us; p = 4, 192 faces 89 -> 44 us, 375 faces
+    // equal, 648 faces 153 (k_matvec) against 170 us
+    if (ctx->max_b <= 45 || ctx->n_face <= 2 * kCUs)
+        hipLaunchKernelGGL(k_matvec_few, dim3(ctx->n_face), dim3(kMvFewThreads), 0, s, ctx->dm, S, x, y);
+    else
+        hipLaunchKernelGGL(k_matvec, dim3(ctx->n_face), dim3(256), 0, s, ctx->dm, S, x, y);
     return (int)hipGetLastError();
 }
 
@@ -894,13 +1170,24 @@ size_t asm_apply_work_bytes(const hdg_ctx *ctx) {
     return (sizeof(double) * (size_t)ctx->tloc_off[ctx->n_elem] + 255) / 256 * 256;
 }
 
-int launch_asm_apply(const hdg_ctx *ctx, int prec, const void *Sinv, const double *r, double *z, void *work,
-                     hipStream_t s) {
+// zloc = S_r^{-1} R_r r for every element
+static void launch_asm_local(const hdg_ctx *ctx, int prec, const void *Sinv, const double *r, double *zloc,
+                             hipStream_t s) {
     const DevMesh &dm = ctx->dm;
-    double *zloc = (double *)work;
-    const dim3 grid(ctx->n_elem, (ctx->max_f + 255) / 256);
     const bool aligned = prec == HDG_FP64 ? ctx->asm_cols_aligned64 : ctx->asm_cols_aligned32;
     const bool per_elem = !aligned && ctx->max_f <= kAsmRowsPerThread * 256;
+    // fewer workgroups than CUs in the kernels below: 27 elements at p = 2 (FP64) 48 -> 14 us,
+    // 216 at p = 4 368 -> 189 us; from there on they read the inverses better (512 elements
+    // at p = 4 415 against 439 us)
+    if (ctx->n_elem * (per_elem ? 1 : (ctx->max_f + 255) / 256) < kCUs) {
+        const dim3 fgrid(ctx->n_elem, (ctx->max_f + kFewRows - 1) / kFewRows);
+        if (prec == HDG_FP64)
+            hipLaunchKernelGGL(k_asm_local_few<double>, fgrid, dim3(64 * kFewWaves), 0, s, dm, (const double *)Sinv, r, zloc);
+        else
+            hipLaunchKernelGGL(k_asm_local_few<float>, fgrid, dim3(64 * kFewWaves), 0, s, dm, (const float *)Sinv, r, zloc);
+        return;
+    }
+    const dim3 grid(ctx->n_elem, (ctx->max_f + 255) / 256);
     if (prec == HDG_FP64) {
         if (per_elem)
             hipLaunchKernelGGL(k_asm_local_elem<double>, dim3(ctx->n_elem), dim3(256), 0, s, dm, (const double *)Sinv, r,
@@ -914,7 +1201,13 @@ int launch_asm_apply(const hdg_ctx *ctx, int prec, const void *Sinv, const doubl
         else
             hipLaunchKernelGGL(k_asm_local<float>, grid, dim3(256), 0, s, dm, (const float *)Sinv, r, zloc);
     }
-    hipLaunchKernelGGL(k_asm_gather, dim3(ctx->n_face), dim3(128), 0, s, dm, (const double *)zloc, z);
+}
+
+int launch_asm_apply(const hdg_ctx *ctx, int prec, const void *Sinv, const double *r, double *z, void *work,
+                     hipStream_t s) {
+    double *zloc = (double *)work;
+    launch_asm_local(ctx, prec, Sinv, r, zloc, s);
+    hipLaunchKernelGGL(k_asm_gather, dim3(ctx->n_face), dim3(128), 0, s, ctx->dm, (const double *)zloc, z);
     return (int)hipGetLastError();
 }
 
@@ -986,50 +1279,42 @@ int launch_gmres(const hdg_ctx *ctx, int prec, const double *S, const void *Sinv
     gmres_layout(ctx, m, off);
     double *W = (double *)work;
     double *V = W + off[0], *w = W + off[1], *t = W + off[2], *zloc = W + off[3], *H = W + off[4];
-    double *cs = W + off[5], *sn = W + off[6], *gam = W + off[7], *hcol = W + off[8], *y = W + off[9];
+    double *cs = W + off[5], *sn = W + off[6], *gam = W + off[7], *y = W + off[9];
     double *partial = W + off[10], *scal = W + off[11];
     const int64_t N = ctx->face_off[ctx->n_face];
-    const int stride = m + 2;
     const int gN = grid_for(N);
+    // slices of at least 64 entries, one workgroup per CU at most
+    const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(kArnBlocks, (N + 63) / 64));
+    double *part2 = partial + (size_t)kArnBlocks * (m + 2);
+    const dim3 gA(nb), tA(kArnThreads);
     int err;
     // r0 = M^{-1} (g - S x0), beta = ||r0||, v0 = r0 / beta
     if (x0) {
         if ((err = launch_matvec(ctx, S, x0, t, s))) return err;
         hipLaunchKernelGGL(k_rsub, dim3(gN), dim3(256), 0, s, g, t, N);
-        if ((err = launch_asm_apply(ctx, prec, Sinv, t, w, zloc, s))) return err;
+        launch_asm_local(ctx, prec, Sinv, t, zloc, s);
     } else {
-        if ((err = launch_asm_apply(ctx, prec, Sinv, g, w, zloc, s))) return err;
+        launch_asm_local(ctx, prec, Sinv, g, zloc, s);
     }
-    hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(256), 0, s, (const double *)w, 1, (int64_t)0,
-                       (const double *)w, N, partial, stride);
-    hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(256), 0, s, (const double *)partial, kDotBlocks, stride, 1, scal, 0);
-    hipLaunchKernelGGL(k_gmres_start, dim3(1), dim3(1), 0, s, (const double *)scal, gam, hist, m);
-    hipLaunchKernelGGL(k_scale_inv, dim3(gN), dim3(256), 0, s, (const double *)w, (const double *)scal, V, N);
+    hipLaunchKernelGGL(k_arn_dot, gA, tA, 0, s, ctx->dm.gsrc, (const double *)zloc, (const double *)V, 0, N, w, partial);
+    hipLaunchKernelGGL(k_arn_next, gA, tA, 0, s, (const double *)w, N, (const double *)partial, V, H, m, -1, cs, sn, gam,
+                       hist);
     for (int j = 0; j < m; ++j) {
         double *vj = V + (int64_t)j * N;
         if ((err = launch_matvec(ctx, S, vj, t, s))) return err;
-        if ((err = launch_asm_apply(ctx, prec, Sinv, t, w, zloc, s))) return err;
+        launch_asm_local(ctx, prec, Sinv, t, zloc, s);
         double *hj = H + (int64_t)j * (m + 1);
         // classical Gram-Schmidt, applied twice
-        for (int pass = 0; pass < 2; ++pass) {
-            hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(256), 0, s, (const double *)V, j + 1, N,
-                               (const double *)w, N, partial, stride);
-            hipLaunchKernelGGL(k_dot_final, dim3(j + 1), dim3(256), 0, s, (const double *)partial,
-                               kDotBlocks, stride, j + 1, pass == 0 ? hj : hcol, 0);
-            hipLaunchKernelGGL(k_sub_multi, dim3(gN), dim3(256), 0, s, (const double *)V, j + 1, N,
-                               (const double *)(pass == 0 ? hj : hcol), w, N);
-            if (pass == 1)
-                hipLaunchKernelGGL(k_dot_final, dim3(j + 1), dim3(256), 0, s, (const double *)partial,
-                                   kDotBlocks, stride, j + 1, hj, 1);
-        }
-        hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(256), 0, s, (const double *)w, 1, (int64_t)0,
-                           (const double *)w, N, partial, stride);
-        hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(256), 0, s, (const double *)partial, kDotBlocks, stride, 1, scal, 0);
-        hipLaunchKernelGGL(k_scale_inv, dim3(gN), dim3(256), 0, s, (const double *)w, (const double *)scal,
-                           V + (int64_t)(j + 1) * N, N);
-        hipLaunchKernelGGL(k_givens, dim3(1), dim3(1), 0, s, H, m, j, (const double *)scal, cs, sn, gam, hist);
+        hipLaunchKernelGGL(k_arn_dot, gA, tA, 0, s, ctx->dm.gsrc, (const double *)zloc, (const double *)V, j + 1, N, w,
+                           partial);
+        hipLaunchKernelGGL(k_arn_sub, gA, tA, 0, s, (const double *)V, j + 1, N, (const double *)partial, part2, w, hj, 0,
+                           0);
+        hipLaunchKernelGGL(k_arn_sub, gA, tA, 0, s, (const double *)V, j + 1, N, (const double *)part2, partial, w, hj, 1,
+                           1);
+        hipLaunchKernelGGL(k_arn_next, gA, tA, 0, s, (const double *)w, N, (const double *)partial, vj + N, H, m, j, cs,
+                           sn, gam, hist);
     }
-    hipLaunchKernelGGL(k_upper_solve, dim3(1), dim3(1), 0, s, (const double *)H, m, (const double *)gam, y);
+    hipLaunchKernelGGL(k_upper_solve, dim3(1), dim3(64), 0, s, (const double *)H, m, (const double *)gam, y);
     hipLaunchKernelGGL(k_combine, dim3(gN), dim3(256), 0, s, (const double *)V, m, N, (const double *)y, x0, x, N);
     return (int)hipGetLastError();
 }
@@ -1105,7 +1390,7 @@ int launch_rb_guess(const hdg_ctx *ctx, int nb, const double *Wb, const double *
     hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(256), 0, s, (const double *)Qz, nb, N, g, N, partial,
                        stride);
     hipLaunchKernelGGL(k_dot_final, dim3(nb), dim3(256), 0, s, (const double *)partial, kDotBlocks, stride, nb, qg, 0);
-    hipLaunchKernelGGL(k_upper_solve, dim3(1), dim3(1), 0, s, (const double *)R, nb, (const double *)qg, c);
+    hipLaunchKernelGGL(k_upper_solve, dim3(1), dim3(64), 0, s, (const double *)R, nb, (const double *)qg, c);
     hipLaunchKernelGGL(k_combine, dim3(gN), dim3(256), 0, s, Wb, nb, N, (const double *)c, (const double *)nullptr,
                        x0, N);
     return (int)hipGetLastError();
