@@ -191,17 +191,26 @@ double invert3(const double J[3][3], double G[3][3]) {
     return det;
 }
 
-template <class T>
-int upload(hdg_ctx *ctx, const std::vector<T> &h, const T **dst) {
-    size_t bytes = std::max<size_t>(h.size(), 1) * sizeof(T);
-    void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return HDG_ERR_OUT_OF_MEMORY;
-    ctx->allocations.push_back(p);
-    if (!h.empty() && hipMemcpy(p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess)
-        return HDG_ERR_DEVICE;
-    *dst = static_cast<const T *>(p);
-    return HDG_OK;
-}
+// The context's tables go to the device in one allocation and one copy (a call of
+// each per table was most of a small context's creation).
+struct Upload {
+    std::vector<char> host;
+    std::vector<std::pair<size_t, const void **>> put;  // offset -> where the pointer belongs
+    template <class T> void add(const std::vector<T> &h, const T **dst) {
+        const size_t at = (host.size() + 255) / 256 * 256;
+        host.resize(at + std::max<size_t>(h.size(), 1) * sizeof(T));
+        if (!h.empty()) std::memcpy(host.data() + at, h.data(), h.size() * sizeof(T));
+        put.emplace_back(at, (const void **)dst);
+    }
+    int send(hdg_ctx *ctx) {
+        void *p = nullptr;
+        if (hipMalloc(&p, host.size()) != hipSuccess) return HDG_ERR_OUT_OF_MEMORY;
+        ctx->allocations.push_back(p);
+        if (hipMemcpy(p, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess) return HDG_ERR_DEVICE;
+        for (auto &q : put) *q.second = (const char *)p + q.first;
+        return HDG_OK;
+    }
+};
 
 int trace_size(int pf) { return 5 * (pf + 1) * (pf + 1); }
 
@@ -337,7 +346,8 @@ int hdg_create(const hdg_mesh_desc *m, const hdg_phys *phys, hdg_ctx **out) {
         ctx->E_off[e + 1] = ctx->E_off[e] + (int64_t)(n + f) * hdg::e_ld(n, f);
         ctx->SK_off[e + 1] = ctx->SK_off[e] + (int64_t)f * (f + 1);
         ctx->asm_off[e + 1] = (ctx->asm_off[e] + (int64_t)f * f + 31) / 32 * 32;  // blocks start on 128-byte lines
-        ctx->qp_off[e + 1] = ctx->qp_off[e] + (int64_t)(hdg::kVJac + hdg::kVRes) * Nq + (int64_t)hdg::kFPer * nqf_tot;
+        ctx->qp_off[e + 1] = ctx->qp_off[e] + (int64_t)(hdg::kVJac + hdg::kVRes) * Nq + (int64_t)hdg::kFPer * nqf_tot +
+                             hdg::scal_size(Np, p + 1, f / 5);
         ctx->vgeo_off[e + 1] = ctx->vgeo_off[e] + 10 * Nq;
         const int fe = hdg::asm_pad(f);  // Schwarz system size
         ctx->asmsys_off[e + 1] = ctx->asmsys_off[e] + (int64_t)fe * hdg::e_ld(fe, fe);
@@ -521,8 +531,8 @@ int hdg_create(const hdg_mesh_desc *m, const hdg_phys *phys, hdg_ctx **out) {
     DevMesh &dm = ctx->dm;
     dm.n_elem = ne;
     dm.n_face = nf;
-    int st = HDG_OK;
-#define UP(vec, field) do { if ((st = upload(ctx, vec, &dm.field)) != HDG_OK) return fail(st); } while (0)
+    Upload up;
+#define UP(vec, field) up.add(vec, &dm.field)
     UP(ctx->elem_p, elem_p);
     UP(ctx->face_p, face_p);
     UP(ctx->elem_face, elem_face);
@@ -562,6 +572,8 @@ int hdg_create(const hdg_mesh_desc *m, const hdg_phys *phys, hdg_ctx **out) {
     UP(av_src, av_src);
     dm.n_vclass = n_vclass;
 #undef UP
+    const int st = up.send(ctx);
+    if (st != HDG_OK) return fail(st);
     ctx->bsr_row_ptr64.assign(ctx->bsr_row_ptr.begin(), ctx->bsr_row_ptr.end());
     ctx->bsr_col64.assign(ctx->bsr_col.begin(), ctx->bsr_col.end());
     *out = ctx;

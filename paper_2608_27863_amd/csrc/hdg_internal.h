@@ -36,6 +36,8 @@ __host__ __device__ inline int tbl_W(int nq, int g) { return kTblW + (nq - 3) * 
 //           bres [c 5][s]              boundary residual w |N| b^_c (boundary faces)
 //           fuh  [c 5][s]              uh_c
 //           bjac [c 5][slot 25][s]     d(b^_c)/d(u, q, uh), weights included (boundary faces)
+//   then the scalar blocks M, G_j, H_j of the gradient rows (scal_size)
+__host__ __device__ inline int64_t scal_size(int Np, int p1, int w) { return (int64_t)4 * Np * Np + 3 * p1 * p1 * w; }
 constexpr int kVJac = 400, kVRes = 80, kFJac = 125, kFPer = 265;
 
 // Device view of a context, passed by value to kernels.

@@ -8,16 +8,17 @@
 //       av-total and the numerical flux of eq. num-flux-hdg, and their exact
 //       Jacobians (derived by hand below), already multiplied by quadrature
 //       weights, the geometric factors and dt / alpha;
-//   k_assemble_field_rows / k_assemble_trace_rows : contract the point
+//   k_conserved_blocks, k_conserved_trace, k_grad_rows, k_trace_rows : contract the point
 //       coefficients with the basis (phi_i, reference derivatives of phi_i,
 //       phi_k, trace basis mu_a) into the rows of the element system
 //       E^K = [[A B R_qu],[C D R_uh]], by sum factorisation over the tensor
-//       Gauss points.  Their bulk stores are nontemporal: a chunk's systems
-//       (21.7 GB for 256 elements at p = 4) are far larger than any cache, so
-//       keeping the written lines only evicts other data.
+//       Gauss points.  A chunk's systems (21.7 GB for 256 elements at p = 4) are
+//       far larger than any cache: the gradient rows, most of them, are stored
+//       nontemporally.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "hdg_internal.h"
 
@@ -410,265 +411,489 @@ __device__ inline void load_face_tables(const DevMesh &dm, int e, int p, int Nq,
     }
 }
 
-// Interior rows of one row field r of the element system (the workgroups that
-// share it are described below the helpers): the 20 column blocks of A, the
-// trace columns B, the residual column and the padding, all written.  Gradient rows r = 3c+j hold the mass
-// block (column field r) and K_j = int phi_k d_j phi_i (column field 15+c) and
-// zeros elsewhere; conservation rows r = 15+c hold the blocks of the point
-// Jacobians plus their face terms.
-//
-// Every N_p x N_p block sum_g phi_k(g) [c0 phi_i + sum_d c_d dref_d phi_i](g) is
-// contracted one direction at a time over the tensor Gauss points (sum
-// factorisation), one i1 slice at a time:
-//   x:  T0 = sum_g1 (L_i1 c0 + D_i1 c1) L_k1,  T2 = sum_g1 L_i1 c2 L_k1,  T3 = sum_g1 L_i1 c3 L_k1
-//   y:  VL = sum_g2 (L_i2 T0 + D_i2 T2) L_k2,   VD = sum_g2 L_i2 T3 L_k2
+// Gradient and conserved rows of the element system, by sum factorisation: every
+// N_p x N_p block sum_g phi_k(g) [c0 phi_i + sum_d c_d dref_d phi_i](g) is contracted
+// one direction at a time over the tensor Gauss points:
+//   x:  T0 = sum_g1 (L_i1 c0 + D_i1 c1) L_k1,  T1 = sum_g1 L_i1 c2 L_k1,  T2 = sum_g1 L_i1 c3 L_k1
+//   y:  VL = sum_g2 (L_i2 T0 + D_i2 T1) L_k2,   VD = sum_g2 L_i2 T2 L_k2
 //   z:  A  = sum_g3 (L_i3 VL + D_i3 VD) L_k3
 // (L, D: the 1-D basis and its derivative at the Gauss points).  The face terms
 // and the trace columns are 2-D contractions over each face's Gauss points.
-constexpr int kP1 = kMaxP + 1, kNQ = kMaxP + 2;
-
 // Instantiated per degree PT (LDS sized for it, loop bounds and index arithmetic
 // known at compile time); workgroups of elements of another degree return.
-// Row fields 0..14 (q) take one workgroup each; each of the five u row fields,
-// whose 20 column-field blocks all carry volume and face terms, is split over
-// kUG workgroups by column fields (the first of them also writes the trace
-// columns, the residual column and the padding).  The launch has 15 + 5 kUG
-// workgroups per element.
+//
+// Bound by LDS reads: in every stage a thread holds its operands of the contracted
+// direction in registers and forms all p+1 (x, y) or (p+1)^2 (z) outputs that share
+// them; the whole block goes through each stage at once (three barriers a block;
+// one i1 slice at a time and one output per thread took 15 barriers and, at p = 4,
+// 30 LDS reads an output instead of 2).  T and V are laid out so that consecutive
+// lanes read consecutive entries.  256 elements at p = 4: 5.09 -> 1.56 ms for the
+// conserved rows' blocks.
+constexpr int kP1 = kMaxP + 1, kNQ = kMaxP + 2;
+
+template <int PT> struct Block {
+    static constexpr int p1 = PT + 1, Np = p1 * p1 * p1, nq = PT + 2, Nq = nq * nq * nq;
+    static constexpr int P2 = p1 * p1, P4 = P2 * P2, Q2 = nq * nq;
+    static constexpr int NT = (P4 + 63) / 64 * 64;  // threads: one per (i1, i2, k1, k2)
+    double L[p1][nq], D[p1][nq];
+    double C[4][nq][Q2];         // coefficient fields of one block, [g1][g2 + nq g3]
+    double T[3][nq][nq * P2];    // x stage, [g2][(g3 p1 + i1) p1 + k1]
+    double V[2][nq][P4];         // y stage, [g3][(i2 p1 + i1) p1^2 + k2 p1 + k1]
+
+    __device__ void load_basis(const DevMesh &dm) {
+        for (int t = threadIdx.x; t < p1 * nq; t += blockDim.x) {
+            L[t / nq][t % nq] = dm.tbl[tbl_L(PT, PT, t / nq, t % nq)];
+            D[t / nq][t % nq] = dm.tbl[tbl_D(PT, t / nq, t % nq)];
+        }
+    }
+    // place of the coefficient d at Gauss point g
+    __device__ double &coef(int d, int g) { return C[d][g % nq][g / nq]; }
+    // The block of the coefficients C: emit(z) on every thread t < P4 of the last stage,
+    // z[i3][k3] its entries; i1, i2, k1, k2 of a thread by split().  Begins and
+    // ends without a barrier: C is read until the first one, V after the last.
+    __device__ static void split(int t, int &i1, int &i2, int &k1, int &k2) {
+        k1 = t % p1;
+        k2 = (t / p1) % p1;
+        i1 = (t / P2) % p1;
+        i2 = t / (P2 * p1);
+    }
+    template <class Emit> __device__ void contract(Emit emit) {
+        const int tid = threadIdx.x;
+        __syncthreads();
+        for (int t = tid; t < p1 * Q2; t += NT) {
+            const int i1 = t / Q2, g23 = t % Q2;
+            double u[3][nq];
+#pragma unroll
+            for (int g1 = 0; g1 < nq; ++g1) {
+                const double l = L[i1][g1];
+                u[0][g1] = l * C[0][g1][g23] + D[i1][g1] * C[1][g1][g23];
+                u[1][g1] = l * C[2][g1][g23];
+                u[2][g1] = l * C[3][g1][g23];
+            }
+            const int g2 = g23 % nq, at = ((g23 / nq) * p1 + i1) * p1;
+#pragma unroll
+            for (int k1 = 0; k1 < p1; ++k1) {
+                double a[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+                for (int g1 = 0; g1 < nq; ++g1)
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) a[d] += u[d][g1] * L[k1][g1];
+#pragma unroll
+                for (int d = 0; d < 3; ++d) T[d][g2][at + k1] = a[d];
+            }
+        }
+        __syncthreads();
+        for (int t = tid; t < p1 * nq * P2; t += NT) {
+            const int q = t % (nq * P2), i2 = t / (nq * P2);  // q = (g3 p1 + i1) p1 + k1
+            double u[nq], d[nq];
+#pragma unroll
+            for (int g2 = 0; g2 < nq; ++g2) {
+                const double l = L[i2][g2];
+                u[g2] = l * T[0][g2][q] + D[i2][g2] * T[1][g2][q];
+                d[g2] = l * T[2][g2][q];
+            }
+            const int g3 = q / P2, at = (i2 * p1 + (q / p1) % p1) * P2 + q % p1;
+#pragma unroll
+            for (int k2 = 0; k2 < p1; ++k2) {
+                double vl = 0.0, vd = 0.0;
+#pragma unroll
+                for (int g2 = 0; g2 < nq; ++g2) {
+                    vl += u[g2] * L[k2][g2];
+                    vd += d[g2] * L[k2][g2];
+                }
+                V[0][g3][at + k2 * p1] = vl;
+                V[1][g3][at + k2 * p1] = vd;
+            }
+        }
+        __syncthreads();
+        if (tid < P4) {
+            double vl[nq], vd[nq];
+#pragma unroll
+            for (int g3 = 0; g3 < nq; ++g3) {
+                vl[g3] = V[0][g3][tid];
+                vd[g3] = V[1][g3][tid];
+            }
+            double z[p1][p1];
+#pragma unroll
+            for (int i3 = 0; i3 < p1; ++i3) {
+                double u[nq];
+#pragma unroll
+                for (int g3 = 0; g3 < nq; ++g3) u[g3] = L[i3][g3] * vl[g3] + D[i3][g3] * vd[g3];
+#pragma unroll
+                for (int k3 = 0; k3 < p1; ++k3) {
+                    double v = 0.0;
+#pragma unroll
+                    for (int g3 = 0; g3 < nq; ++g3) v += u[g3] * L[k3][g3];
+                    z[i3][k3] = v;
+                }
+            }
+            emit(z);
+        }
+    }
+};
+
+// Scalar blocks of one element, in its part of the point workspace (read by
+// k_grad_rows): the mass matrix M, G_j = int phi_k d_j phi_i (j = 0..2), each
+// [N_p][N_p], then per face H_j[a][b] = -int_F phi_a mu_b n_j, [j][p1^2][N_fp] (a, b
+// face-local).  They are the same for every component, so the gradient rows are
+// copies of them; formed per row field as before they took 30 blocks an element
+// instead of four.  kind: 0 M, 1..3 G_j, 4 the faces.
+__device__ inline double *scalar_blocks(const DevMesh &dm, int e, int e0, double *qp, int Np, int p1) {
+    const int w = dm.toff[7 * e + 6] / 5;
+    return qp + (dm.qp_off[e + 1] - dm.qp_off[e0]) - scal_size(Np, p1, w);
+}
+template <int PT> struct BlockShared {
+    Block<PT> sb;
+    double Lf[6][30], Mf[6][30];
+    int Pf[6], Nqf[6];
+    int64_t Fbase[6];
+    double F[6 * Block<PT>::P4];                     // face terms [lf][a0 a1][b0 b1]
+    double G[std::max(6 * Block<PT>::P2 * kNQ, 3 * (PT + 1) * kP1 * kNQ)];  // first stage of the face contractions
+    double Cf[6][kNQ * kNQ];                         // one block's face coefficients
+};
+template <int PT> __device__ void scalar_block(const DevMesh &dm, int e, int e0, int kind, double *qp, BlockShared<PT> &sh) {
+    typedef Block<PT> B;
+    constexpr int p1 = B::p1, Np = B::Np, Nq = B::Nq, NT = B::NT;
+    const int tid = threadIdx.x;
+    double *out = scalar_blocks(dm, e, e0, qp, Np, p1);
+    if (kind < 4) {
+        const double *vg = dm.vgeo + dm.vgeo_off[e];
+        sh.sb.load_basis(dm);
+        for (int t = tid; t < 4 * Nq; t += NT) {
+            const int d = t / Nq, g = t % Nq;
+            double v;
+            if (kind == 0) v = (d == 0) ? vg[g] : 0.0;
+            else v = (d == 0) ? 0.0 : vg[g] * vg[(1 + 3 * (d - 1) + kind - 1) * Nq + g];
+            sh.sb.coef(d, g) = v;
+        }
+        double *dst = out + (int64_t)kind * Np * Np;
+        sh.sb.contract([&](const double (&z)[p1][p1]) {
+            int i1, i2, k1, k2;
+            B::split(tid, i1, i2, k1, k2);
+#pragma unroll
+            for (int i3 = 0; i3 < p1; ++i3)
+#pragma unroll
+                for (int k3 = 0; k3 < p1; ++k3)
+                    dst[(i1 + p1 * (i2 + p1 * i3)) * Np + k1 + p1 * (k2 + p1 * k3)] = z[i3][k3];
+        });
+        return;
+    }
+    load_face_tables(dm, e, PT, Nq, sh.Lf, sh.Mf, sh.Pf, sh.Nqf, sh.Fbase);
+    out += (int64_t)4 * Np * Np;
+    for (int lf = 0; lf < 6; ++lf) {
+        const int pf1 = sh.Pf[lf] + 1, nqf1 = sh.Pf[lf] + 2, Nqf = sh.Nqf[lf], Nfp = pf1 * pf1;
+        const double *fg = dm.fgeo + dm.fgeo_off[6 * e + lf];
+        __syncthreads();
+        for (int t = tid; t < 3 * p1 * pf1 * nqf1; t += NT) {
+            const int j = t / (p1 * pf1 * nqf1), rem = t % (p1 * pf1 * nqf1);
+            const int a0 = rem / (pf1 * nqf1), b0 = (rem / nqf1) % pf1, s1 = rem % nqf1;
+            double v = 0.0;
+            for (int s0 = 0; s0 < nqf1; ++s0)
+                v += sh.Lf[lf][a0 * nqf1 + s0] * sh.Mf[lf][b0 * nqf1 + s0] * fg[j * Nqf + s0 + nqf1 * s1];
+            sh.G[t] = -v;
+        }
+        __syncthreads();
+        for (int t = tid; t < 3 * p1 * p1 * Nfp; t += NT) {
+            const int j = t / (p1 * p1 * Nfp), rem = t % (p1 * p1 * Nfp);
+            const int a = rem / Nfp, b = rem % Nfp;  // a = a0 + p1 a1, b = b0 + pf1 b1
+            const int a0 = a % p1, a1 = a / p1, b0 = b % pf1, b1 = b / pf1;
+            const double *gg = sh.G + ((j * p1 + a0) * pf1 + b0) * nqf1;
+            double v = 0.0;
+            for (int s1 = 0; s1 < nqf1; ++s1) v += sh.Lf[lf][a1 * nqf1 + s1] * sh.Mf[lf][b1 * nqf1 + s1] * gg[s1];
+            out[t] = v;
+        }
+        out += 3 * p1 * p1 * Nfp;
+    }
+}
+
+// Gradient rows (three quarters of A and B): row (c, j, node i) holds M's row i in
+// its own field, G_j's in u_c, H_j's in the trace of component c and zeros elsewhere;
+// its residual is M q_(c,j) + G_j u_c + H_j uh_c, the same integrals.  Bound by the
+// writes: one workgroup takes `nodes` nodes, holds the scalar rows of a node in LDS and
+// streams its 15 rows with 16-byte nontemporal stores, each thread's column pair
+// classified once for all of them (12.5 GB at p = 4 in 2.40 ms, 2.82 with plain
+// stores).
+template <int PT>
+__global__ void __launch_bounds__(256) k_grad_rows(DevMesh dm, int e0, int nodes, const double *__restrict__ Qg,
+                                                   const double *__restrict__ Ug, const double *__restrict__ Uhg,
+                                                   double *__restrict__ qp, double *__restrict__ Ebase) {
+    constexpr int p = PT, p1 = p + 1, Np = p1 * p1 * p1, n = 20 * Np;
+    constexpr int kW = 6 * kP1 * kP1;  // trace unknowns of a component, at most
+    const int e = e0 + blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (dm.elem_p[e] != PT) return;
+    const int *toff = dm.toff + 7 * e;
+    const int f = toff[6], w = f / 5;
+    const int64_t ld = e_ld(n, f), no = dm.node_off[e];
+    double *E = Ebase + (dm.E_off[e] - dm.E_off[e0]);
+    const double *sc = scalar_blocks(dm, e, e0, qp, Np, p1);
+    constexpr int oG = Np, oH = 4 * Np, oR = oH + 3 * kW;
+    __shared__ double sv[oR + 15];  // a node's rows of M | G_0..2 | H_0..2 | its 15 residuals
+    __shared__ int sTf[kW];  // trace unknown t of a component -> its entry in Uhat (component 0)
+    __shared__ int sTn[kW];  // and the face's N_fp
+    for (int t = tid; t < w; t += 256) {
+        int lf = 0;
+        while (5 * t >= toff[lf + 1]) ++lf;
+        sTn[t] = (toff[lf + 1] - toff[lf]) / 5;
+        sTf[t] = (int)(dm.face_off[dm.elem_face[6 * e + lf]] - dm.face_off[dm.elem_face[6 * e]]) + t - toff[lf] / 5;
+    }
+    const double *uh = Uhg + dm.face_off[dm.elem_face[6 * e]];
+    for (int i = blockIdx.x * nodes; i < min((int)(blockIdx.x + 1) * nodes, Np); ++i) {
+        __syncthreads();
+        for (int t = tid; t < 4 * Np; t += 256) {
+            sv[t] = sc[((int64_t)(t / Np) * Np + i) * Np + t % Np];
+        }
+        for (int t = tid; t < 3 * w; t += 256) {
+            const int j = t / w, tt = t % w;
+            int lf = 0;
+            while (5 * tt >= toff[lf + 1]) ++lf;
+            const int nfp = sTn[tt], b = tt - toff[lf] / 5;
+            int a0, a1;
+            double v = 0.0;
+            if (on_face(i, p1, lf, a0, a1))
+                v = sc[(int64_t)4 * Np * Np + 3 * p1 * p1 * (toff[lf] / 5) + ((int64_t)j * p1 * p1 + a0 + p1 * a1) * nfp + b];
+            sv[oH + j * kW + tt] = v;
+        }
+        __syncthreads();
+        for (int r = wave; r < 15; r += 4) {
+            const int c = r / 3, j = r % 3;
+            double a = 0.0;
+            for (int k = lane; k < Np; k += 64)
+                a += sv[k] * Qg[15 * no + (int64_t)r * Np + k] + sv[oG + j * Np + k] * Ug[5 * no + (int64_t)c * Np + k];
+            for (int t = lane; t < w; t += 64) a += sv[oH + j * kW + t] * uh[sTf[t] + c * sTn[t]];
+            for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
+            if (lane == 0) sv[oR + r] = a;
+        }
+        __syncthreads();
+        for (int c2 = tid; c2 < ld / 2; c2 += 256) {  // ld and the row starts are multiples of 8
+            // rows of this column pair's entries that are not zero, and where row j's value is
+            unsigned rows[2];
+            int src[2], step[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int col = 2 * c2 + h;
+                rows[h] = 0;
+                src[h] = step[h] = 0;
+                if (col < 15 * Np) {
+                    const int fld = col / Np;
+                    rows[h] = 1u << fld;
+                    src[h] = col - fld * Np;
+                } else if (col < n) {
+                    const int k = col - 15 * Np, cu = k / Np;
+                    rows[h] = 7u << (3 * cu);
+                    src[h] = oG + k - cu * Np;
+                    step[h] = Np;
+                } else if (col < n + f) {
+                    const int tc = col - n;
+                    int lf = 0;
+                    while (tc >= toff[lf + 1]) ++lf;
+                    const int nfp = (toff[lf + 1] - toff[lf]) / 5, q = tc - toff[lf], ct = q / nfp;
+                    rows[h] = 7u << (3 * ct);
+                    src[h] = oH + toff[lf] / 5 + q - ct * nfp;
+                    step[h] = kW;
+                } else if (col == n + f) {
+                    rows[h] = 0x7FFFu;
+                    src[h] = oR;
+                    step[h] = -1;
+                }
+            }
+            double *dst = E + (int64_t)i * ld + 2 * c2;
+#pragma unroll
+            for (int r = 0; r < 15; ++r) {
+                v2d v = {0.0, 0.0};
+                if ((rows[0] >> r) & 1u) v.x = sv[src[0] + (step[0] < 0 ? r : (r % 3) * step[0])];
+                if ((rows[1] >> r) & 1u) v.y = sv[src[1] + (step[1] < 0 ? r : (r % 3) * step[1])];
+                __builtin_nontemporal_store(v, (v2d *)(dst + (int64_t)r * Np * ld));
+            }
+        }
+    }
+}
+
+// Conserved rows, row field c: its 20 column-field blocks (volume and face terms)
+// over kUG workgroups, its trace columns, residual column and padding in one more.
+// The blocks of gradient fields that the fluxes of row c do not read are zero:
+// they are written as such (21 of the 100 blocks).  blockIdx.x from 5 kUG on: the
+// scalar blocks of the gradient rows.
 constexpr int kUG = 4;
 template <int PT>
-__global__ void __launch_bounds__(256) k_assemble_field_rows(DevMesh dm, Phys P, int e0, const double *__restrict__ qp,
-                                                             double *__restrict__ Ebase) {
-    const int bx = blockIdx.x, e = e0 + blockIdx.y;
-    const int r = bx < 15 ? bx : 15 + (bx - 15) / kUG;  // row field
-    const int ug = bx < 15 ? 0 : (bx - 15) % kUG;        // column-field group of a u row
+__global__ void __launch_bounds__(Block<PT>::NT) k_conserved_blocks(DevMesh dm, Phys P, int e0,
+                                                                    double *qp, double *__restrict__ Ebase) {
+    const int e = e0 + blockIdx.y, c = blockIdx.x / kUG, ug = blockIdx.x % kUG;
     if (dm.elem_p[e] != PT) return;
-    constexpr int p = PT, p1 = p + 1, Np = p1 * p1 * p1, nq = p + 2, Nq = nq * nq * nq;
-    // face-term blocks (6 p1^4) and trace-column blocks (5 p1^2 Nfp, face degree up to kMaxP)
-    constexpr int kSF = std::max(6 * p1 * p1 * p1 * p1, 5 * p1 * p1 * kP1 * kP1);
-    constexpr int kSG = std::max(6 * p1 * p1 * kNQ, 5 * p1 * kP1 * kNQ);
+    __shared__ BlockShared<PT> sh;
+    if (blockIdx.x >= 5 * kUG) {
+        scalar_block<PT>(dm, e, e0, blockIdx.x - 5 * kUG, qp, sh);
+        return;
+    }
+    typedef Block<PT> B;
+    constexpr int p = PT, p1 = B::p1, Np = B::Np, nq = B::nq, Nq = B::Nq, NT = B::NT, P2 = B::P2, P4 = B::P4;
     const int *toff = dm.toff + 7 * e;
     const int n = 20 * Np, f = toff[6];
     const int64_t ld = e_ld(n, f);
-    double *E = Ebase + (dm.E_off[e] - dm.E_off[e0]);
-    double *Er = E + (int64_t)r * Np * ld;
+    double *Er = Ebase + (dm.E_off[e] - dm.E_off[e0]) + (int64_t)(15 + c) * Np * ld;
     const double *qpe = qp + (dm.qp_off[e] - dm.qp_off[e0]);
-    const double *vg = dm.vgeo + dm.vgeo_off[e];
     const int tid = threadIdx.x;
-    const bool qrow = r < 15;
-    const int c = qrow ? r / 3 : r - 15, jdir = qrow ? r % 3 : 0;
-
-    __shared__ double sL[p1][nq], sD[p1][nq];
-    __shared__ double sLf[6][30], sMf[6][30];
-    __shared__ int sPf[6], sNqf[6];
-    __shared__ int64_t sFbase[6];
-    __shared__ double sC[4][Nq];                 // coefficient fields of one block
-    __shared__ double sT[3][p1][nq * nq];        // x stage of one i1 slice
-    __shared__ double sV[2][p1 * p1 * p1][nq];   // y stage of one i1 slice
-    __shared__ double sF[kSF];                   // face terms / trace-column blocks
-    __shared__ double sG[kSG];                   // first stage of the 2-D contractions
     constexpr int kNqfFace = kNQ * kNQ;          // Gauss points of a face, at most
-    __shared__ double sCf[6][kNqfFace];          // one block's face coefficients
-    __shared__ unsigned char sNm[Np];            // faces each node lies on (bit lf)
-    __shared__ unsigned char sNa[6][Np];         // its face-local index a0 p1 + a1 there
-    for (int t = tid; t < p1 * nq; t += blockDim.x) {
-        sL[t / nq][t % nq] = dm.tbl[tbl_L(p, p, t / nq, t % nq)];
-        sD[t / nq][t % nq] = dm.tbl[tbl_D(p, t / nq, t % nq)];
-    }
-    for (int i = tid; i < Np; i += blockDim.x) {
-        const int idx[3] = {i % p1, (i / p1) % p1, i / (p1 * p1)};
-        unsigned m = 0;
-        for (int lf = 0; lf < 6; ++lf) {
-            const int d = lf >> 1;
-            if (idx[d] == ((lf & 1) ? p : 0)) {
-                m |= 1u << lf;
-                const int a0 = (d == 0) ? idx[1] : idx[0], a1 = (d == 2) ? idx[1] : idx[2];
-                sNa[lf][i] = (unsigned char)(a0 * p1 + a1);
-            } else {
-                sNa[lf][i] = 0;
-            }
-        }
-        sNm[i] = (unsigned char)m;
-    }
-    load_face_tables(dm, e, p, Nq, sLf, sMf, sPf, sNqf, sFbase);
+    B &sb = sh.sb;
+    auto &sLf = sh.Lf;
+    auto &sPf = sh.Pf, &sNqf = sh.Nqf;
+    auto &sFbase = sh.Fbase;
+    auto &sF = sh.F;
+    auto &sG = sh.G;
+    auto &sCf = sh.Cf;
+    sb.load_basis(dm);
+    load_face_tables(dm, e, PT, Nq, sLf, sh.Mf, sPf, sNqf, sFbase);
     __syncthreads();
-
-    // face-tangential indices (a0, a1) of volume node (i1, i2, i3) on face lf, or false
-    auto face_idx = [&](int i1, int i2, int i3, int lf, int &a0, int &a1) {
-        const int d = lf >> 1, v = (lf & 1) ? p : 0;
-        const int id = (d == 0) ? i1 : ((d == 1) ? i2 : i3);
-        if (id != v) return false;
-        a0 = (d == 0) ? i2 : i1;
-        a1 = (d == 2) ? i2 : i3;
-        return true;
-    };
-
-    // one sum-factorised block from sC into column field sblk (with the face terms in sF)
-    auto volume_block = [&](int sblk, bool faces) {
-        for (int i1 = 0; i1 < p1; ++i1) {
-            __syncthreads();
-            for (int t = tid; t < p1 * nq * nq; t += blockDim.x) {
-                const int k1 = t / (nq * nq), g23 = t % (nq * nq);
-                double a0 = 0.0, a2 = 0.0, a3 = 0.0;
-                for (int g1 = 0; g1 < nq; ++g1) {
-                    const int g = g1 + nq * g23;
-                    const double lk = sL[k1][g1], li = sL[i1][g1];
-                    a0 += (li * sC[0][g] + sD[i1][g1] * sC[1][g]) * lk;
-                    a2 += li * sC[2][g] * lk;
-                    a3 += li * sC[3][g] * lk;
-                }
-                sT[0][k1][g23] = a0;
-                sT[1][k1][g23] = a2;
-                sT[2][k1][g23] = a3;
-            }
-            __syncthreads();
-            for (int t = tid; t < p1 * p1 * p1 * nq; t += blockDim.x) {
-                const int g3 = t % nq, q = t / nq;  // q = (i2 p1 + k1) p1 + k2
-                const int k2 = q % p1, k1 = (q / p1) % p1, i2 = q / (p1 * p1);
-                double vl = 0.0, vd = 0.0;
-                for (int g2 = 0; g2 < nq; ++g2) {
-                    const int g23 = g2 + nq * g3;
-                    const double lk = sL[k2][g2];
-                    vl += (sL[i2][g2] * sT[0][k1][g23] + sD[i2][g2] * sT[1][k1][g23]) * lk;
-                    vd += sL[i2][g2] * sT[2][k1][g23] * lk;
-                }
-                sV[0][q][g3] = vl;
-                sV[1][q][g3] = vd;
-            }
-            __syncthreads();
-            if constexpr (p1 * p1 * p1 * p1 <= 256) {
-                // one pass of the workgroup: a thread takes the p1 outputs k = k12 + p1^2 k3
-                // that share the z-stage operands of (q, k1, k2), each summed over g3 in
-                // the same order as below (p <= 3)
-                for (int t = tid; t < p1 * p1 * p1 * p1; t += blockDim.x) {
-                    const int k12 = t % (p1 * p1), q = t / (p1 * p1);
-                    const int i2 = q % p1, i3 = q / p1;
-                    const int k1 = k12 % p1, k2 = k12 / p1;
-                    const int vq = (i2 * p1 + k1) * p1 + k2;
-                    double zl[nq];
+    int i1, i2, k1, k2;
+    B::split(min(tid, P4 - 1), i1, i2, k1, k2);
+    // the x and y faces that both (i1, i2, .) and (k1, k2, .) lie on, or -1
+    const int fx = (i1 == k1) ? (i1 == 0 ? 0 : i1 == p ? 1 : -1) : -1;
+    const int fy = (i2 == k2) ? (i2 == 0 ? 2 : i2 == p ? 3 : -1) : -1;
+    double *dst = Er + (int64_t)(i1 + p1 * i2) * ld + k1 + p1 * k2;
+    // gradient fields that row c reads: the first 3 of them (mass), 12 (momentum), 15 (energy)
+    const int nread = (c == 0) ? 3 : (c == 4) ? 15 : 12;
+    constexpr int kLC = (4 * Nq + NT - 1) / NT, kLF = (6 * kNqfFace + NT - 1) / NT;
+    double rc[kLC], rf[kLF];  // the next block's coefficients, in flight during this one's stages
+    auto load = [&](int sblk) {
+        const int slot = (sblk < 15) ? 5 + sblk : sblk - 15;
 #pragma unroll
-                    for (int g3 = 0; g3 < nq; ++g3) zl[g3] = sL[i3][g3] * sV[0][vq][g3] + sD[i3][g3] * sV[1][vq][g3];
-                    const int irow = i1 + p1 * (i2 + p1 * i3);
-                    double *dst = Er + (int64_t)(i1 + p1 * q) * ld + sblk * Np + k12;
+        for (int q = 0; q < kLC; ++q) {
+            const int t = tid + NT * q;
+            if (t < 4 * Nq) rc[q] = qpe[(int64_t)(4 * (20 * c + sblk)) * Nq + t];
+        }
 #pragma unroll
-                    for (int k3 = 0; k3 < p1; ++k3) {
-                        const int k = k12 + p1 * p1 * k3;
-                        double v = 0.0;
-#pragma unroll
-                        for (int g3 = 0; g3 < nq; ++g3) v += zl[g3] * sL[k3][g3];
-                        if (faces) {
-                            // face terms of the faces that both node i and node k lie on (ascending lf)
-                            unsigned m = sNm[irow] & sNm[k];
-                            while (m) {
-                                const int lf = __builtin_ctz(m);
-                                m &= m - 1;
-                                v += sF[lf * p1 * p1 * p1 * p1 + sNa[lf][irow] * p1 * p1 + sNa[lf][k]];
-                            }
-                        }
-                        __builtin_nontemporal_store(v, dst + p1 * p1 * k3);
-                    }
-                }
-            } else {
-                // one output per thread and pass (p = 4: 3125 outputs, 13 passes)
-                for (int t = tid; t < p1 * p1 * Np; t += blockDim.x) {
-                    const int k = t % Np, q = t / Np;
-                    const int i2 = q % p1, i3 = q / p1;
-                    const int k1 = k % p1, k2 = (k / p1) % p1, k3 = k / (p1 * p1);
-                    const int vq = (i2 * p1 + k1) * p1 + k2;
-                    double v = 0.0;
-                    for (int g3 = 0; g3 < nq; ++g3)
-                        v += (sL[i3][g3] * sV[0][vq][g3] + sD[i3][g3] * sV[1][vq][g3]) * sL[k3][g3];
-                    if (faces) {
-                        // face terms of the faces that both node i and node k lie on (ascending lf)
-                        const int irow = i1 + p1 * (i2 + p1 * i3);
-                        unsigned m = sNm[irow] & sNm[k];
-                        while (m) {
-                            const int lf = __builtin_ctz(m);
-                            m &= m - 1;
-                            v += sF[lf * p1 * p1 * p1 * p1 + sNa[lf][irow] * p1 * p1 + sNa[lf][k]];
-                        }
-                    }
-                    __builtin_nontemporal_store(v, Er + (int64_t)(i1 + p1 * q) * ld + sblk * Np + k);
-                }
-            }
+        for (int q = 0; q < kLF; ++q) {
+            const int t = tid + NT * q, lf = t / kNqfFace, sq = t % kNqfFace;
+            if (lf < 6 && sq < sNqf[lf]) rf[q] = qpe[sFbase[lf] + (int64_t)(25 * c + slot) * sNqf[lf] + sq];
         }
     };
-
-    if (qrow) {
-        // zeros over all n interior columns first (16-byte stores; n = 20 N_p is even and
-        // the rows start on 64 bytes), then the mass block and K_j (identical for every
-        // component c) over their columns; volume_block begins with a barrier
-        const v2d zero2 = {0.0, 0.0};
-        for (int t = tid; t < Np * (n / 2); t += blockDim.x)
-            __builtin_nontemporal_store(zero2, (v2d *)(Er + (int64_t)(t / (n / 2)) * ld + 2 * (t % (n / 2))));
-        for (int kind = 0; kind < 2; ++kind) {
-            __syncthreads();
-            for (int t = tid; t < 4 * Nq; t += blockDim.x) {
-                const int d = t / Nq, g = t % Nq;
-                double v;
-                if (kind == 0) v = (d == 0) ? vg[g] : 0.0;
-                else v = (d == 0) ? 0.0 : vg[g] * vg[(1 + 3 * (d - 1) + jdir) * Nq + g];
-                sC[d][g] = v;
-            }
-            volume_block(kind == 0 ? r : 15 + c, false);
+    // the columns in the order zero fields last: nread gradient fields, 5 conserved, the rest
+    auto field = [&](int o) { return o < nread ? o : (o < nread + 5 ? 15 + o - nread : o - 5); };
+    const int o1 = (ug + 1) * (nread + 5) / kUG;
+    int o = ug * (nread + 5) / kUG;
+    if (o < o1) load(field(o));
+    for (; o < o1; ++o) {
+        const int sblk = field(o);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kLC; ++q) {
+            const int t = tid + NT * q;
+            if (t < 4 * Nq) sb.coef(t / Nq, t % Nq) = rc[q];
         }
-    } else {
-        for (int sblk = ug * 20 / kUG; sblk < (ug + 1) * 20 / kUG; ++sblk) {
-            const int slot = (sblk < 15) ? 5 + sblk : sblk - 15;
-            __syncthreads();
-            for (int t = tid; t < 4 * Nq; t += blockDim.x)
-                sC[t / Nq][t % Nq] = qpe[(int64_t)(4 * (20 * c + sblk) + t / Nq) * Nq + t % Nq];
-            // the block's face coefficients at each face's Gauss points
-            for (int t = tid; t < 6 * kNqfFace; t += blockDim.x) {
-                const int lf = t / kNqfFace, sq = t % kNqfFace;
-                if (sq < sNqf[lf]) sCf[lf][sq] = qpe[sFbase[lf] + (int64_t)(25 * c + slot) * sNqf[lf] + sq];
-            }
-            __syncthreads();
-            // face terms: F[a0 a1][b0 b1] = sum_s c(s) phi_a(s) phi_b(s) per face, two 1-D stages
-            for (int t = tid; t < 6 * p1 * p1 * kNQ; t += blockDim.x) {
-                const int lf = t / (p1 * p1 * kNQ), rem = t % (p1 * p1 * kNQ);
-                const int a0 = rem / (p1 * kNQ), b0 = (rem / kNQ) % p1, s1 = rem % kNQ;
-                const int nqf1 = sPf[lf] + 2;
-                double v = 0.0;
-                if (s1 < nqf1) {
-                    const double *cf = sCf[lf];
-                    for (int s0 = 0; s0 < nqf1; ++s0)
-                        v += sLf[lf][a0 * nqf1 + s0] * sLf[lf][b0 * nqf1 + s0] * cf[s0 + nqf1 * s1];
+#pragma unroll
+        for (int q = 0; q < kLF; ++q) {
+            const int t = tid + NT * q;
+            if (t < 6 * kNqfFace) sCf[t / kNqfFace][t % kNqfFace] = rf[q];
+        }
+        __syncthreads();
+        if (o + 1 < o1) load(field(o + 1));
+        // face terms: F[a0 a1][b0 b1] = sum_s c(s) phi_a(s) phi_b(s) per face, two 1-D stages
+        for (int t = tid; t < 6 * p1 * kNQ; t += NT) {
+            const int lf = t / (p1 * kNQ), a0 = t % p1, s1 = (t / p1) % kNQ;
+            const int nqf1 = sPf[lf] + 2;
+            double g[p1];
+#pragma unroll
+            for (int b0 = 0; b0 < p1; ++b0) g[b0] = 0.0;
+            if (s1 < nqf1)
+                for (int s0 = 0; s0 < nqf1; ++s0) {
+                    const double u = P.dt * sLf[lf][a0 * nqf1 + s0] * sCf[lf][s0 + nqf1 * s1];
+#pragma unroll
+                    for (int b0 = 0; b0 < p1; ++b0) g[b0] += u * sLf[lf][b0 * nqf1 + s0];
                 }
-                sG[t] = P.dt * v;
-            }
-            __syncthreads();
-            for (int t = tid; t < 6 * p1 * p1 * p1 * p1; t += blockDim.x) {
-                const int lf = t / (p1 * p1 * p1 * p1), rem = t % (p1 * p1 * p1 * p1);
-                const int b1 = rem % p1, b0 = (rem / p1) % p1, a1 = (rem / (p1 * p1)) % p1, a0 = rem / (p1 * p1 * p1);
-                const int nqf1 = sPf[lf] + 2;
-                const double *gg = sG + lf * p1 * p1 * kNQ + (a0 * p1 + b0) * kNQ;
-                double v = 0.0;
-                for (int s1 = 0; s1 < nqf1; ++s1) v += sLf[lf][a1 * nqf1 + s1] * sLf[lf][b1 * nqf1 + s1] * gg[s1];
-                sF[t] = v;
-            }
-            volume_block(sblk, true);
+#pragma unroll
+            for (int b0 = 0; b0 < p1; ++b0) sG[(lf * kNQ + s1) * P2 + a0 * p1 + b0] = g[b0];
         }
+        __syncthreads();
+        for (int t = tid; t < 6 * P2 * p1; t += NT) {
+            const int lf = t / (P2 * p1), b0 = t % p1, a1 = (t / p1) % p1, a0 = (t / P2) % p1;
+            const int nqf1 = sPf[lf] + 2;
+            double g[p1];
+#pragma unroll
+            for (int b1 = 0; b1 < p1; ++b1) g[b1] = 0.0;
+            for (int s1 = 0; s1 < nqf1; ++s1) {
+                const double u = sLf[lf][a1 * nqf1 + s1] * sG[(lf * kNQ + s1) * P2 + a0 * p1 + b0];
+#pragma unroll
+                for (int b1 = 0; b1 < p1; ++b1) g[b1] += u * sLf[lf][b1 * nqf1 + s1];
+            }
+#pragma unroll
+            for (int b1 = 0; b1 < p1; ++b1) sF[lf * P4 + (a0 * p1 + a1) * P2 + b0 * p1 + b1] = g[b1];
+        }
+        sb.contract([&](double (&z)[p1][p1]) {
+#pragma unroll
+            for (int i3 = 0; i3 < p1; ++i3)
+#pragma unroll
+                for (int k3 = 0; k3 < p1; ++k3) {
+                    double v = z[i3][k3];
+                    if (fx >= 0) v += sF[fx * P4 + (i2 * p1 + i3) * P2 + k2 * p1 + k3];
+                    if (fy >= 0) v += sF[fy * P4 + (i1 * p1 + i3) * P2 + k1 * p1 + k3];
+                    if (i3 == 0 && k3 == 0) v += sF[4 * P4 + (i1 * p1 + i2) * P2 + k1 * p1 + k2];
+                    if (i3 == p && k3 == p) v += sF[5 * P4 + (i1 * p1 + i2) * P2 + k1 * p1 + k2];
+                    dst[(int64_t)P2 * i3 * ld + sblk * Np + P2 * k3] = v;
+                }
+        });
     }
-    if (ug != 0) return;  // uniform per workgroup
+    // the fields that row c does not read (gradient fields nread .. 14), spread over the groups
+    const int z0 = nread * Np, zn = (15 - nread) * Np;
+    for (int t = ug * NT + tid; t < zn * Np; t += kUG * NT)
+        __builtin_nontemporal_store(0.0, Er + (int64_t)(t / zn) * ld + z0 + t % zn);
+}
+
+// Conserved rows, row field c = blockIdx.x: trace columns, residual column, padding.
+template <int PT> struct ConservedTraceShared {
+    static constexpr int p1 = PT + 1, Np = p1 * p1 * p1, nq = PT + 2, Nq = nq * nq * nq;
+    double L[p1][nq], D[p1][nq], C[4][Nq];
+    double Lf[6][30], Mf[6][30];
+    int Pf[6], Nqf[6];
+    int64_t Fbase[6];
+    double F[5 * p1 * p1 * kP1 * kP1];               // trace-column blocks (face degree up to kMaxP)
+    double G[std::max(5 * p1 * kP1 * kNQ, 2 * Np)];  // their first stage
+    signed char Na[Np];                              // each node's index a0 p1 + a1 on the face, or -1
+};
+template <int PT>
+__global__ void __launch_bounds__(256) k_conserved_trace(DevMesh dm, Phys P, int e0, const double *__restrict__ qp,
+                                                         double *__restrict__ Ebase) {
+    const int e = e0 + blockIdx.y, c = blockIdx.x, r = 15 + c;
+    if (dm.elem_p[e] != PT) return;
+    __shared__ ConservedTraceShared<PT> sh;
+    constexpr int NT = 256;
+    constexpr int p1 = PT + 1, Np = p1 * p1 * p1, nq = PT + 2, Nq = nq * nq * nq;
+    const int *toff = dm.toff + 7 * e;
+    const int n = 20 * Np, f = toff[6];
+    const int64_t ld = e_ld(n, f);
+    double *Er = Ebase + (dm.E_off[e] - dm.E_off[e0]) + (int64_t)r * Np * ld;
+    const double *qpe = qp + (dm.qp_off[e] - dm.qp_off[e0]);
+    const int tid = threadIdx.x;
+    auto &sL = sh.L, &sD = sh.D;
+    auto &sC = sh.C;
+    auto &sLf = sh.Lf, &sMf = sh.Mf;
+    auto &sPf = sh.Pf, &sNqf = sh.Nqf;
+    auto &sFbase = sh.Fbase;
+    auto &sF = sh.F;
+    auto &sG = sh.G;
+    auto &sNa = sh.Na;
+    for (int t = tid; t < p1 * nq; t += NT) {
+        sL[t / nq][t % nq] = dm.tbl[tbl_L(PT, PT, t / nq, t % nq)];
+        sD[t / nq][t % nq] = dm.tbl[tbl_D(PT, t / nq, t % nq)];
+    }
+    load_face_tables(dm, e, PT, Nq, sLf, sMf, sPf, sNqf, sFbase);
     // ---- trace columns B: face by face, B_lf[cp][a0 a1][b0 b1] = sum_s c_cp(s) phi_a(s) mu_b(s)
     for (int lf = 0; lf < 6; ++lf) {
         const int pf1 = sPf[lf] + 1, nqf1 = sPf[lf] + 2, Nqf = sNqf[lf], Nfp = pf1 * pf1;
         __syncthreads();
-        for (int t = tid; t < 5 * p1 * pf1 * nqf1; t += blockDim.x) {
+        for (int i = tid; i < Np; i += NT) {
+            int a0, a1;
+            sNa[i] = (signed char)(on_face(i, p1, lf, a0, a1) ? a0 * p1 + a1 : -1);
+        }
+        for (int t = tid; t < 5 * p1 * pf1 * nqf1; t += NT) {
             const int cp = t / (p1 * pf1 * nqf1), rem = t % (p1 * pf1 * nqf1);
             const int a0 = rem / (pf1 * nqf1), b0 = (rem / nqf1) % pf1, s1 = rem % nqf1;
+            const double *cf = qpe + sFbase[lf] + (int64_t)(25 * c + 20 + cp) * Nqf;
             double v = 0.0;
-            if (!qrow || cp == c) {
-                const double *cf = qrow ? dm.fgeo + dm.fgeo_off[6 * e + lf] + (int64_t)jdir * Nqf
-                                        : qpe + sFbase[lf] + (int64_t)(25 * c + 20 + cp) * Nqf;
-                for (int s0 = 0; s0 < nqf1; ++s0)
-                    v += sLf[lf][a0 * nqf1 + s0] * sMf[lf][b0 * nqf1 + s0] * cf[s0 + nqf1 * s1];
-                v *= qrow ? -1.0 : P.dt;
-            }
-            sG[t] = v;
+            for (int s0 = 0; s0 < nqf1; ++s0)
+                v += sLf[lf][a0 * nqf1 + s0] * sMf[lf][b0 * nqf1 + s0] * cf[s0 + nqf1 * s1];
+            sG[t] = P.dt * v;
         }
         __syncthreads();
-        for (int t = tid; t < 5 * p1 * p1 * Nfp; t += blockDim.x) {
+        for (int t = tid; t < 5 * p1 * p1 * Nfp; t += NT) {
             const int cp = t / (p1 * p1 * Nfp), rem = t % (p1 * p1 * Nfp);
             const int a = rem / Nfp, b = rem % Nfp;
             const int a0 = a / p1, a1 = a % p1, b0 = b % pf1, b1 = b / pf1;
@@ -680,21 +905,21 @@ __global__ void __launch_bounds__(256) k_assemble_field_rows(DevMesh dm, Phys P,
         __syncthreads();
         // a thread keeps one column (ncol = 5 N_fp <= 125) and walks rows; a row
         // off the face is zero, a row on it reads its face-local index a0 p1 + a1
-        const int ncol = 5 * Nfp, groups = blockDim.x / ncol;
+        const int ncol = 5 * Nfp, groups = NT / ncol;
         if (tid < groups * ncol) {
             const int col = tid % ncol, cp = col / Nfp, b = col % Nfp;
             const double *fc = sF + cp * p1 * p1 * Nfp + b;
             double *dst = Er + n + toff[lf] + col;
             for (int i = tid / ncol; i < Np; i += groups)
-                __builtin_nontemporal_store(((sNm[i] >> lf) & 1u) ? fc[sNa[lf][i] * Nfp] : 0.0, dst + (int64_t)i * ld);
+                __builtin_nontemporal_store(sNa[i] >= 0 ? fc[sNa[i] * Nfp] : 0.0, dst + (int64_t)i * ld);
         }
     }
+    __syncthreads();
     // ---- residual column and padding: the residual's point coefficients in LDS,
     // the sum over the Gauss points split over two halves of the threads
-    __syncthreads();
     {
         const double *rc = qpe + (int64_t)kVJac * Nq + (int64_t)(4 * r) * Nq;
-        for (int t = tid; t < 4 * Nq; t += blockDim.x) sC[t / Nq][t % Nq] = rc[t];
+        for (int t = tid; t < 4 * Nq; t += NT) sC[t / Nq][t % Nq] = rc[t];
     }
     __syncthreads();
     static_assert(2 * Np <= 256, "two threads per row");
@@ -711,134 +936,167 @@ __global__ void __launch_bounds__(256) k_assemble_field_rows(DevMesh dm, Phys P,
         sG[tid] = v;
     }
     __syncthreads();
-    for (int i = tid; i < Np; i += blockDim.x) {
+    for (int i = tid; i < Np; i += NT) {
         double v = sG[i] + sG[Np + i];
-        const int i1 = i % p1, i2 = (i / p1) % p1, i3 = i / (p1 * p1);
         for (int lf = 0; lf < 6; ++lf) {
             int a0, a1;
-            if (!face_idx(i1, i2, i3, lf, a0, a1)) continue;
+            if (!on_face(i, p1, lf, a0, a1)) continue;
             const int Nqf = sNqf[lf], nqf1 = sPf[lf] + 2;
             const double *fb = qpe + sFbase[lf];
-            const double *fgl = dm.fgeo + dm.fgeo_off[6 * e + lf];
-            for (int s = 0; s < Nqf; ++s) {
-                const double ph = sLf[lf][a0 * nqf1 + s % nqf1] * sLf[lf][a1 * nqf1 + s / nqf1];
-                if (qrow) v -= fgl[jdir * Nqf + s] * fb[(135 + c) * Nqf + s] * ph;
-                else v += P.dt * fb[(125 + c) * Nqf + s] * ph;
-            }
+            for (int s = 0; s < Nqf; ++s)
+                v += P.dt * fb[(125 + c) * Nqf + s] * sLf[lf][a0 * nqf1 + s % nqf1] * sLf[lf][a1 * nqf1 + s / nqf1];
         }
         Er[(int64_t)i * ld + n + f] = v;
         for (int64_t col = n + f + 1; col < ld; ++col) Er[(int64_t)i * ld + col] = 0.0;
     }
 }
 
-// Trace rows of local face lf: [C | D | R_uh] rows of this element's side, one
-// workgroup per (face, element): the numerical flux on an interior face, the
+// Trace rows of local face lf: [C | D | R_uh] rows of this element's side, kTC of
+// the five components per workgroup: the numerical flux on an interior face, the
 // boundary residual on a boundary face.  Only the columns of the face's own
-// nodes (C), of the face's trace block (D) and the residual column are
-// nonzero.  Rows go component by component (c = row / N_fp), kTR rows per
-// pass.  In a pass each thread takes one (row, slot) pair (slots 0..19: C by
-// column field, 20..24: D by trace component, 25: the residual column), forms
-// its weights w(s) = coefficient(c, slot)(s) mu_a(s) at the face's Gauss
-// points in registers and all of the pair's entries as dot products over the
-// Gauss points with phi_k(s) (C) or mu_b(s) (D), into a compact LDS row; a
-// column map then writes every row in one coalesced sweep, zeros included.
-constexpr int kTR = 8;                              // trace rows per pass
+// nodes (C), of the face's trace block (D) and the residual column are nonzero.
+// Entry (a, k) of a slot (0..19: C by column field, u then q; 20..24: D by trace
+// component) is sum_s coef(s) mu_a(s) phi_k(s), contracted one direction at a time:
+// all slots' first stage G[s1][a0][k0] in LDS, then per a1 the entries of the rows
+// a = (a0, a1) into compact LDS rows; a column map then writes those rows in one
+// coalesced sweep, zeros included, each thread's column pair looked up once for
+// all of them.  Bound by the writes: the rows are consecutive and start on 64
+// bytes, so half lines of neighbouring stores meet in L2, and plain stores are
+// faster than nontemporal ones (5.0 GB at p = 4 in 1.14 against 2.30 ms; dot products
+// over all Gauss points of the face, five times the multiplications, took 2.29).
 constexpr int kNqfMax = kNQ * kNQ, kNfpMax = kP1 * kP1;
-constexpr int kLdMax = (20 * kP1 * kP1 * kP1 + 30 * kNfpMax + 1 + 7) / 8 * 8;
-constexpr int kTOut = 20 * kNfpMax + 5 * kNfpMax + 1;  // nonzero entries of a trace row, at most
-
-__global__ void __launch_bounds__(256) k_assemble_trace_rows(DevMesh dm, Phys P, int e0, const double *__restrict__ qp,
-                                                             double *__restrict__ Ebase) {
-    const int e = e0 + blockIdx.y, lf = blockIdx.x;
-    const int p = dm.elem_p[e], p1 = p + 1, Np = p1 * p1 * p1, nq = p + 2, Nq = nq * nq * nq;
+template <int PT> struct TraceCfg {
+    static constexpr int p1 = PT + 1, Np = p1 * p1 * p1;
+    static constexpr int TC = PT <= 2 ? 5 : 1;                                // components per workgroup
+    static constexpr int GS = kP1 * (20 * p1 + 5 * kP1);                      // G entries per s1, at most
+    static constexpr int RO = 20 * p1 * p1 + 5 * kNfpMax + 1;                 // nonzero entries of a row, at most
+    static constexpr int LD = (20 * Np + 30 * kNfpMax + 1 + 7) / 8 * 8;       // columns, at most
+};
+template <int PT> struct TraceShared {
+    typedef TraceCfg<PT> Cfg;
+    double L[30], M[30];             // element and trace basis at the face's Gauss points
+    double K[26][kNqfMax];           // coefficients of the component
+    double G[kNQ][Cfg::GS];          // first stage: [s1][C: (slot, a0, k0) | D: (cp, a0, b0)]
+    double R[kNQ][kP1];              // first stage of the residual: [s1][a0]
+    double Out[kP1][Cfg::RO];        // the nonzero entries of the pass's rows
+    short Map[Cfg::LD];              // column -> index into a row of Out, or -1
+};
+template <int PT>
+__global__ void __launch_bounds__(256) k_trace_rows(DevMesh dm, int e0, const double *__restrict__ qp,
+                                                    double *__restrict__ Ebase) {
+    typedef TraceCfg<PT> Cfg;
+    __shared__ TraceShared<PT> sh;
+    if (dm.elem_p[e0 + blockIdx.y] != PT) return;
+    constexpr int p1 = Cfg::p1, Np = Cfg::Np, n = 20 * Np, nq = PT + 2, Nq = nq * nq * nq, nC = 20 * p1 * p1;
+    const int e = e0 + blockIdx.y, lf = blockIdx.x % 6, c0 = blockIdx.x / 6 * Cfg::TC;
     const int *toff = dm.toff + 7 * e;
-    const int n = 20 * Np, f = toff[6];
-    const int ld = (int)e_ld(n, f);
+    const int f = toff[6], ld = (int)e_ld(n, f);
     double *E = Ebase + (dm.E_off[e] - dm.E_off[e0]);
-    const double *qpe = qp + (dm.qp_off[e] - dm.qp_off[e0]);
     const int tid = threadIdx.x;
-    __shared__ double sLf[6][30], sMf[6][30];
-    __shared__ int sPf[6], sNqf[6];
-    __shared__ int64_t sFbase[6];
-    __shared__ double sPhi[kNfpMax][kNqfMax], sMu[kNfpMax][kNqfMax];
-    __shared__ double sK[26][kNqfMax];  // coefficients of the current component c
-    __shared__ double sOut[kTR][kTOut];  // the nonzero entries of the pass's rows
-    __shared__ int sMap[kLdMax];         // column -> index into a row of sOut, or -1
-    load_face_tables(dm, e, p, Nq, sLf, sMf, sPf, sNqf, sFbase);
-    __syncthreads();
-    const int pf1 = sPf[lf] + 1, nqf1 = pf1 + 1, Nfp = pf1 * pf1, Nqf = sNqf[lf];
-    const int F = dm.elem_face[6 * e + lf], bc = dm.face_bc[F];
-    const double *fb = qpe + sFbase[lf];
+    const int F = dm.elem_face[6 * e + lf], bc = dm.face_bc[F], pf = dm.face_p[F];
+    const int pf1 = pf + 1, nqf1 = pf + 2, Nfp = pf1 * pf1, Nqf = nqf1 * nqf1;
+    const double *fb = qp + (qp_face_base(dm, e, lf, Nq) - dm.qp_off[e0]);
     double *Et = E + (int64_t)(n + toff[lf]) * ld;
-    const int nC = 20 * p1 * p1;  // C entries of a row: column field x, face node y at x p1^2 + y
-    // element basis phi_k and trace basis mu_b at the face's Gauss points
-    for (int t = tid; t < kNfpMax * Nqf; t += blockDim.x) {
-        const int k = t / Nqf, sq = t % Nqf, s0 = sq % nqf1, s1 = sq / nqf1;
-        sPhi[k][sq] = (k < p1 * p1) ? sLf[lf][(k % p1) * nqf1 + s0] * sLf[lf][(k / p1) * nqf1 + s1] : 0.0;
-        sMu[k][sq] = (k < Nfp) ? sMf[lf][(k % pf1) * nqf1 + s0] * sMf[lf][(k / pf1) * nqf1 + s1] : 0.0;
+    auto &sL = sh.L, &sM = sh.M;
+    auto &sK = sh.K;
+    auto &sG = sh.G;
+    auto &sR = sh.R;
+    auto &sOut = sh.Out;
+    auto &sMap = sh.Map;
+    for (int t = tid; t < 30; t += 256) {
+        const int a = t / nqf1, q = t % nqf1;
+        sL[t] = (a < p1) ? dm.tbl[tbl_L(PT, pf, a, q)] : 0.0;
+        sM[t] = (a < pf1) ? dm.tbl[tbl_L(pf, pf, a, q)] : 0.0;
     }
-    for (int col = tid; col < ld; col += blockDim.x) {
+    for (int col = tid; col < ld; col += 256) {
         int idx = -1;
         if (col < n) {
-            const int sblk = col / Np, k = col % Np;
+            const int sblk = col / Np, k = col - sblk * Np;
             int ka0, ka1;
-            if (on_face(k, p1, lf, ka0, ka1)) {
-                const int slot = (sblk < 15) ? 5 + sblk : sblk - 15;
-                idx = slot * p1 * p1 + ka0 + p1 * ka1;
-            }
+            if (on_face(k, p1, lf, ka0, ka1)) idx = ((sblk < 15) ? 5 + sblk : sblk - 15) * p1 * p1 + ka0 + p1 * ka1;
         } else if (col < n + f) {
             const int cc = col - n;
             if (cc >= toff[lf] && cc < toff[lf + 1]) idx = nC + (cc - toff[lf]);
         } else if (col == n + f) {
             idx = nC + 5 * Nfp;
         }
-        sMap[col] = idx;
+        sMap[col] = (short)idx;
     }
-    const int rr_t = tid / 26, slot_t = tid % 26;  // this thread's (row of the pass, slot)
-    for (int c = 0; c < 5; ++c) {
+    const int gC = 20 * pf1 * p1, gD = 5 * pf1 * pf1;
+    for (int c = c0; c < c0 + Cfg::TC; ++c) {
         __syncthreads();
-        for (int t = tid; t < 26 * Nqf; t += blockDim.x) {
+        for (int t = tid; t < 26 * Nqf; t += 256) {
             const int slot = t / Nqf, sq = t % Nqf;
             sK[slot][sq] = (slot == 25) ? fb[(int64_t)((bc ? 130 : 125) + c) * Nqf + sq]
                                         : fb[(int64_t)((bc ? 140 : 0) + 25 * c + slot) * Nqf + sq];
         }
-        for (int a0 = 0; a0 < Nfp; a0 += kTR) {
-            const int nr = min(kTR, Nfp - a0);
-            __syncthreads();  // sK ready; the previous pass's sweep is done with sOut
-            if (rr_t < nr) {
-                const int a = a0 + rr_t;  // trace row c Nfp + a tests mu_a
-                double w[kNqfMax];
+        __syncthreads();
+        for (int t = tid; t < 26 * pf1 * nqf1; t += 256) {
+            const int a0 = t % pf1, s1 = (t / pf1) % nqf1, slot = t / (pf1 * nqf1);
+            double g[kP1];
 #pragma unroll
-                for (int sq = 0; sq < kNqfMax; ++sq) w[sq] = sq < Nqf ? sK[slot_t][sq] * sMu[a][sq] : 0.0;
-                double *out = sOut[rr_t];
-                if (slot_t == 25) {
-                    double v = 0.0;
-#pragma unroll
-                    for (int sq = 0; sq < kNqfMax; ++sq)
-                        if (sq < Nqf) v += w[sq];
-                    out[nC + 5 * Nfp] = v;
+            for (int k = 0; k < kP1; ++k) g[k] = 0.0;
+            const double *tab = slot < 20 ? sL : sM;
+            for (int s0 = 0; s0 < nqf1; ++s0) {
+                const double u = sK[slot][s0 + nqf1 * s1] * sM[a0 * nqf1 + s0];
+                if (slot == 25) {
+                    g[0] += u;
                 } else {
-                    const bool isC = slot_t < 20;
-                    const int ny = isC ? p1 * p1 : Nfp;
-                    double *o = isC ? out + slot_t * p1 * p1 : out + nC + (slot_t - 20) * Nfp;
-                    for (int y = 0; y < ny; ++y) {
-                        const double *brow = isC ? sPhi[y] : sMu[y];
-                        double v = 0.0;
 #pragma unroll
-                        for (int sq = 0; sq < kNqfMax; ++sq)
-                            if (sq < Nqf) v += w[sq] * brow[sq];
-                        o[y] = v;
+                    for (int k = 0; k < kP1; ++k)
+                        if (k < (slot < 20 ? p1 : pf1)) g[k] += u * tab[k * nqf1 + s0];
+                }
+            }
+            if (slot == 25) {
+                sR[s1][a0] = g[0];
+            } else {
+                const int nk = slot < 20 ? p1 : pf1;
+                double *o = sG[s1] + (slot < 20 ? (slot * pf1 + a0) * p1 : gC + ((slot - 20) * pf1 + a0) * pf1);
+#pragma unroll
+                for (int k = 0; k < kP1; ++k)
+                    if (k < nk) o[k] = g[k];
+            }
+        }
+        for (int a1 = 0; a1 < pf1; ++a1) {
+            __syncthreads();  // the first stage (or the previous sweep) is done
+            for (int t = tid; t < gC + gD + pf1; t += 256) {
+                const bool isC = t < gC;
+                double v[kP1];
+#pragma unroll
+                for (int k = 0; k < kP1; ++k) v[k] = 0.0;
+                if (t < gC + gD) {
+                    const int nk = isC ? p1 : pf1, q = isC ? t : t - gC;
+                    const double *tab = isC ? sL : sM;
+                    for (int s1 = 0; s1 < nqf1; ++s1) {
+                        const double u = sG[s1][t] * sM[a1 * nqf1 + s1];
+#pragma unroll
+                        for (int k = 0; k < kP1; ++k)
+                            if (k < nk) v[k] += u * tab[k * nqf1 + s1];
                     }
+                    const int k0 = q % nk, a0 = (q / nk) % pf1, sl = q / (nk * pf1);
+                    double *o = sOut[a0] + (isC ? sl * p1 * p1 : nC + sl * Nfp) + k0;
+#pragma unroll
+                    for (int k = 0; k < kP1; ++k)
+                        if (k < nk) o[k * nk] = v[k];
+                } else {
+                    const int a0 = t - gC - gD;
+                    for (int s1 = 0; s1 < nqf1; ++s1) v[0] += sR[s1][a0] * sM[a1 * nqf1 + s1];
+                    sOut[a0][nC + 5 * Nfp] = v[0];
                 }
             }
             __syncthreads();
-            for (int rr = 0; rr < nr; ++rr) {
-                double *dst = Et + (int64_t)(c * Nfp + a0 + rr) * ld;
-                const double *out = sOut[rr];
-                for (int c2 = tid; c2 < ld / 2; c2 += blockDim.x) {  // ld and the row starts are multiples of 8
-                    const int i0 = sMap[2 * c2], i1 = sMap[2 * c2 + 1];
-                    const v2d v = {i0 >= 0 ? out[i0] : 0.0, i1 >= 0 ? out[i1] : 0.0};
-                    __builtin_nontemporal_store(v, (v2d *)(dst + 2 * c2));
+            double *row = Et + (int64_t)(c * Nfp + a1 * pf1) * ld;
+            for (int c2 = tid; c2 < ld / 2; c2 += 256) {  // ld and the row starts are multiples of 8
+                const int i0 = sMap[2 * c2], i1 = sMap[2 * c2 + 1];
+                double *dst = row + 2 * c2;
+                if (i0 < 0 && i1 < 0) {
+                    const v2d zero = {0.0, 0.0};
+                    for (int a0 = 0; a0 < pf1; ++a0) *(v2d *)(dst + (int64_t)a0 * ld) = zero;
+                } else {
+                    for (int a0 = 0; a0 < pf1; ++a0) {
+                        const v2d v = {i0 >= 0 ? sOut[a0][i0] : 0.0, i1 >= 0 ? sOut[a0][i1] : 0.0};
+                        *(v2d *)(dst + (int64_t)a0 * ld) = v;
+                    }
                 }
             }
         }
@@ -857,11 +1115,20 @@ int launch_element_system(const hdg_ctx *ctx, int e0, int ne, const double *Q, c
     const double *qpc = qp;
     unsigned degrees = 0;
     for (int e = e0; e < e0 + ne; ++e) degrees |= 1u << ctx->elem_p[e];
-    if (degrees & 2u) hipLaunchKernelGGL(k_assemble_field_rows<1>, dim3(15 + 5 * kUG, ne), dim3(256), 0, s, dm, P, e0, qpc, E);
-    if (degrees & 4u) hipLaunchKernelGGL(k_assemble_field_rows<2>, dim3(15 + 5 * kUG, ne), dim3(256), 0, s, dm, P, e0, qpc, E);
-    if (degrees & 8u) hipLaunchKernelGGL(k_assemble_field_rows<3>, dim3(15 + 5 * kUG, ne), dim3(256), 0, s, dm, P, e0, qpc, E);
-    if (degrees & 16u) hipLaunchKernelGGL(k_assemble_field_rows<4>, dim3(15 + 5 * kUG, ne), dim3(256), 0, s, dm, P, e0, qpc, E);
-    hipLaunchKernelGGL(k_assemble_trace_rows, dim3(6, ne), dim3(256), 0, s, dm, P, e0, qpc, E);
+    auto rows = [&](auto degree) {
+        constexpr int PT = decltype(degree)::value, Np = (PT + 1) * (PT + 1) * (PT + 1);
+        // k_grad_rows: at least 200 KB a workgroup where that leaves four workgroups per CU
+        const int nodes = (PT > 2 || ne * Np < 4 * 256 * 8) ? 1 : (PT == 1) ? 8 : 3;
+        if (!(degrees & (1u << PT))) return;
+        hipLaunchKernelGGL(k_conserved_blocks<PT>, dim3(5 * kUG + 5, ne), dim3(Block<PT>::NT), 0, s, dm, P, e0, qp, E);
+        hipLaunchKernelGGL(k_grad_rows<PT>, dim3((Np + nodes - 1) / nodes, ne), dim3(256), 0, s, dm, e0, nodes, Q, U, Uhat, qp, E);
+        hipLaunchKernelGGL(k_conserved_trace<PT>, dim3(5, ne), dim3(256), 0, s, dm, P, e0, qpc, E);
+        hipLaunchKernelGGL(k_trace_rows<PT>, dim3(30 / TraceCfg<PT>::TC, ne), dim3(256), 0, s, dm, e0, qpc, E);
+    };
+    rows(std::integral_constant<int, 1>{});
+    rows(std::integral_constant<int, 2>{});
+    rows(std::integral_constant<int, 3>{});
+    rows(std::integral_constant<int, 4>{});
     return (int)hipGetLastError();
 }
 
