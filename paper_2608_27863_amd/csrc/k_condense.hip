@@ -24,9 +24,10 @@
 //
 // Two-level blocking, all elements of a chunk advancing together.  Per block
 // of kNBO = 128 pivot columns (two panels of kNB = 64):
-//   k_panel      one workgroup per element factors a 64-column panel (8-column
-//                sub-panels held in registers) in two 32-column halves, records
-//                its pivots, the net row permutation, L11^{-1} and U11^{-1}
+//   k_panel_reg  one workgroup per element factors a 64-column panel in two
+//                32-column halves held in registers, records its pivots, the
+//                net row permutation, L11^{-1} and U11^{-1} (k_panel, in 8-column
+//                sub-panels, while more than 1024 rows are left)
 //   k_half       the first half's update of the second half's columns
 //   k_crows      multipliers of the trace rows, L_C = C_panel U11^{-1}
 //   k_rowperm    within the block: applies panel a's permutation to panel b's
@@ -213,6 +214,29 @@ template <typename T> __device__ inline void wave_argmax(T &v, int &r) {
     argmax_swap<32>(v, r);
 }
 
+// Maximum over groups of N lanes (a power of two), by the same steps.
+template <int CTRL> __device__ inline unsigned max_dpp(unsigned v) {
+    return max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true));
+}
+template <int W> __device__ inline unsigned max_swap(unsigned v) {
+    unsigned a, b;
+    swap_pair<W>(v, a, b);
+    return max(a, b);
+}
+template <int N> __device__ inline unsigned lanes_max(unsigned v) {
+    if (N > 1) v = max_dpp<0xB1>(v);
+    if (N > 2) v = max_dpp<0x4E>(v);
+    if (N > 4) v = max_dpp<0x124>(v);
+    if (N > 8) v = max_dpp<0x128>(v);
+    if (N > 16) v = max_swap<16>(v);
+    if (N > 32) v = max_swap<32>(v);
+    return v;
+}
+// The upper word of a value >= 0: a larger one is a larger value.
+__device__ inline unsigned upper_word(double x) { return (unsigned)((unsigned long long)__double_as_longlong(x) >> 32); }
+__device__ inline unsigned upper_word(float x) { return __float_as_uint(x); }
+template <typename T> constexpr unsigned kInfWord = sizeof(T) == 8 ? 0x7FF00000u : 0x7F800000u;
+
 // Net row permutation of the swaps (row base+t <-> row piv[t]), t = 0 .. w-1, applied
 // in order, with piv[t] >= base+t.  top_src[t] is the row whose content ends in row
 // base+t; disp holds (dst, src) for every row >= base+w that a swap touched, in the
@@ -268,6 +292,152 @@ __device__ inline bool xcd_item(int ne, int tiles, int &el, int &t) {
 inline int xcd_grid(int ne, int tiles) { return 8 * ((ne + 7) / 8) * tiles; }
 
 // ------------------------------------------------------------------ panel
+// L^{-1} and U^{-1} of a factored 64 x 64 block in LDS, in place (below the diagonal
+// L^{-1}, its unit diagonal implied; on and above it U^{-1}), by NT >= 128 threads: the
+// 16 x 16 diagonal blocks by substitution, one thread per column, wave 0 for L and
+// wave 1 for U, then twice the size at a time by the matrix cores,
+// X21 = -X22 (L21 X11) and Y12 = -Y11 (U12 Y22).  One chain of 16 steps and four
+// products take the place of two chains of 64 steps over 8 x 8 blocks; one panel's
+// inverses (n = 136, 128 threads): 124 000 cycles before, 38 000 now.
+template <int NT, typename T>
+__device__ __forceinline__ void invert_triangles(T (*t)[kNB + 1]) {
+    typedef typename MF<T>::acc_t acc_t;
+    constexpr int NW = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    {
+        const int j = lane, b = j & ~15, jl = j & 15;
+        T x[16];
+        if (wave == 0) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                T v = (r == jl) ? T(1) : T(0);
+#pragma unroll
+                for (int c = 0; c < r; ++c) v -= t[b + r][b + c] * x[c];
+                x[r] = (r >= jl) ? v : T(0);
+            }
+        } else if (wave == 1) {
+#pragma unroll
+            for (int r = 15; r >= 0; --r) {
+                T v = (r == jl) ? T(1) : T(0);
+#pragma unroll
+                for (int c = r + 1; c < 16; ++c) v -= t[b + r][b + c] * x[c];
+                x[r] = (r <= jl) ? v / t[b + r][b + r] : T(0);
+            }
+        }
+        __syncthreads();
+        if (wave < 2) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (wave == 0 ? r > jl : r <= jl) t[b + r][j] = x[r];
+        }
+        __syncthreads();
+    }
+    const int fr = lane & 15, fk = lane >> 4;
+#pragma unroll
+    for (int h = 1; h <= 2; ++h) {  // blocks of 16 h join into blocks of 32 h
+        constexpr int kMaxQ = (8 + NW - 1) / NW;
+        const int nq = 4 * h, S = 16 * h;  // 16 x 16 tiles: (64 / 2S) joins, h * h tiles, L and U
+        // tile q: upper triangle (U) or not, join offset o, tile row and column
+        auto place = [&](int q, bool &up, int &o, int &ti, int &tj) {
+            up = q & 1;
+            const int m = q >> 1;
+            tj = m % h;
+            ti = (m / h) % h;
+            o = 2 * S * (m / (h * h));
+        };
+        acc_t acc[kMaxQ];
+        // P = L21 X11 (U12 Y22), over its operand
+#pragma unroll
+        for (int i = 0; i < kMaxQ; ++i) {
+            const int q = wave + NW * i;
+            acc[i] = (acc_t){T(0), T(0), T(0), T(0)};
+            if (q >= nq) continue;
+            bool up;
+            int o, ti, tj;
+            place(q, up, o, ti, tj);
+            const int ra = up ? o + 16 * ti : o + S + 16 * ti, ca = up ? o + S : o;
+            const int lo = up ? 0 : tj, hi = up ? tj : h - 1;
+            for (int kb = lo; kb <= hi; ++kb)
+#pragma unroll
+                for (int kk = 0; kk < 16; kk += 4) {
+                    const int k = kk + fk;
+                    const T a = t[ra + fr][ca + 16 * kb + k];
+                    T b = t[ca + 16 * kb + k][ca + 16 * tj + fr];
+                    if (kb == tj) b = up ? (k <= fr ? b : T(0)) : (k > fr ? b : (k == fr ? T(1) : T(0)));
+                    acc[i] = MF<T>::mfma(a, b, acc[i]);
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kMaxQ; ++i) {
+            const int q = wave + NW * i;
+            if (q >= nq) continue;
+            bool up;
+            int o, ti, tj;
+            place(q, up, o, ti, tj);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                t[(up ? o : o + S) + 16 * ti + MF<T>::rowof(lane, r)][(up ? o + S : o) + 16 * tj + fr] = acc[i][r];
+        }
+        __syncthreads();
+        // X21 = -X22 P (Y12 = -Y11 P), over P
+#pragma unroll
+        for (int i = 0; i < kMaxQ; ++i) {
+            const int q = wave + NW * i;
+            acc[i] = (acc_t){T(0), T(0), T(0), T(0)};
+            if (q >= nq) continue;
+            bool up;
+            int o, ti, tj;
+            place(q, up, o, ti, tj);
+            const int da = up ? o : o + S, cp = (up ? o + S : o) + 16 * tj;
+            const int lo = up ? ti : 0, hi = up ? h - 1 : ti;
+            for (int kb = lo; kb <= hi; ++kb)
+#pragma unroll
+                for (int kk = 0; kk < 16; kk += 4) {
+                    const int k = kk + fk;
+                    T a = t[da + 16 * ti + fr][da + 16 * kb + k];
+                    if (kb == ti) a = up ? (k >= fr ? a : T(0)) : (k < fr ? a : (k == fr ? T(1) : T(0)));
+                    acc[i] = MF<T>::mfma(a, t[da + 16 * kb + k][cp + fr], acc[i]);
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kMaxQ; ++i) {
+            const int q = wave + NW * i;
+            if (q >= nq) continue;
+            bool up;
+            int o, ti, tj;
+            place(q, up, o, ti, tj);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                t[(up ? o : o + S) + 16 * ti + MF<T>::rowof(lane, r)][(up ? o + S : o) + 16 * tj + fr] = -acc[i][r];
+        }
+        __syncthreads();
+    }
+}
+
+// L11^{-1} and U11^{-1} of a factored panel [k0, k0+nb) to the workspace, by the NT >= 128
+// threads of the element's workgroup.  Rows and columns >= nb act as identity and
+// are returned as zero.  Inlined: called, it would reach LDS by flat addresses.
+template <int NT, typename T>
+__device__ __forceinline__ void panel_inverses(const T *E, int64_t ld, int k0, int nb, int slot, T *wd, T (*t)[kNB + 1]) {
+    const int tid = threadIdx.x;
+    for (int q = tid; q < kNB * kNB; q += NT) {
+        const int r = q / kNB, c = q % kNB;
+        t[r][c] = (r < nb && c < nb) ? E[(int64_t)(k0 + r) * ld + k0 + c] : T(r == c);
+    }
+    __syncthreads();
+    invert_triangles<NT, T>(t);
+    T *li = wd + slot * kNB * kNB, *ui = wd + (2 + slot) * kNB * kNB;
+    for (int q = tid; q < kNB * kNB; q += NT) {
+        const int r = q / kNB, c = q % kNB;
+        const bool in = r < nb && c < nb;
+        const T v = t[r][c];
+        li[q] = in ? (c < r ? v : T(r == c)) : T(0);
+        ui[q] = in && c >= r ? v : T(0);
+    }
+}
+
 // Factor the panel columns [k0, k0+nb) over the pivot rows [k0, n) (the trace
 // rows n.. get their multipliers from k_crows).  Rows are distributed over the
 // threads (row cb + tid + kPT i), kW columns at a time held in registers.  The
@@ -297,7 +467,8 @@ __global__ void __launch_bounds__(kPT, sizeof(T) == 4 ? 4 : 2) k_panel(DevMesh d
     __shared__ T s_L[kW][kW];
     __shared__ T s_U[kW][kNB];
     __shared__ int s_piv2[kNBO], s_wcnt[2];
-    __shared__ T s_T[kNB][kNB + 1], s_I[kNB][kNB + 1];
+    __shared__ T s_T[kNB][kNB + 1];
+    T (*s_I)[kNB + 1] = s_T + kHalf;
     int info_k = 0;
     // part 1: the first half (ending with its U12 rows), part 2: the second
     // half and the records; a panel of at most kHalf columns is done by part 1
@@ -547,7 +718,6 @@ __global__ void __launch_bounds__(kPT, sizeof(T) == 4 ? 4 : 2) k_panel(DevMesh d
         return;
     }
     // record pivots, the panel's net permutation, L11^{-1} and U11^{-1}
-    T *wd = ws.d + (int64_t)blockIdx.x * ws.ds;
     for (int t = tid; t < nb; t += kPT) wi[kWsPiv + slot * kNB + t] = s_piv[t];
     {
         int *pm = wi + (slot == 0 ? kWsPerm0 : kWsPerm1);
@@ -562,93 +732,389 @@ __global__ void __launch_bounds__(kPT, sizeof(T) == 4 ? 4 : 2) k_panel(DevMesh d
         int *pm = wi + kWsPerm128;
         block_net_perm(kbase, nbo, s_piv2, pm + 1, pm, pm + 1 + kNBO, s_wcnt);
     }
-    for (int t = tid; t < kNB * kNB; t += kPT) {
-        const int r = t / kNB, c = t % kNB;
-        s_T[r][c] = (r < nb && c < nb) ? E[(int64_t)(k0 + r) * ld + k0 + c] : T(0);
-        s_I[r][c] = T(0);
-    }
-    __syncthreads();
-    // Both inverses by 8 x 8 block substitution over the whole block: first the
-    // diagonal blocks (one thread per column), then one block row at a time,
-    // P = (off-diagonal part of the row) x (finished rows of the inverse) and
-    // X_row = -X_diag P.  Rows and columns >= nb act as identity and are
-    // returned as zero.
-    T (*s_P)[kNB] = s_U;  // [8][64] partial products
-    if (tid < kNB) {
-        // diagonal block of L11^{-1}: forward substitution, unit diagonal
-        const int j = tid, bi = j & ~7, jl = j & 7;
-        T x[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            T v = (r == jl) ? T(1) : T(0);
-#pragma unroll
-            for (int c = 0; c < r; ++c) v -= s_T[bi + r][bi + c] * x[c];
-            x[r] = (r >= jl) ? v : T(0);
-            s_I[bi + r][j] = x[r];
+    panel_inverses<kPT, T>(E, ld, k0, nb, slot, ws.d + (int64_t)blockIdx.x * ws.ds, s_T);
+    if (tid == 0 && info_k && info[e] == 0) info[e] = info_k;
+}
+
+// A recorded permutation of W swaps (see kPerm64) for rows base .. base + rows - 1 as a
+// map: map[x - base] is the row whose content ends in row x.  For all threads.
+template <int NT>
+__device__ __forceinline__ void map_identity(int *map, int base, int rows) {
+    for (int t = threadIdx.x; t < rows; t += NT) map[t] = base + t;
+}
+// The permutation of wa swaps from row `base` (map ma, displaced rows da[2 t], t < na)
+// followed by that of wb swaps from row base + wa (mb, db, nb) as one of wa + wb swaps:
+// its top rows' sources, displaced (dst, src) pairs and their count.  na, nb <= 64;
+// for all threads of the workgroup, NT >= 128, the maps complete.
+template <int NT>
+__device__ __forceinline__ void join_perms(int base, int wa, int wb, const int *ma, const int *mb, const int *da, int na,
+                                           const int *db, int nb, int *top_src, int *disp, int *ndisp, int *s_wcnt) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, w = wa + wb;
+    auto source = [&](int x) { return ma[mb[x - base] - base]; };
+    if (tid < w) top_src[tid] = source(base + tid);
+    // wave 0: rows the second permutation displaced; wave 1: rows only the first one did
+    int y = 0, src = 0;
+    bool keep = false;
+    if (wave < 2 && lane < (wave == 0 ? nb : na)) {
+        y = wave == 0 ? db[2 * lane] : da[2 * lane];
+        if (y >= base + w) {
+            src = source(y);
+            keep = src != y && (wave == 0 || mb[y - base] == y);
         }
     }
+    const unsigned long long bal = __ballot(keep);
+    if (lane == 0 && wave < 2) s_wcnt[wave] = __popcll(bal);
     __syncthreads();
-    for (int bI = 8; bI < kNB; bI += 8) {
-        const int i = tid & 7, j = tid >> 3;  // j < bI: columns left of the block row
-        if (j < bI) {
-            T v = T(0);
-            for (int k = j & ~7; k < bI; ++k) v += s_T[bI + i][k] * s_I[k][j];
-            s_P[i][j] = v;
+    if (keep) {
+        const int pos = (wave == 1 ? s_wcnt[0] : 0) + __popcll(bal & ((1ull << lane) - 1));
+        disp[2 * pos] = y;
+        disp[2 * pos + 1] = src;
+    }
+    if (tid == 0) *ndisp = s_wcnt[0] + s_wcnt[1];
+}
+
+// The same panel for at most R NT rows below k0: each thread holds the 32 columns of
+// its R rows in registers for the whole half, so a half reads and writes the panel
+// once.  What bounds it is the chain of 32 pivot steps, with one or two waves on a
+// SIMD and nothing to overlap but the step itself.  Hence
+//  - one barrier a step: each wave finds its own best row and puts that row and the
+//    reciprocal of its pivot in LDS, and all threads pick the best wave's after the barrier;
+//  - both searches compare the upper words of the values, which take one instruction a
+//    step, and go over the whole values only where two of those agree;
+//  - rows are not exchanged: pos is the place a row has come to, and is where it is
+//    written at the end.  The permutations follow from it and are joined by maps;
+//  - a loop over kU columns at a time, after which the registers move round by kU, so
+//    that every register index is fixed in a body of a few KB.  Unrolled over all 32
+//    columns, rows exchanged in two barriers, it was 50 KB and 2 800 cycles a step.  Finished columns take part with a pivot row of zeros.
+// A step takes about 2 000 cycles (n = 136, 128 threads) to 3 900 (n = 628, 512
+// threads).  A half with its records, before (k_panel) and now: n = 136 elements of a
+// step at p = 2, 63 -> 44 us; 480-row Schwarz blocks at p = 3, 159 -> 79; 256 systems of
+// 628, 90 -> 74; 4096 systems of 40, 89 -> 35 (LDS 73 -> 36 KB, four workgroups a CU).
+// k_panel, whose 8-column sub-panels go through memory between updates, remains for
+// systems with more than 1024 rows left, whose rows do not fit the registers in FP64.
+template <int R, int NT, int TAG, typename T>
+__global__ void __launch_bounds__(NT) k_panel_reg(DevMesh dm, SysDesc sd, int e0, int k0, int slot, int kbase, int part,
+                                                  T *__restrict__ Ebase, WS<T> ws, int *__restrict__ info) {
+    constexpr int kVN = 16 / sizeof(T);  // values per 16-byte access
+    typedef T vq __attribute__((ext_vector_type(kVN)));
+    constexpr int NW = NT / 64, H = kHalf, kU = 4, NQ = H / kU;
+    static_assert(kU % 2 == 0 && kU % kVN == 0, "step parity and 16-byte groups are fixed per column group");
+    const int e = e0 + blockIdx.x;
+    const ElemDims dd = elem_dims(dm, sd, e);
+    if (k0 >= dd.n) return;
+    const int n = dd.n, nb = min(kNB, n - k0);
+    const bool split = nb > H;  // a panel of at most 32 columns is done by part 1
+    if (part == 2 && !split) return;
+    T *E = Ebase + (sd.off[e] - sd.off[e0]);
+    const int64_t ld = dd.ld;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // two steps' candidates; row NW is zero, taken where no pivot can be; row NW + 1
+    // takes the columns that nobody reads
+    constexpr int BUF = (NW + 2) * H;
+    __shared__ __attribute__((aligned(16))) T rows[2 * BUF];
+    __shared__ __attribute__((aligned(8))) int s_key[2][NW][2];  // upper word, position
+    __shared__ T s_val[2][NW], s_inv[2][NW + 1];
+    __shared__ int s_top[kNB], s_disp[2 * kNB], s_nd, s_wcnt[2];
+    __shared__ T s_t[kNB][kNB + 1];
+    int *wi = ws.i + (int64_t)blockIdx.x * ws.is;
+    const int j0 = (part == 2) ? H : 0, cb = k0 + j0, w = min(H, nb - j0);
+    int info_k = 0;
+    if (tid < 2 * H) rows[(tid / H) * BUF + NW * H + tid % H] = T(0);
+    if (tid < 2) s_inv[tid][NW] = T(0);
+    T a[R][H];
+    int pos[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int r = cb + tid + NT * i;
+        const T *src = E + (int64_t)min(r, n - 1) * ld + cb;
+        pos[i] = r < n ? r : -1;
+#pragma unroll
+        for (int c = 0; c < H; c += kVN) {
+            // 16-byte loads: cb is a multiple of 32, ld of 8, so a group is inside the row
+            // or beyond ld
+            vq v = (vq)T(0);
+            if (cb + c < ld) v = *(const vq *)(src + c);
+#pragma unroll
+            for (int u = 0; u < kVN; ++u) a[i][c + u] = (r < n && c + u < w) ? v[u] : T(0);
+        }
+    }
+    // The wave's pivot candidate for position k from the values in column C: largest
+    // |a| over the rows at positions >= k (smallest position on ties); NaN wins.  Its row
+    // goes to LDS with column SH first, group b of its columns to put[b] (finished groups
+    // to the unread row) and zeros to the group that was finished last.
+    int put[NQ], zero = (NW + 1) * H;
+#pragma unroll
+    for (int b = 0; b < NQ; ++b) put[b] = wave * H;
+    auto candidate = [&](auto column, auto shift, int buf, int k) {
+        constexpr int C = decltype(column)::value, SH = decltype(shift)::value;
+        T best = T(0), val = T(0);
+        int bpos = INT_MAX;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            T v = fabs(a[i][C]);
+            v = v == v ? v : T(INFINITY);
+            const bool take = (pos[i] >= k) & ((bpos == INT_MAX) | (v > best) | ((v == best) & (pos[i] < bpos)));
+            best = take ? v : best;
+            val = take ? a[i][C] : val;
+            bpos = take ? pos[i] : bpos;
+        }
+        T inv = T(1) / val;  // before the search, whose latency it fills
+        asm volatile("" : "+v"(inv));
+        const unsigned key = upper_word(best), top = lanes_max<64>(key);
+        bool mine = key == top && bpos != INT_MAX;
+        const unsigned long long tie = __ballot(mine);
+        if ((tie & (tie - 1)) != 0) {  // by the whole values, then by position
+            T v = mine ? best : T(-1);
+            int one = mine ? bpos : INT_MAX;
+            wave_argmax(v, one);
+            mine = bpos == one;
+        }
+        if (tie == 0) {  // no row of this wave is left
+            if (lane == 0) {
+                s_key[buf][wave][0] = 0;
+                s_key[buf][wave][1] = INT_MAX;
+            }
+            return;
+        }
+        if (mine) {
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                if (R == 1 || pos[i] == bpos)
+#pragma unroll
+                    for (int c = 0; c < H; c += kVN) {
+                        vq v;
+#pragma unroll
+                        for (int u = 0; u < kVN; ++u) v[u] = a[i][(c + u + SH) % H];
+                        *(vq *)(rows + buf * BUF + put[c / kU] + c) = v;
+                    }
+            if constexpr (C <= 1 || SH > 0)  // the first candidate of its parity in the group
+#pragma unroll
+                for (int c = 0; c < kU; c += kVN) *(vq *)(rows + buf * BUF + zero + c) = (vq)T(0);
+            s_key[buf][wave][0] = (int)key;
+            s_key[buf][wave][1] = bpos;
+            s_val[buf][wave] = best;
+            s_inv[buf][wave] = inv;
+        }
+    };
+    using std::integral_constant;
+    candidate(integral_constant<int, 0>{}, integral_constant<int, 0>{}, 0, cb);
+    int piv = 0;  // lane t of each wave: the half's pivot t
+    // the step of the column in register S, k = cb + q kU + S
+    auto step = [&](auto column, int q) {
+        constexpr int S = decltype(column)::value, buf = S & 1;
+        const int jj = q * kU + S, k = cb + jj;
+        if (jj >= w) return;  // uniform
+        __syncthreads();
+        // the best wave: lane l looks at wave l % NW
+        const unsigned key = (unsigned)s_key[buf][lane % NW][0];
+        const int wpos = s_key[buf][lane % NW][1];
+        const unsigned top = lanes_max<NW>(key);
+        const unsigned tie = (unsigned)__ballot(key == top) & ((1u << NW) - 1);
+        const unsigned utop = (unsigned)__builtin_amdgcn_readfirstlane((int)top);
+        int from = __ffs((int)tie) - 1, pr = __builtin_amdgcn_readlane(wpos, from);
+        if ((tie & (tie - 1)) != 0 || utop == 0 || utop >= kInfWord<T>) {
+            T bv = T(-1);
+            pr = INT_MAX;
+            for (int t = 0; t < NW; ++t) {
+                const T v = s_val[buf][t];
+                const int p = s_key[buf][t][1];
+                if (p != INT_MAX && (v > bv || (v == bv && p < pr))) {
+                    bv = v;
+                    pr = p;
+                    from = t;
+                }
+            }
+            if (!(bv > T(0)) || !(bv < T(INFINITY))) {
+                pr = k;
+                from = NW;
+                if (info_k == 0) info_k = k + 1 + red_before(dm, sd, e);
+            }
+            pr = __builtin_amdgcn_readfirstlane(pr);
+            from = __builtin_amdgcn_readfirstlane(from);
+        }
+        piv = lane == jj ? pr : piv;
+        T pinv = s_inv[buf][from];
+        asm volatile("" : "+v"(pinv));  // read by all, not under the rows' mask
+        const T *prow = rows + buf * BUF + from * H;
+        T l[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            pos[i] = pos[i] == pr ? k : (pos[i] == k ? pr : pos[i]);
+            const bool below = pos[i] > k;
+            const T m = a[i][S] * pinv;
+            l[i] = below ? m : T(0);
+            a[i][S] = below ? m : a[i][S];
+        }
+#pragma unroll
+        for (int c = S + 1; c < H; ++c) {
+            const T p = prow[c];
+#pragma unroll
+            for (int i = 0; i < R; ++i) a[i][c] -= l[i] * p;
+        }
+        if constexpr (S + 1 == kU) {
+            zero = wave * H + H - (q + 1) * kU;
+#pragma unroll
+            for (int b = 0; b < NQ; ++b) put[b] = (b < NQ - 1 - q ? wave : NW + 1) * H;
+        }
+        if (jj + 1 < w) {
+            if constexpr (S + 1 < kU)
+                candidate(integral_constant<int, S + 1>{}, integral_constant<int, 0>{}, buf ^ 1, k + 1);
+            else
+                candidate(integral_constant<int, kU>{}, integral_constant<int, kU>{}, buf ^ 1, k + 1);
+        }
+    };
+#pragma unroll 1
+    for (int q = 0; q < NQ; ++q) {
+        step(integral_constant<int, 0>{}, q);
+        step(integral_constant<int, 1>{}, q);
+        step(integral_constant<int, 2>{}, q);
+        step(integral_constant<int, 3>{}, q);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            T f[kU];
+#pragma unroll
+            for (int c = 0; c < kU; ++c) f[c] = a[i][c];
+#pragma unroll
+            for (int c = 0; c < H - kU; ++c) a[i][c] = a[i][c + kU];
+#pragma unroll
+            for (int c = 0; c < kU; ++c) a[i][H - kU + c] = f[c];
+        }
+    }
+    const bool first = part == 1 && split;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        if (pos[i] < 0) continue;
+        T *dst = E + (int64_t)pos[i] * ld + cb;
+        // 16 bytes at a time while inside the half: w < 32 only where the panel ends
+#pragma unroll
+        for (int c = 0; c < H; c += kVN) {
+            vq v;
+#pragma unroll
+            for (int u = 0; u < kVN; ++u) v[u] = a[i][c + u];
+            if (c + kVN <= w) {
+                *(vq *)(dst + c) = v;
+            } else {
+#pragma unroll
+                for (int u = 0; u < kVN - 1; ++u)
+                    if (c + u < w) dst[c + u] = v[u];
+            }
+        }
+        // The half's net permutation, from the rows' places: the sources of the top rows
+        // here, and below the rows that a top row's content went to (no other content
+        // can leave its row but for the top).
+        if (pos[i] < cb + w) {
+            s_top[pos[i] - cb] = cb + tid + NT * i;
+            if (first)  // L11 by columns, for the U12 rows
+#pragma unroll
+                for (int c = 0; c < H; ++c) s_t[c][pos[i] - cb] = a[i][c];
+        }
+    }
+    if (wave == 0) {
+        const bool moved = tid < w && pos[0] >= cb + w;
+        const unsigned long long bal = __ballot(moved);
+        if (moved) {
+            const int d = __popcll(bal & ((1ull << lane) - 1));
+            s_disp[2 * d] = pos[0];
+            s_disp[2 * d + 1] = cb + tid;
+        }
+        if (lane == 0) s_nd = __popcll(bal);
+        if (tid < w) wi[kWsPiv + slot * kNB + j0 + tid] = piv;
+    }
+    __syncthreads();
+    // on the panel's other half: its right columns (part 1, not yet factored, the top rows
+    // to LDS for the solve below) or its left ones (part 2, the first half's L)
+    const int ocol = (part == 2) ? k0 : k0 + H, nother = (part == 2) ? H : max(0, nb - H);
+    const int nd = s_nd;
+    {
+        constexpr int Q = 2 * H * H / NT;
+        const int items = w + nd, c = tid % H;  // <= 2 H rows of H columns
+        T vals[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int ridx = tid / H + q * (NT / H);
+            vals[q] = T(0);
+            if (ridx < items && c < nother) {
+                const int src = (ridx < w) ? s_top[ridx] : s_disp[2 * (ridx - w) + 1];
+                vals[q] = E[(int64_t)src * ld + ocol + c];
+            }
         }
         __syncthreads();
-        if (j < bI) {
-            T v = T(0);
 #pragma unroll
-            for (int c = 0; c < 8; ++c) v -= s_I[bI + i][bI + c] * s_P[c][j];
-            s_I[bI + i][j] = v;
+        for (int q = 0; q < Q; ++q) {
+            const int ridx = tid / H + q * (NT / H);
+            if (ridx < items && c < nother) {
+                if (first && ridx < w) {
+                    s_t[H + ridx][c] = vals[q];
+                } else {
+                    const int dst = (ridx < w) ? cb + ridx : s_disp[2 * (ridx - w)];
+                    E[(int64_t)dst * ld + ocol + c] = vals[q];
+                }
+            }
         }
-        __syncthreads();
-    }
-    T *li = wd + slot * kNB * kNB;
-    for (int t = tid; t < kNB * kNB; t += kPT) {
-        const int r = t / kNB, c = t % kNB;
-        li[t] = (r < nb && c < nb) ? s_I[r][c] : T(0);
-    }
-    __syncthreads();
-    for (int t = tid; t < kNB * kNB; t += kPT) s_I[t / kNB][t % kNB] = T(0);
-    __syncthreads();
-    if (tid < kNB) {
-        // diagonal block of U11^{-1}: back substitution
-        const int j = tid, bi = j & ~7, jl = j & 7;
-        T x[8];
-#pragma unroll
-        for (int r = 7; r >= 0; --r) {
-            T v = (r == jl) ? T(1) : T(0);
-#pragma unroll
-            for (int c = r + 1; c < 8; ++c) v -= s_T[bi + r][bi + c] * x[c];
-            const T d = (bi + r < nb) ? s_T[bi + r][bi + r] : T(1);
-            x[r] = (r <= jl) ? v / d : T(0);
-            s_I[bi + r][j] = x[r];
-        }
-    }
-    __syncthreads();
-    for (int bI = kNB - 16; bI >= 0; bI -= 8) {
-        const int i = tid & 7, j = bI + 8 + (tid >> 3);  // columns right of the block row
-        if (j < kNB) {
-            T v = T(0);
-            for (int k = bI + 8; k <= (j | 7); ++k) v += s_T[bI + i][k] * s_I[k][j];
-            s_P[i][j] = v;
-        }
-        __syncthreads();
-        if (j < kNB) {
-            T v = T(0);
-#pragma unroll
-            for (int c = 0; c < 8; ++c) v -= s_I[bI + i][bI + c] * s_P[c][j];
-            s_I[bI + i][j] = v;
-        }
-        __syncthreads();
-    }
-    T *ui = wd + (2 + slot) * kNB * kNB;
-    for (int t = tid; t < kNB * kNB; t += kPT) {
-        const int r = t / kNB, c = t % kNB;
-        ui[t] = (r < nb && c < nb) ? s_I[r][c] : T(0);
     }
     if (tid == 0 && info_k && info[e] == 0) info[e] = info_k;
+    int *pm = wi + (slot == 0 ? kWsPerm0 : kWsPerm1);
+    if (part == 1) {
+        // the half's permutation: the panel's record, or for the second launch to join
+        for (int t = tid; t < w; t += NT) pm[1 + t] = s_top[t];
+        for (int t = tid; t < 2 * nd; t += NT) pm[1 + kNB + t] = s_disp[t];
+        if (tid == 0) pm[0] = nd;
+    }
+    __syncthreads();
+    if (first) {
+        // U12 = L11^{-1} A12 on the top 32 rows, one thread per column with its column in
+        // registers; A22 -= L21 U12 below is k_half's
+        if (tid < nother) {
+            T x[H];
+#pragma unroll
+            for (int r = 0; r < H; ++r) x[r] = s_t[H + r][tid];
+#pragma unroll
+            for (int q = 0; q < H; ++q)
+#pragma unroll
+                for (int r = q + 1; r < H; ++r) x[r] -= s_t[q][r] * x[q];
+#pragma unroll
+            for (int r = 0; r < H; ++r) E[(int64_t)(k0 + r) * ld + ocol + tid] = x[r];
+        }
+        return;
+    }
+    // The net permutations of the panel and, with its second panel, of the 128-column block,
+    // by maps over the rows from kbase in s_t: at most 1024 + 96 rows.
+    static_assert(2 * (R * NT + 3 * H) * sizeof(int) <= sizeof(s_t), "maps");
+    int *ma = (int *)s_t, *mb = ma + R * NT + 3 * H;
+    const int nrow = n - kbase;
+    if (part == 2) {
+        const int na = pm[0];
+        map_identity<NT>(ma, kbase, nrow);
+        map_identity<NT>(mb, kbase, nrow);
+        __syncthreads();
+        for (int t = tid; t < H; t += NT) ma[k0 - kbase + t] = pm[1 + t];
+        for (int t = tid; t < na; t += NT) ma[pm[1 + kNB + 2 * t] - kbase] = pm[1 + kNB + 2 * t + 1];
+        for (int t = tid; t < w; t += NT) mb[cb - kbase + t] = s_top[t];
+        for (int t = tid; t < nd; t += NT) mb[s_disp[2 * t] - kbase] = s_disp[2 * t + 1];
+        __syncthreads();
+        join_perms<NT>(k0, H, w, ma + (k0 - kbase), mb + (k0 - kbase), pm + 1 + kNB, na, s_disp, nd, s_top, s_disp, &s_nd, s_wcnt);
+        __syncthreads();
+        for (int t = tid; t < nb; t += NT) pm[1 + t] = s_top[t];
+        for (int t = tid; t < 2 * s_nd; t += NT) pm[1 + kNB + t] = s_disp[t];
+        if (tid == 0) pm[0] = s_nd;
+        __syncthreads();
+    }
+    if (slot == 1) {  // the first panel's record comes from the launches before
+        const int *p0 = wi + kWsPerm0;
+        int *pb = wi + kWsPerm128;
+        const int na = p0[0], nd1 = s_nd;
+        map_identity<NT>(ma, kbase, nrow);
+        map_identity<NT>(mb, kbase, nrow);
+        __syncthreads();
+        for (int t = tid; t < kNB; t += NT) ma[t] = p0[1 + t];
+        for (int t = tid; t < na; t += NT) ma[p0[1 + kNB + 2 * t] - kbase] = p0[1 + kNB + 2 * t + 1];
+        for (int t = tid; t < nb; t += NT) mb[kNB + t] = s_top[t];
+        for (int t = tid; t < nd1; t += NT) mb[s_disp[2 * t] - kbase] = s_disp[2 * t + 1];
+        __syncthreads();
+        join_perms<NT>(kbase, kNB, nb, ma, mb, p0 + 1 + kNB, na, s_disp, nd1, pb + 1, pb + 1 + kNBO, pb, s_wcnt);
+        __syncthreads();
+    }
+    panel_inverses<NT, T>(E, ld, k0, nb, slot, ws.d + (int64_t)blockIdx.x * ws.ds, s_t);
 }
 
 // acc (rows 16 wave .. +15, C columns) = Ls (64x64) * X (64 x C), both in LDS.
@@ -1834,10 +2300,22 @@ static int run_lu(const hdg_ctx *ctx, const SysDesc &sd, int e0, int ne, T *E, i
     auto factor_block = [&](int k0, const WS<T> &wb) {
         auto panel = [&](int kp, int slot) {
             auto half = [&](int part) {
-                if (R <= 1) hipLaunchKernelGGL((k_panel<1, TAG, T>), dim3(ne), dim3(kPT), 0, s, dm, sd, e0, kp, slot, k0, part, E, wb, info);
-                else if (R <= 2) hipLaunchKernelGGL((k_panel<2, TAG, T>), dim3(ne), dim3(kPT), 0, s, dm, sd, e0, kp, slot, k0, part, E, wb, info);
-                else if (R <= 3) hipLaunchKernelGGL((k_panel<3, TAG, T>), dim3(ne), dim3(kPT), 0, s, dm, sd, e0, kp, slot, k0, part, E, wb, info);
-                else hipLaunchKernelGGL((k_panel<5, TAG, T>), dim3(ne), dim3(kPT), 0, s, dm, sd, e0, kp, slot, k0, part, E, wb, info);
+                const int rows = maxn - kp - (part == 2 ? kHalf : 0);
+                if (rows <= 0) return;
+                auto reg = [&](auto kernel, int threads) {
+                    hipLaunchKernelGGL(kernel, dim3(ne), dim3(threads), 0, s, dm, sd, e0, kp, slot, k0, part, E, wb, info);
+                };
+                // The rows of a half in registers up to 1024, the most that 512 threads hold in
+                // FP64; both parts by one kernel, for the first leaves its permutation.  The
+                // smallest workgroup with one row a thread up to 256 rows, with two beyond:
+                // 256 to 512 rows by <2, 256> 67 us against <1, 512> 79 (628-column systems).
+                const bool held = maxn - kp <= 1024;
+                if (held && rows <= 128) reg(k_panel_reg<1, 128, TAG, T>, 128);
+                else if (held && rows <= 256) reg(k_panel_reg<1, 256, TAG, T>, 256);
+                else if (held && rows <= 512) reg(k_panel_reg<2, 256, TAG, T>, 256);
+                else if (held) reg(k_panel_reg<2, 512, TAG, T>, 512);
+                else if (R <= 3) reg(k_panel<3, TAG, T>, kPT);
+                else reg(k_panel<5, TAG, T>, kPT);
             };
             half(1);
             if (maxn - kp > kHalf)

@@ -177,3 +177,35 @@ def test_mixed_routes_agree(p, walls, chunk):
         print(f"  element {e}: X {err[0]:.2e} (all columns: {err[1]:.2e})")
         assert err[0] <= max(err[1], 1e-11)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("p", [1, 2, 3])
+def test_pivot_search_with_ties(p, precision):
+    """Systems of whole numbers in [-2, 2]: in the first pivot columns nearly every largest
+    value is tied, also between the rows that different waves hold.  n = 160, 540 and
+    1280 pivot columns pass every size at which the panels change their split.  S = D - B
+    A^{-1} C against the same in 64 bits.  Tolerance: a backward-stable solve is within
+    4 cond(A) u of |B| |A^{-1} C|, here two of them (u of the factorisation's type)."""
+    import torch
+    from paper_2608_27863_amd import hdg, pipeline
+    wl = _workload(p, False)
+    print(f"[reduce] ties, p={p} {precision}", flush=True)
+    st = pipeline.NewtonStep(wl, prec=hdg.HDG_FP64 if precision == "fp64" else hdg.HDG_MIXED_FAST)
+    ctx = st.ctx
+    rng = np.random.default_rng(11)
+    host = rng.integers(-2, 3, size=st.E.numel()).astype(np.float64)
+    st.E.copy_(torch.as_tensor(host))
+    st.condense()
+    torch.cuda.synchronize()
+    assert not st.info.any().item()
+    SK = st.SK.cpu().numpy()
+    for e in (0, ctx.n_elem - 1):
+        Ev, _ = e_view(ctx, host, e)
+        n = int(ctx.layout["elem_n"][e])
+        X = np.linalg.solve(Ev[:n, :n], Ev[:n, n:])
+        R = Ev[n:, n:] - Ev[n:, :n] @ X
+        S, g = sk_view(ctx, SK, e)
+        size = np.linalg.norm(np.abs(Ev[n:, :n]) @ np.abs(X))
+        tol = 8 * np.linalg.cond(Ev[:n, :n], 1) * (U64 if precision == "fp64" else 2.0 ** -24) * size
+        assert np.linalg.norm(S - R[:, :-1]) <= tol and np.linalg.norm(g + R[:, -1]) <= tol, e
