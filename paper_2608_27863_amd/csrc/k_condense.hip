@@ -789,7 +789,7 @@ __device__ __forceinline__ void join_perms(int base, int wa, int wb, const int *
 // A step takes about 2 000 cycles (n = 136, 128 threads) to 3 900 (n = 628, 512
 // threads).  A half with its records, before (k_panel) and now: n = 136 elements of a
 // step at p = 2, 63 -> 44 us; 480-row Schwarz blocks at p = 3, 159 -> 79; 256 systems of
-// 628, 90 -> 74; 4096 systems of 40, 89 -> 35 (LDS 73 -> 36 KB, four workgroups a CU).
+// 628, 90 -> 74; 1728 systems of 40, 89 -> 35 (LDS 73 -> 36 KB, four workgroups a CU).
 // k_panel, whose 8-column sub-panels go through memory between updates, remains for
 // systems with more than 1024 rows left, whose rows do not fit the registers in FP64.
 template <int R, int NT, int TAG, typename T>

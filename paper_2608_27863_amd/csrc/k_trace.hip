@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <mutex>
 
 #include "hdg_internal.h"
@@ -324,12 +325,16 @@ __global__ void __launch_bounds__(256) k_asm_local(DevMesh dm, const T *__restri
     zloc[dm.tloc_off[e] + i] = acc;
 }
 
-// The same product with one workgroup per element, for inverses whose columns
-// do not start on 128-byte lines (f <= 768).  The element's block (starting on a
+// The same product with one workgroup per element (f <= 768), also where the inverse's
+// columns do not start on 128-byte lines.  The element's block (starting on a
 // line, zero padding after it) streams through LDS in 32 KB pieces with
 // nontemporal 16-byte loads, eight in flight per thread, so every line is read
 // once and whole; each thread owns rows i, i + 256, i + 512 and sums over j in
-// the same order as k_asm_local, so the two give identical results.
+// the same order as k_asm_local, so the two give identical results.  The next
+// piece's loads are in flight under a piece's products, and a row's place in the
+// next piece follows from the last one's by subtraction (with divisions, and loads only
+// between the products, 512 blocks at p = 4 took 415 us in FP64 and 262 in FP32, now 340 and
+// 171, where the read rate allows 324 and 162; not unrolled, 384 in FP32).
 constexpr int kAsmRowsPerThread = 3;
 constexpr int kAsmPieceBytes = 32768;
 
@@ -351,17 +356,23 @@ __global__ void __launch_bounds__(256) k_asm_local_elem(DevMesh dm, const T *__r
         for (int t = tid; t < len; t += blockDim.x) sy[to[lf] + t] = r[dm.face_off[F] + t];
     }
     const T *M = Sinv + dm.asm_off[e];
-    const int64_t n = (int64_t)f * f;
+    const int n = f * f;
     double acc[kAsmRowsPerThread] = {};
-    for (int64_t p0 = 0; p0 < n; p0 += kPiece) {
-        const int len = (int)min((int64_t)kPiece, n - p0);
-        const int units = (len + kVN - 1) / kVN;  // the last unit may take zeros of the padding
-        vq v[kLoads];
+    int j[kAsmRowsPerThread] = {}, at[kAsmRowsPerThread];  // row q's next column, its place in the piece
+#pragma unroll
+    for (int q = 0; q < kAsmRowsPerThread; ++q) at[q] = tid + 256 * q < f ? tid + 256 * q : INT_MAX;
+    vq v[kLoads];
+    auto load = [&](int p0) {
+        const int units = (min(kPiece, n - p0) + kVN - 1) / kVN;  // the last unit may take zeros of the padding
 #pragma unroll
         for (int q = 0; q < kLoads; ++q) {
             const int u = tid + 256 * q;
             if (u < units) v[q] = __builtin_nontemporal_load((const vq *)(M + p0) + u);
         }
+    };
+    load(0);
+    for (int p0 = 0; p0 < n; p0 += kPiece) {
+        const int len = min(kPiece, n - p0), units = (len + kVN - 1) / kVN;
         __syncthreads();  // the previous piece has been read (and, first, sy is complete)
 #pragma unroll
         for (int q = 0; q < kLoads; ++q) {
@@ -369,16 +380,13 @@ __global__ void __launch_bounds__(256) k_asm_local_elem(DevMesh dm, const T *__r
             if (u < units) *(vq *)(sp + kVN * u) = v[q];
         }
         __syncthreads();
+        if (p0 + kPiece < n) load(p0 + kPiece);  // under this piece's products
 #pragma unroll
         for (int q = 0; q < kAsmRowsPerThread; ++q) {
-            const int i = tid + 256 * q;
-            if (i >= f) continue;
-            // columns j with j f + i in [p0, p0 + len)
-            const int jlo = p0 > i ? (int)((p0 - i + f - 1) / f) : 0;
-            const int64_t last = p0 + len - 1 - i;
-            const int jhi = last >= 0 ? (int)(last / f) : -1;
-            const T *col = sp + ((int64_t)jlo * f + i - p0);
-            for (int j = jlo; j <= jhi; ++j, col += f) acc[q] += (double)*col * sy[j];
+            if (at[q] == INT_MAX) continue;
+#pragma unroll 4
+            for (; at[q] < len; at[q] += f, ++j[q]) acc[q] += (double)sp[at[q]] * sy[j[q]];
+            at[q] -= kPiece;
         }
     }
     double *z = zloc + dm.tloc_off[e];
@@ -1174,11 +1182,16 @@ size_t asm_apply_work_bytes(const hdg_ctx *ctx) {
 static void launch_asm_local(const hdg_ctx *ctx, int prec, const void *Sinv, const double *r, double *zloc,
                              hipStream_t s) {
     const DevMesh &dm = ctx->dm;
+    // One workgroup per element, unless the columns are whole lines and the elements too few
+    // to keep the chip reading with a workgroup each: at p = 3, 252 elements 86 us by rows
+    // against 92 (FP64) and 392 66 against 68 (FP32); 294 elements 114 against 102 and
+    // 448 79 against 71; 512 elements 172 against 147 and 87 against 80.
     const bool aligned = prec == HDG_FP64 ? ctx->asm_cols_aligned64 : ctx->asm_cols_aligned32;
-    const bool per_elem = !aligned && ctx->max_f <= kAsmRowsPerThread * 256;
+    const bool per_elem = ctx->max_f <= kAsmRowsPerThread * 256 &&
+                          (!aligned || ctx->n_elem >= (prec == HDG_FP64 ? 288 : 400));
     // fewer workgroups than CUs in the kernels below: 27 elements at p = 2 (FP64) 48 -> 14 us,
-    // 216 at p = 4 368 -> 189 us; from there on they read the inverses better (512 elements
-    // at p = 4 415 against 439 us)
+    // 216 at p = 4 368 -> 189 us; from there on they read the inverses better (252 elements
+    // at p = 4 212 against 215 us, 512 340 against 439)
     if (ctx->n_elem * (per_elem ? 1 : (ctx->max_f + 255) / 256) < kCUs) {
         const dim3 fgrid(ctx->n_elem, (ctx->max_f + kFewRows - 1) / kFewRows);
         if (prec == HDG_FP64)

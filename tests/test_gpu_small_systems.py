@@ -61,7 +61,7 @@ def test_matvec_on_both_sides_of_the_switch(n, p, walls):
 
 @pytest.mark.parametrize("prec", ["FP64", "MIXED"])
 @pytest.mark.parametrize("n,p", [((2, 2, 2), 1), ((6, 6, 7), 2), ((6, 6, 8), 2), ((5, 5, 5), 3), ((8, 4, 4), 3),
-                                 ((3, 3, 3), 4), ((6, 7, 6), (1, 3))])
+                                 ((8, 6, 6), 3), ((8, 10, 5), 3), ((3, 3, 3), 4), ((6, 7, 6), (1, 3))])
 def test_schwarz_apply_on_both_sides_of_the_switch(n, p, prec):
     import torch
     from paper_2608_27863_amd import hdg
@@ -127,3 +127,23 @@ def test_gmres_vector_kernels(n, p, m):
     assert abs(true - h[-1]) <= 1e-10 * true + 1e-13 * h[0]
     if m >= 25:
         assert np.linalg.norm(b - mul(got)) <= 1e-12 * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("n,p", [((11, 10, 10), 1), ((8, 8, 5), 2)])
+def test_gradient_rows_by_several_nodes(n, p):
+    """A call over many small elements gives a workgroup 8 (p = 1) or 3 nodes (p = 2): the
+    same bits as calls over few elements, one node a workgroup."""
+    import torch
+    from paper_2608_27863_amd import pipeline, synth
+    mesh = synth.box_mesh(n, periodic=(True, True, True), p=p, perturb=0.1, seed=3)
+    wl = synth.make_state(mesh, lambda x: synth.tgv_state(x, 1.25), mach=1.25, noise=1e-3, nu_amp=5e-4, seed=5)
+    print(f"[small] gradient rows, {mesh.n_elem} elements at p={p}", flush=True)
+    got = []
+    for chunk in (mesh.n_elem, 100):
+        st = pipeline.NewtonStep(wl, chunk=chunk)
+        st.E.fill_(float("nan"))
+        st.residual_jacobian()
+        torch.cuda.synchronize()
+        got.append(st.E.clone())
+        del st
+    assert torch.equal(got[0], got[1])
