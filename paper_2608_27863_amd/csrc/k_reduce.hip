@@ -585,7 +585,10 @@ __global__ void __launch_bounds__(256) k_rescol(DevMesh dm, RedBuf rb, int e0, c
 }
 
 // -------------------------------------------------------------- write back
-// The factored rows of the conserved fields return to E (U and L^{-1} P [B | R]).
+// The factored rows of the conserved fields return to E (U, from the row's 64-column
+// block on, and L^{-1} P [B | R]; the recovery reads nothing to the left).  256
+// elements at p = 4: 0.59 ms (all columns 0.95; nontemporal stores, whose rows share
+// lines, 0.76).
 __global__ void __launch_bounds__(256) k_wb_rows(DevMesh dm, RedBuf rb, int e0, double *__restrict__ Ebase) {
     const int el = blockIdx.y, e = e0 + el;
     if (!rb.sel[el]) return;
@@ -595,38 +598,43 @@ __global__ void __launch_bounds__(256) k_wb_rows(DevMesh dm, RedBuf rb, int e0, 
     const int64_t ld = e_ld(20 * Np, f), ldk = e_ld(nu, f);
     const double *src = rb.K + (rb.k_off[e] - rb.k_off[e0]) + (int64_t)r * ldk;
     double *dst = Ebase + (dm.E_off[e] - dm.E_off[e0]) + (int64_t)(15 * Np + r) * ld + 15 * Np;
-    for (int c = lane; c < 5 * Np; c += 64) __builtin_nontemporal_store(src[c], dst + c);
-    for (int c = lane; c <= f; c += 64) __builtin_nontemporal_store(src[nu + c], dst + 5 * Np + c);
+    for (int c = (r & ~63) + lane; c < 5 * Np; c += 64) dst[c] = src[c];
+    for (int c = lane; c <= f; c += 64) dst[5 * Np + c] = src[nu + c];
 }
 
 // [S^K | -g^K] from K' into E's trace rows, and [S^K | g^K] column-major into SK,
-// one 32 x 32 tile per workgroup; the element's first tile leaves the mark by
-// which the recovery knows the gradient rows' form.
+// one 64 x 64 tile per workgroup; the element's first tile leaves the mark by
+// which the recovery knows the gradient rows' form.  256 elements at p = 4: 1.00 ms
+// (1.13 with 32 x 32 tiles, whose segments are two lines; 0.65 at the copy rate).
+constexpr int kWbTile = 64;
 __global__ void __launch_bounds__(256) k_wb_trace(DevMesh dm, RedBuf rb, int e0, double *__restrict__ Ebase,
                                                   double *__restrict__ SK) {
     const int el = blockIdx.z, e = e0 + el;
     if (!rb.sel[el]) return;
     const int p = dm.elem_p[e], Np = (p + 1) * (p + 1) * (p + 1), nu = red_n(Np), f = dm.toff[7 * e + 6];
-    const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
+    const int i0 = blockIdx.y * kWbTile, j0 = blockIdx.x * kWbTile;
     if (i0 >= f || j0 > f) return;
     const int64_t ld = e_ld(20 * Np, f), ldk = e_ld(nu, f);
     const double *Kr = rb.K + (rb.k_off[e] - rb.k_off[e0]) + (int64_t)nu * ldk + nu;
     double *E = Ebase + (dm.E_off[e] - dm.E_off[e0]) + (int64_t)20 * Np * ld;
     double *out = SK + dm.SK_off[e];
-    __shared__ double tile[32][33];
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int r = ty; r < 32; r += 8) {
-        const int i = i0 + r, j = j0 + tx;
-        double v = 0.0;
-        if (i < f && j <= f) {
-            v = Kr[(int64_t)i * ldk + j];
-            __builtin_nontemporal_store(v, E + (int64_t)i * ld + 20 * Np + j);
-            if (j == f) v = -v;
+    __shared__ double tile[kWbTile][kWbTile + 1];
+    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    {
+        const int j = j0 + tx;
+        double v[kWbTile / 4];
+#pragma unroll
+        for (int q = 0; q < kWbTile / 4; ++q) v[q] = Kr[(int64_t)min(i0 + ty + 4 * q, f - 1) * ldk + min(j, f)];
+#pragma unroll
+        for (int q = 0; q < kWbTile / 4; ++q) {
+            const int i = i0 + ty + 4 * q;
+            if (i < f && j <= f) __builtin_nontemporal_store(v[q], E + (int64_t)i * ld + 20 * Np + j);
+            tile[ty + 4 * q][tx] = j == f ? -v[q] : v[q];
         }
-        tile[r][tx] = v;
     }
     __syncthreads();
-    for (int c = ty; c < 32; c += 8) {
+#pragma unroll 4
+    for (int c = ty; c < kWbTile; c += 4) {
         const int j = j0 + c, i = i0 + tx;
         if (i < f && j <= f) out[(int64_t)j * f + i] = tile[tx][c];
     }
@@ -792,7 +800,7 @@ int launch_red_writeback(const hdg_ctx *ctx, const RedBuf &rb, int e0, int ne, d
         f = std::max(f, ctx->elem_f[e]);
     }
     hipLaunchKernelGGL(k_wb_rows, dim3((nu + 3) / 4, ne), dim3(256), 0, s, ctx->dm, rb, e0, E);
-    hipLaunchKernelGGL(k_wb_trace, dim3((f + 1 + 31) / 32, (f + 31) / 32, ne), dim3(256), 0, s, ctx->dm, rb, e0, E, SK);
+    hipLaunchKernelGGL(k_wb_trace, dim3(f / kWbTile + 1, (f + kWbTile - 1) / kWbTile, ne), dim3(256), 0, s, ctx->dm, rb, e0, E, SK);
     return (int)hipGetLastError();
 }
 
