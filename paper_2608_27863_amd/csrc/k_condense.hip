@@ -51,6 +51,7 @@
 #include <climits>
 
 #include "hdg_internal.h"
+#include "lanes.h"
 
 namespace hdg {
 namespace {
@@ -173,15 +174,6 @@ template <int CTRL> __device__ inline double dpp_val(double x) {
 template <int CTRL, typename T> __device__ inline void argmax_dpp(T &v, int &r) {
     argmax_combine(v, r, dpp_val<CTRL>(v), dpp_int<CTRL>(r));
 }
-// Lane pairs (l, l ^ 16) or (l, l ^ 32) by the gfx950 row swaps: with both
-// operands the same register, the two results hold, lane by lane, the lane's own
-// value and its partner's (in some order), which is all a symmetric combine needs.
-template <int W> __device__ inline void swap_pair(unsigned x, unsigned &a, unsigned &b) {
-    const auto p = (W == 16) ? __builtin_amdgcn_permlane16_swap(x, x, false, false)
-                             : __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    a = p[0];
-    b = p[1];
-}
 template <int W> __device__ inline void argmax_swap(float &v, int &r) {
     unsigned va, vb, ra, rb;
     swap_pair<W>(__float_as_uint(v), va, vb);
@@ -214,27 +206,6 @@ template <typename T> __device__ inline void wave_argmax(T &v, int &r) {
     argmax_swap<32>(v, r);
 }
 
-// Maximum over groups of N lanes (a power of two), by the same steps.
-template <int CTRL> __device__ inline unsigned max_dpp(unsigned v) {
-    return max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true));
-}
-template <int W> __device__ inline unsigned max_swap(unsigned v) {
-    unsigned a, b;
-    swap_pair<W>(v, a, b);
-    return max(a, b);
-}
-template <int N> __device__ inline unsigned lanes_max(unsigned v) {
-    if (N > 1) v = max_dpp<0xB1>(v);
-    if (N > 2) v = max_dpp<0x4E>(v);
-    if (N > 4) v = max_dpp<0x124>(v);
-    if (N > 8) v = max_dpp<0x128>(v);
-    if (N > 16) v = max_swap<16>(v);
-    if (N > 32) v = max_swap<32>(v);
-    return v;
-}
-// The upper word of a value >= 0: a larger one is a larger value.
-__device__ inline unsigned upper_word(double x) { return (unsigned)((unsigned long long)__double_as_longlong(x) >> 32); }
-__device__ inline unsigned upper_word(float x) { return __float_as_uint(x); }
 template <typename T> constexpr unsigned kInfWord = sizeof(T) == 8 ? 0x7FF00000u : 0x7F800000u;
 
 // Net row permutation of the swaps (row base+t <-> row piv[t]), t = 0 .. w-1, applied

@@ -25,6 +25,7 @@
 #include <algorithm>
 
 #include "hdg_internal.h"
+#include "lanes.h"
 
 namespace hdg {
 namespace {
@@ -176,110 +177,129 @@ __global__ void __launch_bounds__(256) k_check(DevMesh dm, int e0, int nq, const
 }
 
 // ------------------------------------------------------------ mass matrix
-// M^{-1} by Gauss-Jordan elimination with partial pivoting in LDS, one workgroup
-// per element (the 125 x 125 block at p = 4 fits); bound by the latency of its
-// N_p dependent steps, about 1 us each, which a chunk's elements share.  A zero or
-// non-finite k-th pivot sends the element to the dense LU (sel = 0), or is
+// M^{-1} by Gauss-Jordan elimination with partial pivoting, one workgroup per element,
+// the matrix in registers: thread (rg, cg) of 32 x 16 holds rows rg + 32 i and
+// columns cg + 16 j, which move round by one j after every 16 steps so that the
+// step's column is in register 0.  Rows are not exchanged; the inverse's rows and
+// columns are put in place when it is written.  Bound by the latency of its N_p
+// dependent steps (two barriers, the search by every wave, one division).  256 elements
+// at p = 4: 347 us (70 elements: 199); with the matrix in LDS, read and written in
+// every step, 584 (438).  A zero or non-finite k-th pivot sends the element to the dense LU (sel = 0), or is
 // reported as info[e] = k+1 in a call that runs without it (checked).  With `unit` the 15 diagonal
 // blocks of the gradient rows of E become identities (the block factor M is
 // divided out of those rows).
 template <int P>
 __global__ void __launch_bounds__(512) k_minv(DevMesh dm, RedBuf rb, int e0, int checked, int unit,
                                               double *__restrict__ Ebase, int *__restrict__ info) {
-    constexpr int p1 = P + 1, Np = p1 * p1 * p1, S = Np | 1, NT = 512;
+    constexpr int p1 = P + 1, Np = p1 * p1 * p1, NT = 512, RI = (Np + 31) / 32, CJ = (Np + 15) / 16;
     const int e = e0 + blockIdx.x;
     if (dm.elem_p[e] != P || !rb.sel[blockIdx.x]) return;
     const int f = dm.toff[7 * e + 6], n = 20 * Np;
     const int64_t ld = e_ld(n, f);
     double *E = Ebase + (dm.E_off[e] - dm.E_off[e0]);
     const Aux ax = aux_of(rb, e, e0, Np, f / 5);
-    __shared__ double sM[Np * S];
-    __shared__ double sprow[Np], sfac[Np];
-    __shared__ int sperm[Np], spiv;
-    __shared__ int sbad;
-    const int tid = threadIdx.x, lane = tid & 63;
-    for (int t = tid; t < Np * Np; t += NT) sM[(t / Np) * S + t % Np] = E[(int64_t)(t / Np) * ld + t % Np];
-    if (tid == 0) sbad = 0;
+    __shared__ double sfac[2][128], srow[16 * CJ];  // the step's column; its scaled pivot row
+    __shared__ int sstep[128], spiv[16 * CJ];       // step of a pivot row; pivot row of a step
+    const int tid = threadIdx.x, lane = tid & 63, cg = tid & 15, rg = tid >> 4;
+    double a[RI][CJ];
+#pragma unroll
+    for (int i = 0; i < RI; ++i)
+#pragma unroll
+        for (int j = 0; j < CJ; ++j) {
+            const int r = rg + 32 * i, c = cg + 16 * j;
+            a[i][j] = (r < Np && c < Np) ? E[(int64_t)r * ld + c] : 0.0;
+        }
+    if (tid < 256) sfac[tid >> 7][tid & 127] = 0.0;
     __syncthreads();
-    const int row = tid >> 2;
-    for (int k = 0; k < Np; ++k) {
-        if (tid < 64) {  // pivot: largest |a| over rows k.. (smallest row on ties, NaN wins)
-            double best = -1.0;
-            int br = Np;
-            for (int r = k + lane; r < Np; r += 64) {
-                double v = fabs(sM[r * S + k]);
+    if (cg == 0)
+#pragma unroll
+        for (int i = 0; i < RI; ++i) sfac[0][rg + 32 * i] = a[i][0];
+    bool free0 = lane < Np, free1 = 64 + lane < Np;  // rows lane and 64 + lane, not pivots yet
+    int bad = 0;
+#pragma unroll 1
+    for (int jb = 0; jb < CJ; ++jb) {
+#pragma unroll 1
+        for (int kc = 0; kc < 16; ++kc) {
+            const int k = 16 * jb + kc, buf = k & 1;
+            if (k >= Np) break;  // uniform
+            __syncthreads();
+            // pivot: largest |a| over the rows left (smallest row on ties, NaN wins), by the
+            // upper words and, where two of those agree, the values
+            double best = free0 ? fabs(sfac[buf][lane]) : -1.0;
+            if (!(best == best)) best = INFINITY;
+            int p = lane;
+            if (Np > 64) {
+                double v = free1 ? fabs(sfac[buf][64 + lane]) : -1.0;
                 if (!(v == v)) v = INFINITY;
-                if (v > best) { best = v; br = r; }
+                if (v > best) { best = v; p = 64 + lane; }
             }
-            for (int off = 32; off > 0; off >>= 1) {
-                const double ov = __shfl_xor(best, off);
-                const int orr = __shfl_xor(br, off);
-                if (ov > best || (ov == best && orr < br)) { best = ov; br = orr; }
-            }
-            if (lane == 0) {
-                if (!(best > 0.0) || !(best < INFINITY)) {
-                    br = k;
-                    if (!sbad) sbad = k + 1;
+            const unsigned key = best >= 0.0 ? upper_word(best) : 0u, top = lanes_max<64>(key);
+            const unsigned long long tie = __ballot(key == top);
+            if ((tie & (tie - 1)) != 0)
+                for (int off = 32; off > 0; off >>= 1) {
+                    const double ov = __shfl_xor(best, off);
+                    const int op = __shfl_xor(p, off);
+                    if (ov > best || (ov == best && op < p)) { best = ov; p = op; }
                 }
-                spiv = br;
-                sperm[k] = br;
+            else
+                p = __builtin_amdgcn_readlane(p, __ffsll((long long)tie) - 1);
+            p = __builtin_amdgcn_readfirstlane(p);
+            const double d = sfac[buf][p], pinv = (d != 0.0) ? 1.0 / d : 0.0;
+            if (bad == 0 && !(fabs(d) > 0.0 && fabs(d) < INFINITY)) bad = k + 1;
+            free0 &= lane != p;
+            free1 &= 64 + lane != p;
+            if (rg == (p & 31))
+#pragma unroll
+                for (int i = 0; i < RI; ++i)
+                    if (i == p >> 5)
+#pragma unroll
+                        for (int j = 0; j < CJ; ++j) srow[16 * j + cg] = (j == 0 && cg == kc) ? pinv : a[i][j] * pinv;
+            if (tid == 0) {
+                sstep[p] = k;
+                spiv[k] = p;
             }
+            __syncthreads();
+            double s[CJ];
+#pragma unroll
+            for (int j = 0; j < CJ; ++j) s[j] = srow[16 * j + cg];
+#pragma unroll
+            for (int i = 0; i < RI; ++i) {
+                const int r = rg + 32 * i;
+                const double fct = sfac[buf][r];
+                if (cg == kc) a[i][0] = 0.0;
+#pragma unroll
+                for (int j = 0; j < CJ; ++j) a[i][j] = (r == p) ? s[j] : a[i][j] - fct * s[j];
+            }
+            if (cg == ((kc + 1) & 15))  // the next step's column
+#pragma unroll
+                for (int i = 0; i < RI; ++i) sfac[buf ^ 1][rg + 32 * i] = (kc == 15) ? a[i][CJ > 1 ? 1 : 0] : a[i][0];
         }
-        __syncthreads();
-        const int pr = spiv;
-        const double d = sM[pr * S + k];
-        const double pinv = (d != 0.0) ? 1.0 / d : 0.0;
-        // rows k and pr exchanged; the pivot row scaled, its column-k entry 1 / d
-        double a = 0.0, b = 0.0;
-        if (tid < Np) {
-            a = sM[pr * S + tid];
-            b = sM[k * S + tid];
+#pragma unroll
+        for (int i = 0; i < RI; ++i) {
+            const double t = a[i][0];
+#pragma unroll
+            for (int j = 0; j < CJ - 1; ++j) a[i][j] = a[i][j + 1];
+            a[i][CJ - 1] = t;
         }
-        if (tid >= 128 && tid - 128 < Np) {
-            const int r = tid - 128;
-            const int src = (r == pr) ? k : r;  // after the exchange
-            sfac[r] = sM[src * S + k];
-        }
-        __syncthreads();
-        if (tid < Np) {
-            if (pr != k) sM[pr * S + tid] = (tid == k) ? 0.0 : b;
-            const double v = (tid == k) ? pinv : a * pinv;
-            sprow[tid] = v;
-            sM[k * S + tid] = v;
-        }
-        if (tid >= 128 && tid - 128 < Np) {
-            const int r = tid - 128;
-            if (r != k && r != pr) sM[r * S + k] = 0.0;
-        }
-        __syncthreads();
-        if (row < Np && row != k) {
-            const double fct = sfac[row];
-            for (int c = tid & 3; c < Np; c += 4) sM[row * S + c] -= fct * sprow[c];
-        }
-        __syncthreads();
     }
-    if (sbad) {  // uniform: a singular block leaves the element to the dense LU where that follows
+    if (bad) {  // uniform: a singular block leaves the element to the dense LU where that follows
         if (tid == 0) {
-            if (checked) info[e] = sbad;
+            if (checked) info[e] = bad;
             else rb.sel[blockIdx.x] = 0;
         }
         if (!checked) return;
     }
-    // undo the row exchanges as column exchanges, last first
-    for (int k = Np - 1; k >= 0; --k) {
-        const int pr = sperm[k];
-        if (pr != k) {  // uniform
-            if (tid < Np) {
-                const double t = sM[tid * S + k];
-                sM[tid * S + k] = sM[tid * S + pr];
-                sM[tid * S + pr] = t;
-            }
-        }
-    }
     __syncthreads();
-    for (int t = tid; t < Np * ax.ldm; t += NT) {
-        const int r = t / ax.ldm, c = t % ax.ldm;
-        ax.Minv[t] = (c < Np) ? sM[r * S + c] : 0.0;
+    // entry (p_k, j) of the result is entry (k, p_j) of the inverse
+#pragma unroll
+    for (int i = 0; i < RI; ++i) {
+        const int r = rg + 32 * i;
+        if (r >= Np) continue;
+        double *out = ax.Minv + (int64_t)sstep[r] * ax.ldm;
+#pragma unroll
+        for (int j = 0; j < CJ; ++j)
+            if (cg + 16 * j < Np) out[spiv[cg + 16 * j]] = a[i][j];
+        for (int c = Np + cg; c < ax.ldm; c += 16) out[c] = 0.0;
     }
     if (unit)
         for (int m = 0; m < 15; ++m)
