@@ -387,12 +387,114 @@ __device__ __forceinline__ void invert_triangles(T (*t)[kNB + 1]) {
     }
 }
 
+// The same in FP32, through 8 x 8 blocks and with every sum in increasing index: FP32
+// inverses (Schwarz blocks) keep their rounding, which the joins above would change
+// by 1e-8 of the result.  s_T: LDS for the panel's block.
+template <int NT, typename T>
+__device__ __forceinline__ void panel_inverses_by_rows(const T *E, int64_t ld, int k0, int nb, int slot, T *wd,
+                                                       T (*s_T)[kNB + 1]) {
+    const int tid = threadIdx.x;
+    __shared__ T s_I[kNB][kNB + 1], s_P[8][kNB];  // s_P: partial products
+    for (int t = tid; t < kNB * kNB; t += NT) {
+        const int r = t / kNB, c = t % kNB;
+        s_T[r][c] = (r < nb && c < nb) ? E[(int64_t)(k0 + r) * ld + k0 + c] : T(0);
+        s_I[r][c] = T(0);
+    }
+    __syncthreads();
+    // Both inverses by 8 x 8 block substitution over the whole block: first the
+    // diagonal blocks (one thread per column), then one block row at a time,
+    // P = (off-diagonal part of the row) x (finished rows of the inverse) and
+    // X_row = -X_diag P.  Rows and columns >= nb act as identity and are
+    // returned as zero.
+    if (tid < kNB) {
+        // diagonal block of L11^{-1}: forward substitution, unit diagonal
+        const int j = tid, bi = j & ~7, jl = j & 7;
+        T x[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            T v = (r == jl) ? T(1) : T(0);
+#pragma unroll
+            for (int c = 0; c < r; ++c) v -= s_T[bi + r][bi + c] * x[c];
+            x[r] = (r >= jl) ? v : T(0);
+            s_I[bi + r][j] = x[r];
+        }
+    }
+    __syncthreads();
+    for (int bI = 8; bI < kNB; bI += 8) {
+        for (int t = tid; t < 8 * bI; t += NT) {  // columns left of the block row
+            const int i = t & 7, j = t >> 3;
+            T v = T(0);
+            for (int k = j & ~7; k < bI; ++k) v += s_T[bI + i][k] * s_I[k][j];
+            s_P[i][j] = v;
+        }
+        __syncthreads();
+        for (int t = tid; t < 8 * bI; t += NT) {
+            const int i = t & 7, j = t >> 3;
+            T v = T(0);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) v -= s_I[bI + i][bI + c] * s_P[c][j];
+            s_I[bI + i][j] = v;
+        }
+        __syncthreads();
+    }
+    T *li = wd + slot * kNB * kNB;
+    for (int t = tid; t < kNB * kNB; t += NT) {
+        const int r = t / kNB, c = t % kNB;
+        li[t] = (r < nb && c < nb) ? s_I[r][c] : T(0);
+    }
+    __syncthreads();
+    for (int t = tid; t < kNB * kNB; t += NT) s_I[t / kNB][t % kNB] = T(0);
+    __syncthreads();
+    if (tid < kNB) {
+        // diagonal block of U11^{-1}: back substitution
+        const int j = tid, bi = j & ~7, jl = j & 7;
+        T x[8];
+#pragma unroll
+        for (int r = 7; r >= 0; --r) {
+            T v = (r == jl) ? T(1) : T(0);
+#pragma unroll
+            for (int c = r + 1; c < 8; ++c) v -= s_T[bi + r][bi + c] * x[c];
+            const T d = (bi + r < nb) ? s_T[bi + r][bi + r] : T(1);
+            x[r] = (r <= jl) ? v / d : T(0);
+            s_I[bi + r][j] = x[r];
+        }
+    }
+    __syncthreads();
+    for (int bI = kNB - 16; bI >= 0; bI -= 8) {
+        const int nc = kNB - 8 - bI;  // columns right of the block row
+        for (int t = tid; t < 8 * nc; t += NT) {
+            const int i = t & 7, j = bI + 8 + (t >> 3);
+            T v = T(0);
+            for (int k = bI + 8; k <= (j | 7); ++k) v += s_T[bI + i][k] * s_I[k][j];
+            s_P[i][j] = v;
+        }
+        __syncthreads();
+        for (int t = tid; t < 8 * nc; t += NT) {
+            const int i = t & 7, j = bI + 8 + (t >> 3);
+            T v = T(0);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) v -= s_I[bI + i][bI + c] * s_P[c][j];
+            s_I[bI + i][j] = v;
+        }
+        __syncthreads();
+    }
+    T *ui = wd + (2 + slot) * kNB * kNB;
+    for (int t = tid; t < kNB * kNB; t += NT) {
+        const int r = t / kNB, c = t % kNB;
+        ui[t] = (r < nb && c < nb) ? s_I[r][c] : T(0);
+    }
+}
+
 // L11^{-1} and U11^{-1} of a factored panel [k0, k0+nb) to the workspace, by the NT >= 128
 // threads of the element's workgroup.  Rows and columns >= nb act as identity and
 // are returned as zero.  Inlined: called, it would reach LDS by flat addresses.
 template <int NT, typename T>
 __device__ __forceinline__ void panel_inverses(const T *E, int64_t ld, int k0, int nb, int slot, T *wd, T (*t)[kNB + 1]) {
     const int tid = threadIdx.x;
+    if constexpr (sizeof(T) == 4) {
+        panel_inverses_by_rows<NT, T>(E, ld, k0, nb, slot, wd, t);
+        return;
+    }
     for (int q = tid; q < kNB * kNB; q += NT) {
         const int r = q / kNB, c = q % kNB;
         t[r][c] = (r < nb && c < nb) ? E[(int64_t)(k0 + r) * ld + k0 + c] : T(r == c);
