@@ -2077,6 +2077,7 @@ struct MixSys {
     const int *sel;
     const int64_t *off;    // [n_elem+1] FP64 systems
     const int64_t *m_off;  // [n_elem+1] their interior rows in FP32
+    unsigned *fields;      // red = 0: per element and row field of A, k_fields' mask
 };
 __device__ inline bool mixed_dims(const DevMesh &dm, const MixSys &ms, int e, int e0, int &n, int &f, int64_t &ld,
                                   int64_t &ldx) {
@@ -2131,23 +2132,41 @@ __global__ void __launch_bounds__(256) k_xupdate(DevMesh dm, MixSys ms, int e0, 
         }
 }
 
-// Column fields of A that can be nonzero in row field fr (fields: q_(c,j) = 3c+j,
-// u_c = 15+c).  R_q couples q_(c,j) to itself (mass) and to u_c; R_u couples
-// u_c to every u (convective, viscous, mass and tau terms) and to the gradients
-// its fluxes read: the artificial viscosity term only for c = 0, the velocity
-// gradients (q of c' = 0..3) for the momentum rows, all of q for the energy row.
-__device__ inline unsigned a_field_mask(int fr) {
-    if (fr < 15) return (1u << fr) | (1u << (15 + fr / 3));
-    const unsigned u = 0x1Fu << 15;
-    const int c = fr - 15;
-    return c == 0 ? (u | 0x7u) : (c == 4 ? (u | 0x7FFFu) : (u | 0xFFFu));
+// Column fields of A (N_p columns each) that hold an entry other than zero in row
+// field blockIdx.x, one bit each.  The elements that come here lack the structure
+// of k_reduce.hip somewhere, so nothing is taken for zero unread.
+__global__ void __launch_bounds__(256) k_fields(DevMesh dm, MixSys ms, int e0, const double *__restrict__ Ebase) {
+    const int e = e0 + blockIdx.y, fr = blockIdx.x;
+    int n, f;
+    int64_t ld, ldx;
+    if (!mixed_dims(dm, ms, e, e0, n, f, ld, ldx)) return;
+    const int Np = n / 20, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const double *E = Ebase + (ms.off[e] - ms.off[e0]) + (int64_t)fr * Np * ld;
+    __shared__ unsigned s_mask;
+    if (threadIdx.x == 0) s_mask = 0;
+    __syncthreads();
+    unsigned m = 0;
+    for (int c = 2 * lane; c < n; c += 128) {
+        bool x = false, y = false;
+#pragma unroll 4
+        for (int r = wave; r < Np; r += 4) {
+            const MF<double>::v2 v = *(const MF<double>::v2 *)(E + (int64_t)r * ld + c);
+            x |= !(v.x == 0.0);
+            y |= !(v.y == 0.0);
+        }
+        if (x) m |= 1u << (c / Np);
+        if (y) m |= 1u << ((c + 1) / Np);
+    }
+    atomicOr(&s_mask, m);
+    __syncthreads();
+    if (threadIdx.x == 0) ms.fields[20 * blockIdx.y + fr] = s_mask;
 }
 
 // FP64 products of the mixed path, 128 x 128 tiles on FP64 matrix cores:
 //   OP 0 (refinement residual): R = [B | R_qu] - A X over rows 0..n-1, stored in
 //        FP32 into the right-hand columns of the FP32 system.  K chunks whose
-//        column fields are structurally zero in every row field of the tile are
-//        skipped (those entries of A are exact zeros).
+//        column fields are zero in every row field of the tile (k_fields) are
+//        skipped.
 //   OP 1 (Schur complement): [S^K | -g^K] = [D | R_uh] - C X over rows n..n+f-1,
 //        written to SK column-major with the last column negated.
 template <int OP>
@@ -2214,11 +2233,12 @@ __global__ void __launch_bounds__(256, 2) k_gemm64(DevMesh dm, MixSys ms, int e0
     // K chunks this tile needs (a reduced system has no zero blocks to skip)
     const bool skip = OP == 0 && !ms.red;
     const int Np = (n + 19) / 20;
+    const unsigned *fields = ms.fields + 20 * el;
     unsigned rmask = 0xFFFFFu;
     if (skip) {
         rmask = 0;
         const int fr1 = (min(r0 + kTM, Mrows) - 1) / Np;
-        for (int fr = r0 / Np; fr <= fr1; ++fr) rmask |= a_field_mask(fr);
+        for (int fr = r0 / Np; fr <= fr1; ++fr) rmask |= fields[fr];
     }
     const int nchunks = (K + C::KC - 1) / C::KC;
     auto needed = [&](int ch) {
@@ -2240,7 +2260,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm64(DevMesh dm, MixSys ms, int e0
         bmask[bi] = 0;
         if (!skip) bmask[bi] = 0xFFFFFu;
         else if (lo < Mrows)
-            for (int fr = lo / Np; fr <= hi / Np; ++fr) bmask[bi] |= a_field_mask(fr);
+            for (int fr = lo / Np; fr <= hi / Np; ++fr) bmask[bi] |= fields[fr];
     }
     acc_t acc[4][4];
 #pragma unroll
@@ -2609,9 +2629,9 @@ int run_asm_inversion(const hdg_ctx *ctx, int prec, void *sys, int *info, void *
 }
 
 // ---------------------------------------------------------------- mixed path
-// Workspace of a chunk: FP32 systems | X (FP64) | per-block LU records (FP32 values, ints) | flags.
+// Workspace of a chunk: FP32 systems | X (FP64) | per-block LU records (FP32 values, ints) | flags | field masks.
 struct MixedLayout {
-    size_t m_off, x_off, wd_off, wi_off, sel_off, total;
+    size_t m_off, x_off, wd_off, wi_off, sel_off, fields_off, total;
     int nblk;
 };
 static MixedLayout mixed_layout(const hdg_ctx *ctx, int e0, int ne) {
@@ -2624,7 +2644,8 @@ static MixedLayout mixed_layout(const hdg_ctx *ctx, int e0, int ne) {
     L.wd_off = L.x_off + r256(sizeof(double) * (size_t)(ctx->x_off[e0 + ne] - ctx->x_off[e0]));
     L.wi_off = L.wd_off + r256(sizeof(float) * (size_t)ne * L.nblk * kWsDbl);
     L.sel_off = L.wi_off + r256(sizeof(int) * (size_t)ne * L.nblk * kWsInt);
-    L.total = L.sel_off + r256(sizeof(int) * (size_t)ne);
+    L.fields_off = L.sel_off + r256(sizeof(int) * (size_t)ne);
+    L.total = L.fields_off + r256(sizeof(unsigned) * 20 * (size_t)ne);
     return L;
 }
 
@@ -2698,6 +2719,7 @@ int launch_condense_mixed(const hdg_ctx *ctx, int e0, int ne, int refine, bool f
     float *M = (float *)(wb + L.m_off);
     double *X = (double *)(wb + L.x_off);
     int *sel = (int *)(wb + L.sel_off);
+    unsigned *fields = (unsigned *)(wb + L.fields_off);
     WS<float> ws{(float *)(wb + L.wd_off), (int *)(wb + L.wi_off), (int64_t)L.nblk * kWsDbl,
                  (int64_t)L.nblk * kWsInt};
     const int rhs_cols = maxf + 1, tn = (rhs_cols + kTN - 1) / kTN, TMr = update_tile_rows(ctx, maxn);
@@ -2736,10 +2758,12 @@ int launch_condense_mixed(const hdg_ctx *ctx, int e0, int ne, int refine, bool f
     if (err) return err;
     float *M32r = M + (ctx->m32r_off[e0] - ctx->m32_off[e0]);
     const SysDesc sr{4, dm.m32r_off, sel, e0, 1}, sd{2, dm.m32_off, sel, e0, 0};
-    if ((err = solve(MixSys{1, sel, dm.mk_off, dm.m32r_off}, sr, rb.K, M32r, maxu))) return err;
+    if ((err = solve(MixSys{1, sel, dm.mk_off, dm.m32r_off, nullptr}, sr, rb.K, M32r, maxu))) return err;
     if ((err = launch_red_xq(ctx, rb, e0, ne, X, E, s))) return err;
     if (formed) return 0;
-    return solve(MixSys{0, sel, dm.E_off, dm.m32_off}, sd, E, M, maxn);
+    const MixSys ms{0, sel, dm.E_off, dm.m32_off, fields};
+    hipLaunchKernelGGL(k_fields, dim3(20, ne), dim3(256), 0, s, dm, ms, e0, (const double *)E);
+    return solve(ms, sd, E, M, maxn);
 }
 
 }  // namespace hdg
