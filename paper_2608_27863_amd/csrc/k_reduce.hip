@@ -102,23 +102,31 @@ __global__ void k_red_init(int ne, int structured, int *__restrict__ info, int *
 
 // sel[el] = 0 unless the element's system has the structure above, entry by
 // entry (a NaN differs from everything).  Bound by HBM: the gradient rows are
-// three quarters of A and B.  blockIdx.x < nq: kCN nodes of the gradient rows
-// (all 15 fields, against the rows of component 0); else kCR rows of the other
-// equations (the entries in gradient columns that have to be zero).
+// three quarters of A and B.  Part q < nq of an element: kCN nodes of the gradient rows
+// (all 15 fields, against the rows of component 0); the later ones: kCR rows of the other
+// equations (the entries in gradient columns that have to be zero).  Elements one after
+// another, `rest` parts each, an odd number, so that every XCD gets parts of both kinds (with
+// 32 parts at p = 2 the gradient rows fell to 6 of the 8 XCDs: 512 elements 836 us, now 380).
+// From p = 2 on the first parts of all elements come before that: where they find a
+// difference, the others return at once (512 elements at p = 2 that all differ there: 136 us;
+// at p = 1, where an element has two gradient parts, it costs more than it gives: 1000
+// elements 130 us, with leading parts 152).
 constexpr int kCN = 5, kCR = 16;
+template <int P> constexpr int kLead = P > 1 ? 1 : 0;  // leading parts per element
 template <int P>
-__global__ void __launch_bounds__(256) k_check(DevMesh dm, int e0, int nq, const double *__restrict__ Ebase,
-                                               int *__restrict__ sel) {
+__global__ void __launch_bounds__(256) k_check(DevMesh dm, int e0, int ne, int nq, int rest,
+                                               const double *__restrict__ Ebase, int *__restrict__ sel) {
     constexpr int p1 = P + 1, Np = p1 * p1 * p1;
-    const int e = e0 + blockIdx.y;
-    if (dm.elem_p[e] != P) return;
+    const int i = (int)blockIdx.x - kLead<P> * ne, el = i < 0 ? i + ne : i / rest, part = i < 0 ? 0 : kLead<P> + i % rest;
+    const int e = e0 + el;
+    if (dm.elem_p[e] != P || __hip_atomic_load(sel + el, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
     const int *to = dm.toff + 7 * e;
     const int f = to[6], n = 20 * Np;
     const int64_t ld = e_ld(n, f);
     const double *E = Ebase + (dm.E_off[e] - dm.E_off[e0]);
     bool bad = false;
-    if ((int)blockIdx.x < nq) {
-        const int i0 = blockIdx.x * kCN;
+    if (part < nq) {
+        const int i0 = part * kCN;
         for (int col = threadIdx.x; col < n + f; col += 256) {
             // the field (or trace component) of this column and where component 0's
             // rows hold the value that belongs there
@@ -151,7 +159,7 @@ __global__ void __launch_bounds__(256) k_check(DevMesh dm, int e0, int nq, const
             }
         }
     } else {
-        const int r0 = ((int)blockIdx.x - nq) * kCR;
+        const int r0 = (part - nq) * kCR;
         const int rows = 5 * Np + f;
         for (int r = r0; r < min(r0 + kCR, rows); ++r) {
             int c, lf = -1;
@@ -173,7 +181,7 @@ __global__ void __launch_bounds__(256) k_check(DevMesh dm, int e0, int nq, const
             }
         }
     }
-    if (bad) sel[blockIdx.y] = 0;
+    if (bad) __hip_atomic_store(sel + el, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ------------------------------------------------------------ mass matrix
@@ -760,7 +768,8 @@ void eliminate(const hdg_ctx *ctx, const RedBuf &rb, int e0, int ne, int maxf, i
     const int w = maxf / 5;
     if (!checked) {
         const int nq = (Np + kCN - 1) / kCN, nr = (5 * Np + maxf + kCR - 1) / kCR;
-        hipLaunchKernelGGL(k_check<P>, dim3(nq + nr, ne), dim3(256), 0, s, dm, e0, nq, (const double *)E, rb.sel);
+        const int rest = (nq + nr - kLead<P>) | 1;
+        hipLaunchKernelGGL(k_check<P>, dim3(ne * (kLead<P> + rest)), dim3(256), 0, s, dm, e0, ne, nq, rest, (const double *)E, rb.sel);
     }
     hipLaunchKernelGGL(k_minv<P>, dim3(ne), dim3(512), 0, s, dm, rb, e0, checked ? 1 : 0, write ? 1 : 0, E, info);
     const int yt = (Np + w + 5 + 63) / 64;
