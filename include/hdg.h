@@ -214,7 +214,8 @@ int hdg_peak_copy(const void *src, void *dst, size_t bytes, void *stream);
 
 /* Workspace sizes in bytes (caller allocates, 256-byte aligned).  `op` is the
  * entry point: 0 hdg_local_residual_jacobian and 1 hdg_condense (for a chunk
- * of ne elements starting at e0), 2 hdg_asm_setup, 3 hdg_asm_block_apply,
+ * of ne elements starting at e0; hdg_condense with HDG_FP64 needs the same for
+ * every e0), 2 hdg_asm_setup, 3 hdg_asm_block_apply,
  * 4 hdg_gmres / hdg_gmres_x0 (with Krylov dimension m = ne), 5 hdg_rb_guess
  * (with ne = the largest basis size used), 6 hdg_residual_gather /
  * hdg_residual_norm, 7 hdg_av_field. */

@@ -360,6 +360,7 @@ int hdg_create(const hdg_mesh_desc *m, const hdg_phys *phys, hdg_ctx **out) {
         ctx->x_off[e + 1] = ctx->x_off[e] + (int64_t)n * hdg::x_ld(f);
         ctx->kred_off[e + 1] = ctx->kred_off[e] + hdg::red_k_size(Np, f);
         ctx->aux_off[e + 1] = ctx->aux_off[e] + hdg::red_aux_size(Np, f);
+        ctx->max_red = std::max(ctx->max_red, hdg::red_k_size(Np, f) + hdg::red_aux_size(Np, f));
     }
     for (int F = 0; F < nf; ++F) ctx->max_b = std::max(ctx->max_b, trace_size(ctx->face_p[F]));
     // ---- tables and geometry
@@ -644,7 +645,7 @@ int hdg_workspace_size(const hdg_ctx *ctx, int op, int prec, int e0, int ne, siz
             return HDG_OK;
         case 1:  // hdg_condense
             if (!chunk_ok(ctx, e0, ne)) return HDG_ERR_INVALID_ARGUMENT;
-            *bytes = (prec == HDG_FP64)    ? hdg::condense_fp64_work_bytes(ctx, e0, ne)
+            *bytes = (prec == HDG_FP64)    ? hdg::condense_fp64_work_bytes(ctx, ne)
                      : (prec == HDG_MIXED) ? hdg::condense_mixed_work_bytes(ctx, e0, ne)
                                            : hdg::condense_fast_work_bytes(ctx, e0, ne);
             return HDG_OK;

@@ -137,6 +137,7 @@ struct hdg_ctx {
     int n_elem = 0, n_face = 0;
     hdg::Phys phys{};
     int max_n = 0, max_f = 0, max_b = 0, max_p = 0;
+    int64_t max_red = 0;  // largest reduced system with its auxiliary region (doubles)
     int n_vclass = 0;  // vertex classes of the artificial-viscosity smoothing
     bool uniform_p = true;
     bool repeated_face = false;  // some element meets the same face twice
@@ -162,7 +163,7 @@ int launch_element_system(const hdg_ctx *ctx, int e0, int ne, const double *Q, c
 // formed: the systems come straight from launch_element_system (no structure check)
 int launch_condense_fp64(const hdg_ctx *ctx, int e0, int ne, bool formed, double *E, double *SK, int *info,
                          void *work, hipStream_t s);
-size_t condense_fp64_work_bytes(const hdg_ctx *ctx, int e0, int ne);
+size_t condense_fp64_work_bytes(const hdg_ctx *ctx, int ne);
 // gradient elimination (k_reduce.hip)
 void launch_red_init(int ne, bool structured, int *info, int *sel, hipStream_t s);
 int launch_red_eliminate(const hdg_ctx *ctx, const RedBuf &rb, int e0, int ne, bool checked, bool write, double *E,

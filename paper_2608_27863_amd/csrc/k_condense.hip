@@ -2465,24 +2465,21 @@ static void zero_info(int *info, int ne, hipStream_t s) {
 }
 
 // FP64 condensation in pieces of at most kPieceBytes of workspace, so that a
-// call over a whole mesh needs no more (285 elements at p = 4: more than one
+// call over a whole mesh needs no more (289 elements at p = 4: more than one
 // panel workgroup per CU).  An element takes its K' and auxiliary region, two
 // blocks' LU records and a flag.
 constexpr int64_t kPieceBytes = (int64_t)9 << 29;  // 4.5 GiB
+static int64_t fp64_elem_bytes(int64_t red) { return 8 * (red + 2 * kWsDbl) + 4 * (2 * kWsInt + 1); }
 static int64_t fp64_elem_bytes(const hdg_ctx *ctx, int e) {
-    return 8 * (ctx->kred_off[e + 1] - ctx->kred_off[e] + ctx->aux_off[e + 1] - ctx->aux_off[e] + 2 * kWsDbl) +
-           4 * (2 * kWsInt + 1);
+    return fp64_elem_bytes(ctx->kred_off[e + 1] - ctx->kred_off[e] + ctx->aux_off[e + 1] - ctx->aux_off[e]);
 }
 constexpr int64_t kPieceRound = 5 * 256;
 
-size_t condense_fp64_work_bytes(const hdg_ctx *ctx, int e0, int ne) {
-    int64_t total = 0, most = 0;
-    for (int e = e0; e < e0 + ne; ++e) {
-        const int64_t b = fp64_elem_bytes(ctx, e);
-        total += b;
-        most = std::max(most, b);
-    }
-    return (size_t)((std::min(total, std::max(most, kPieceBytes)) + kPieceRound + 255) / 256 * 256);
+// Sized by the count of elements alone, as if each were the mesh's largest: a size taken once
+// for the largest chunk serves every chunk, wherever it lies.
+size_t condense_fp64_work_bytes(const hdg_ctx *ctx, int ne) {
+    const int64_t most = fp64_elem_bytes(ctx->max_red);
+    return (size_t)((std::min(ne * most, std::max(most, kPieceBytes)) + kPieceRound + 255) / 256 * 256);
 }
 
 static size_t r256(size_t b) { return (b + 255) / 256 * 256; }

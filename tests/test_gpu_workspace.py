@@ -1,0 +1,45 @@
+"""Workspace sizes: what a caller may size once, and what the calls write."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _step(n, p, seed=4, **more):
+    from paper_2608_27863_amd import pipeline, synth
+    ne = n[0] * n[1] * n[2]
+    ep = p if isinstance(p, int) else np.random.default_rng(seed).choice(p, size=ne)
+    mesh = synth.box_mesh(n, periodic=(True, True, True), p=ep, perturb=0.1, seed=seed)
+    wl = synth.make_state(mesh, lambda x: synth.tgv_state(x, 1.25), mach=1.25, noise=1e-3, nu_amp=5e-4, seed=5)
+    return pipeline.NewtonStep(wl, **more)
+
+
+def test_fp64_condensation_is_sized_by_the_count_of_elements():
+    """Elements of degree 1 first: a workspace sized for that chunk serves every chunk of as
+    many elements, and of fewer."""
+    import torch
+    from paper_2608_27863_amd import pipeline, synth
+    ep = np.repeat([1, 2, 3, 4], 6)
+    mesh = synth.box_mesh((4, 3, 2), periodic=(True, True, True), p=ep, perturb=0.1, seed=4)
+    wl = synth.make_state(mesh, lambda x: synth.tgv_state(x, 1.25), mach=1.25, noise=1e-3, nu_amp=5e-4, seed=5)
+    st = pipeline.NewtonStep(wl)
+    ctx = st.ctx
+    print("[workspace] FP64 condensation, degrees 1..4", flush=True)
+    for ne in (1, 5, 6, 24):
+        sizes = {ctx.workspace_size(1, 0, e0, ne) for e0 in range(0, ctx.n_elem - ne + 1)}
+        assert len(sizes) == 1, (ne, sizes)
+    assert ctx.workspace_size(1, 0, 0, 5) <= ctx.workspace_size(1, 0, 0, 6)
+    st.residual_jacobian()
+    E0 = st.E.clone()
+    st.condense()
+    torch.cuda.synchronize()
+    ref = st.SK.clone()
+    work = torch.empty(ctx.workspace_size(1, 0, 0, 5), dtype=torch.uint8, device="cuda")
+    o = ctx.layout["E_off"]
+    st.SK.zero_()
+    for e0 in range(0, ctx.n_elem, 5):
+        ne = min(5, ctx.n_elem - e0)
+        E = E0[int(o[e0]):int(o[e0 + ne])].clone()
+        ctx.hdg_condense(0, 1, e0, ne, E, st.SK, st.info, work)
+    torch.cuda.synchronize()
+    assert not st.info.any().item() and torch.equal(st.SK, ref)
