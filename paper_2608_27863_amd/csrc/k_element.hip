@@ -630,10 +630,12 @@ __global__ void __launch_bounds__(256) k_grad_rows(DevMesh dm, int e0, int nodes
     __shared__ double sv[oR + 15];  // a node's rows of M | G_0..2 | H_0..2 | its 15 residuals
     __shared__ int sTf[kW];  // trace unknown t of a component -> its entry in Uhat (component 0)
     __shared__ int sTn[kW];  // and the face's N_fp
+    __shared__ signed char sTl[kW];  // and the local face
     for (int t = tid; t < w; t += 256) {
         int lf = 0;
         while (5 * t >= toff[lf + 1]) ++lf;
         sTn[t] = (toff[lf + 1] - toff[lf]) / 5;
+        sTl[t] = (signed char)lf;
         sTf[t] = (int)(dm.face_off[dm.elem_face[6 * e + lf]] - dm.face_off[dm.elem_face[6 * e]]) + t - toff[lf] / 5;
     }
     const double *uh = Uhg + dm.face_off[dm.elem_face[6 * e]];
@@ -643,9 +645,7 @@ __global__ void __launch_bounds__(256) k_grad_rows(DevMesh dm, int e0, int nodes
             sv[t] = sc[((int64_t)(t / Np) * Np + i) * Np + t % Np];
         }
         for (int t = tid; t < 3 * w; t += 256) {
-            const int j = t / w, tt = t % w;
-            int lf = 0;
-            while (5 * tt >= toff[lf + 1]) ++lf;
+            const int j = t / w, tt = t % w, lf = sTl[tt];
             const int nfp = sTn[tt], b = tt - toff[lf] / 5;
             int a0, a1;
             double v = 0.0;
@@ -654,12 +654,17 @@ __global__ void __launch_bounds__(256) k_grad_rows(DevMesh dm, int e0, int nodes
             sv[oH + j * kW + tt] = v;
         }
         __syncthreads();
+        // the faces the node lies on: the trace of the others has no part in its residuals
+        // (not even as a product with zero: it may not be finite)
+        unsigned faces = 0;
+        for (int lf = 0, a0, a1; lf < 6; ++lf) faces |= (unsigned)on_face(i, p1, lf, a0, a1) << lf;
         for (int r = wave; r < 15; r += 4) {
             const int c = r / 3, j = r % 3;
             double a = 0.0;
             for (int k = lane; k < Np; k += 64)
                 a += sv[k] * Qg[15 * no + (int64_t)r * Np + k] + sv[oG + j * Np + k] * Ug[5 * no + (int64_t)c * Np + k];
-            for (int t = lane; t < w; t += 64) a += sv[oH + j * kW + t] * uh[sTf[t] + c * sTn[t]];
+            for (int t = lane; t < w; t += 64)
+                if ((faces >> sTl[t]) & 1u) a += sv[oH + j * kW + t] * uh[sTf[t] + c * sTn[t]];
             for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
             if (lane == 0) sv[oR + r] = a;
         }
