@@ -183,11 +183,14 @@ __global__ void __launch_bounds__(kMvFewThreads) k_matvec_few(DevMesh dm, const 
             double v[4], xv[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int c = min(c0 + u * W, sxo[nk] - 1);  // past the end: the last column, times zero
+                const int c = min(c0 + u * W, sxo[nk] - 1);  // past the end: the last column is read, and zero taken
                 while (c >= sxo[q + 1]) ++q;
                 v[u] = S[svo[q] + (int64_t)(c - sxo[q]) * bF + i];
-                xv[u] = (c0 + u * W < sxo[nk]) ? sx[c] : 0.0;
+                xv[u] = sx[c];
             }
+#pragma unroll
+            for (int u = 1; u < 4; ++u)
+                if (c0 + u * W >= sxo[nk]) v[u] = xv[u] = 0.0;
 #pragma unroll
             for (int u = 0; u < 4; ++u) acc += v[u] * xv[u];
         }
