@@ -1306,9 +1306,9 @@ __global__ void __launch_bounds__(256) k_crows(DevMesh dm, SysDesc sd, int e0, i
     const T *ui = ws.d + (int64_t)blockIdx.y * ws.ds + (2 + slot) * kNB * kNB;
     for (int t = tid; t < kNB * kNB; t += 256) sU[t >> 6][t & 63] = ui[t];
     __syncthreads();
-    // K = nb rounded up to 16: U11^{-1} is zero beyond nb, and the C entries there
-    // are finite (the next panel's columns, or the row padding)
-    const int kend = (nb + 15) & ~15;
+    // whole 16-wide steps of K, then the rest, whose columns beyond nb are those of D
+    // (or padding): zero is taken there, for an entry of D may not be finite
+    const int kfull = nb & ~15, krest = nb - kfull;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int rb = r0 + 32 * wave + 16 * h;
@@ -1317,7 +1317,17 @@ __global__ void __launch_bounds__(256) k_crows(DevMesh dm, SysDesc sd, int e0, i
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = (acc_t){T(0), T(0), T(0), T(0)};
         const int ra = min(rb + cl, dd.mrows - 1);
-        mfma_rowblock<T, 4>(E + (int64_t)ra * ld + kp + kq, sU, 0, 0, kend, kq, cl, acc);
+        const T *arow = E + (int64_t)ra * ld + kp + kq;
+        mfma_rowblock<T, 4>(arow, sU, 0, 0, kfull, kq, cl, acc);
+        if (krest) {  // uniform
+            T a[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) a[q] = 4 * q + kq < krest ? arow[kfull + 4 * q] : T(0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[j] = MF<T>::mfma(a[q], sU[kfull + 4 * q + kq][16 * j + cl], acc[j]);
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll

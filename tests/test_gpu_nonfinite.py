@@ -89,3 +89,39 @@ def test_matvec_with_an_infinite_entry(n, p):
         assert z[i] == v, (i, z[i])
         z[i] = y[i]
     assert np.array_equal(y, z)
+
+
+@pytest.mark.parametrize("prec", ["FP64", "MIXED_FAST"])
+@pytest.mark.parametrize("p", [1, 2, 4])
+def test_trace_block_entry_stays_in_place(p, prec):
+    """A NaN in D (trace row r, trace column c) is a NaN in S^K at (r, c) and nowhere else,
+    also in the columns next to a last panel of fewer than 64 (reduced systems of 40, 136
+    and 628 columns, whole ones of 160, 540 and 2500)."""
+    import torch
+    from paper_2608_27863_amd import hdg, pipeline
+    wl = _workload((2, 2, 2), p)
+    print(f"[nonfinite] an entry of D, p={p} {prec}", flush=True)
+    st = pipeline.NewtonStep(wl, prec=getattr(hdg, "HDG_" + prec))
+    ctx = st.ctx
+    st.residual_jacobian()
+    E = st.E.clone()
+    st.condense()
+    torch.cuda.synchronize()
+    ref = st.SK.cpu().numpy().copy()
+    at = {e: (11 * e + 2, e) for e in range(ctx.n_elem)}
+    for e, (r, c) in at.items():
+        o, n, f = (int(ctx.layout[k][e]) for k in ("E_off", "elem_n", "elem_f"))
+        ld = (int(ctx.layout["E_off"][e + 1]) - o) // (n + f)
+        E[o + (n + r) * ld + n + c] = float("nan")
+    st.E.copy_(E)
+    st.condense()
+    torch.cuda.synchronize()
+    assert not st.info.any().item()
+    got = st.SK.cpu().numpy()
+    for e, (r, c) in at.items():
+        S, g = sk_view(ctx, got, e)
+        Sr, gr = sk_view(ctx, ref, e)
+        assert np.isnan(S[r, c])
+        S = S.copy()
+        S[r, c] = Sr[r, c]
+        assert np.array_equal(S, Sr) and np.array_equal(g, gr), e
