@@ -475,16 +475,7 @@ int hdg_create(const hdg_mesh_desc *m, const hdg_phys *phys, hdg_ctx **out) {
             face_src.insert(face_src.end(), fs[F].begin(), fs[F].end());
         }
     }
-    // the (at most two) element-local entries that add up to each trace unknown
-    std::vector<int> gsrc((size_t)2 * ctx->face_off[nf], -1);
-    if (ctx->tloc_off[ne] > INT_MAX) return fail(HDG_ERR_UNSUPPORTED);
-    for (int F = 0; F < nf; ++F)
-        for (int s = face_src_ptr[F]; s < face_src_ptr[F + 1]; ++s) {
-            const int e = face_src[2 * s], a = face_src[2 * s + 1];
-            for (int64_t i = ctx->face_off[F]; i < ctx->face_off[F + 1]; ++i)
-                gsrc[2 * i + (s - face_src_ptr[F])] =
-                    (int)(ctx->tloc_off[e] + ctx->toff[7 * e + a] + (i - ctx->face_off[F]));
-        }
+    const std::vector<int64_t> gsrc = hdg::trace_sources(ctx->face_off, ctx->tloc_off, ctx->toff, face_src_ptr, face_src);
     // ---- vertex classes for the artificial-viscosity smoothing: the corners of
     // the two sides of every two-sided face (periodic pairs included) are the
     // same vertices; matching corners have the same tangential position

@@ -78,7 +78,7 @@ struct DevMesh {
     const int *blk_src;        // [n][3]: elem, local face a (row), local face b (col)
     const int *face_src_ptr;   // [n_face+1] elements touching each face
     const int *face_src;       // [n][2]: elem, local face
-    const int *gsrc;           // [2 N_uh]: entries of the element-local trace vectors that meet in a trace unknown
+    const int64_t *gsrc;       // [2 N_uh]: trace_sources
     const int *asm_blk;        // [n_elem][36]: bsr block index of (face a, face b)
     // artificial-viscosity smoothing: element corners grouped into vertex
     // classes (vertices identified through every two-sided face, periodic
@@ -114,6 +114,20 @@ __host__ __device__ inline int red_ldm(int Np) { return (Np + 15) / 16 * 16; }
 inline int64_t red_k_size(int Np, int f) { return ((int64_t)(red_n(Np) + f) * e_ld(red_n(Np), f) + 15) / 16 * 16; }
 inline int64_t red_aux_size(int Np, int f) {
     return ((int64_t)3 * Np * red_ldy(Np, f / 5) + (int64_t)Np * red_ldm(Np) + 5 * (red_n(Np) + f) + 15) / 16 * 16;
+}
+// The (at most two) entries of the element-local trace vectors that add up to each trace
+// unknown, -1 for none.
+inline std::vector<int64_t> trace_sources(const std::vector<int64_t> &face_off, const std::vector<int64_t> &tloc_off,
+                                          const std::vector<int> &toff, const std::vector<int> &face_src_ptr,
+                                          const std::vector<int> &face_src) {
+    std::vector<int64_t> src((size_t)2 * face_off.back(), -1);
+    for (size_t F = 0; F + 1 < face_off.size(); ++F)
+        for (int s = face_src_ptr[F]; s < face_src_ptr[F + 1]; ++s) {
+            const int e = face_src[2 * s], a = face_src[2 * s + 1];
+            for (int64_t i = face_off[F]; i < face_off[F + 1]; ++i)
+                src[2 * i + (s - face_src_ptr[F])] = tloc_off[e] + toff[7 * e + a] + (i - face_off[F]);
+        }
+    return src;
 }
 // Buffers of a chunk's reduced systems: element e's K' at K + k_off[e] - k_off[e0],
 // its auxiliary region at aux + aux_off[e] - aux_off[e0]; sel[e - e0] = 1 if the

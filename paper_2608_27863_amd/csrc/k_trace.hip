@@ -578,7 +578,7 @@ __device__ inline void arn_total(const double *__restrict__ part, int nv, int nb
 }
 
 // gsrc[2 i], gsrc[2 i + 1]: entries of zloc that add up to trace unknown i (-1: none)
-__global__ void __launch_bounds__(kArnThreads) k_arn_dot(const int *__restrict__ gsrc, const double *__restrict__ zloc,
+__global__ void __launch_bounds__(kArnThreads) k_arn_dot(const int64_t *__restrict__ gsrc, const double *__restrict__ zloc,
                                                          const double *__restrict__ V, int nv, int64_t N,
                                                          double *__restrict__ w, double *__restrict__ part) {
     __shared__ double sw[kArnTile], sacc[256];
@@ -589,7 +589,7 @@ __global__ void __launch_bounds__(kArnThreads) k_arn_dot(const int *__restrict__
         const int n = (int)min((int64_t)kArnTile, sl.i1 - t0);
         __syncthreads();
         if (tid < n) {
-            const int a = gsrc[2 * (t0 + tid)], b = gsrc[2 * (t0 + tid) + 1];
+            const int64_t a = gsrc[2 * (t0 + tid)], b = gsrc[2 * (t0 + tid) + 1];
             double x = zloc[a];
             if (b >= 0) x += zloc[b];
             sw[tid] = x;

@@ -65,3 +65,24 @@ def test_bench_refuses_several_gpus():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True,
                        text=True, timeout=120)
     assert r.returncode == 2 and "one GPU" in r.stderr
+
+
+def test_trace_sources_beyond_32_bits(tmp_path):
+    """Where the element-local trace entries behind each trace unknown lie: the table holds
+    positions past 2^31 (two elements sharing a face, the second far into a large mesh)."""
+    src = tmp_path / "sources.cpp"
+    src.write_text('#include "' + os.path.join(ROOT, "paper_2608_27863_amd", "csrc", "hdg_internal.h") + '"\n' + """
+#include <cstdio>
+int main() {
+    const int64_t far = (int64_t)5 << 30;
+    const std::vector<int64_t> face_off = {0, 3, 5}, tloc_off = {0, far};
+    const std::vector<int> toff = {0, 3, 5, 5, 5, 5, 5, 0, 2, 5, 5, 5, 5, 5};
+    // face 0: element 0's local face 0 and element 1's local face 1; face 1: element 1's local face 0
+    for (int64_t v : hdg::trace_sources(face_off, tloc_off, toff, {0, 2, 3}, {0, 0, 1, 1, 1, 0})) std::printf("%lld ", (long long)v);
+}
+""")
+    exe = tmp_path / "sources"
+    subprocess.check_call(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", str(src), "-o", str(exe)])
+    far = 5 << 30
+    got = [int(v) for v in subprocess.check_output([str(exe)], text=True).split()]
+    assert got == [0, far + 2, 1, far + 3, 2, far + 4, far, -1, far + 1, -1]
