@@ -191,23 +191,44 @@ double invert3(const double J[3][3], double G[3][3]) {
     return det;
 }
 
-// The context's tables go to the device in one allocation and one copy (a call of
-// each per table was most of a small context's creation).
+// The context's tables go to the device in one allocation (a call of each per table was most
+// of a small context's creation): the small ones packed into one copy, those of kPackBytes
+// or more from where they are, so that the host holds no large table twice.  The tables
+// stay in place until send().
 struct Upload {
-    std::vector<char> host;
-    std::vector<std::pair<size_t, const void **>> put;  // offset -> where the pointer belongs
+    static constexpr size_t kPackBytes = (size_t)1 << 20;
+    struct Table {
+        const void *src;
+        size_t bytes;
+        const void **dst;  // where the device pointer belongs
+    };
+    std::vector<Table> tables;
     template <class T> void add(const std::vector<T> &h, const T **dst) {
-        const size_t at = (host.size() + 255) / 256 * 256;
-        host.resize(at + std::max<size_t>(h.size(), 1) * sizeof(T));
-        if (!h.empty()) std::memcpy(host.data() + at, h.data(), h.size() * sizeof(T));
-        put.emplace_back(at, (const void **)dst);
+        tables.push_back({h.data(), h.size() * sizeof(T), (const void **)dst});
     }
     int send(hdg_ctx *ctx) {
+        std::stable_partition(tables.begin(), tables.end(), [](const Table &t) { return t.bytes < kPackBytes; });
+        auto room = [](const Table &t) { return std::max<size_t>((t.bytes + 255) / 256, 1) * 256; };
+        size_t size = 0, small = 0;
+        for (const Table &t : tables) {
+            size += room(t);
+            if (t.bytes < kPackBytes) small += room(t);
+        }
         void *p = nullptr;
-        if (hipMalloc(&p, host.size()) != hipSuccess) return HDG_ERR_OUT_OF_MEMORY;
+        if (hipMalloc(&p, size) != hipSuccess) return HDG_ERR_OUT_OF_MEMORY;
         ctx->allocations.push_back(p);
-        if (hipMemcpy(p, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess) return HDG_ERR_DEVICE;
-        for (auto &q : put) *q.second = (const char *)p + q.first;
+        std::vector<char> packed(small);
+        size_t at = 0;
+        for (const Table &t : tables) {
+            *t.dst = (const char *)p + at;
+            if (t.bytes < kPackBytes) {
+                if (t.bytes) std::memcpy(packed.data() + at, t.src, t.bytes);
+            } else if (hipMemcpy((char *)p + at, t.src, t.bytes, hipMemcpyHostToDevice) != hipSuccess) {
+                return HDG_ERR_DEVICE;
+            }
+            at += room(t);
+        }
+        if (hipMemcpy(p, packed.data(), small, hipMemcpyHostToDevice) != hipSuccess) return HDG_ERR_DEVICE;
         return HDG_OK;
     }
 };
