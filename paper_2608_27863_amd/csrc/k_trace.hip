@@ -1263,45 +1263,44 @@ int launch_asm_apply_noalloc(const hdg_ctx *ctx, int prec, const void *Sinv, con
 }
 
 // GMRES workspace (doubles): V[(m+1) N] | w[N] | t[N] | zloc | H[(m+1) m] | cs[m] | sn[m] | gam[m+1] |
-//                            hcol[m+1] | y[m] | partial[kDotBlocks (m+2)] | scal[8]
+//                            y[m] | two arrays of the slices' parts [(m+2) kArnBlocks]
+enum { kGmV, kGmW, kGmT, kGmZloc, kGmH, kGmCs, kGmSn, kGmGam, kGmY, kGmPart, kGmPart2, kGmArrays };
 static size_t gmres_layout(const hdg_ctx *ctx, int m, size_t *off) {
     const size_t N = (size_t)ctx->face_off[ctx->n_face];
     const size_t nz = (size_t)ctx->tloc_off[ctx->n_elem];
     size_t o = 0;
     auto take = [&](size_t n) { size_t at = o; o += (n + 31) / 32 * 32; return at; };
-    off[0] = take((m + 1) * N);
-    off[1] = take(N);
-    off[2] = take(N);
-    off[3] = take(nz);
-    off[4] = take((size_t)(m + 1) * m);
-    off[5] = take(m);
-    off[6] = take(m);
-    off[7] = take(m + 1);
-    off[8] = take(m + 1);
-    off[9] = take(m);
-    off[10] = take((size_t)kDotBlocks * (m + 2));
-    off[11] = take(8);
+    off[kGmV] = take((m + 1) * N);
+    off[kGmW] = take(N);
+    off[kGmT] = take(N);
+    off[kGmZloc] = take(nz);
+    off[kGmH] = take((size_t)(m + 1) * m);
+    off[kGmCs] = take(m);
+    off[kGmSn] = take(m);
+    off[kGmGam] = take(m + 1);
+    off[kGmY] = take(m);
+    off[kGmPart] = take((size_t)kArnBlocks * (m + 2));
+    off[kGmPart2] = take((size_t)kArnBlocks * (m + 2));
     return o * sizeof(double);
 }
 
 size_t gmres_work_bytes(const hdg_ctx *ctx, int m) {
-    size_t off[12];
+    size_t off[kGmArrays];
     return gmres_layout(ctx, m, off);
 }
 
 int launch_gmres(const hdg_ctx *ctx, int prec, const double *S, const void *Sinv, const double *g, const double *x0,
                  int m, double *x, double *hist, void *work, hipStream_t s) {
-    size_t off[12];
+    size_t off[kGmArrays];
     gmres_layout(ctx, m, off);
     double *W = (double *)work;
-    double *V = W + off[0], *w = W + off[1], *t = W + off[2], *zloc = W + off[3], *H = W + off[4];
-    double *cs = W + off[5], *sn = W + off[6], *gam = W + off[7], *y = W + off[9];
-    double *partial = W + off[10], *scal = W + off[11];
+    double *V = W + off[kGmV], *w = W + off[kGmW], *t = W + off[kGmT], *zloc = W + off[kGmZloc], *H = W + off[kGmH];
+    double *cs = W + off[kGmCs], *sn = W + off[kGmSn], *gam = W + off[kGmGam], *y = W + off[kGmY];
+    double *partial = W + off[kGmPart], *part2 = W + off[kGmPart2];
     const int64_t N = ctx->face_off[ctx->n_face];
     const int gN = grid_for(N);
     // slices of at least 64 entries, one workgroup per CU at most
     const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(kArnBlocks, (N + 63) / 64));
-    double *part2 = partial + (size_t)kArnBlocks * (m + 2);
     const dim3 gA(nb), tA(kArnThreads);
     int err;
     // r0 = M^{-1} (g - S x0), beta = ||r0||, v0 = r0 / beta

@@ -43,3 +43,25 @@ def test_fp64_condensation_is_sized_by_the_count_of_elements():
         ctx.hdg_condense(0, 1, e0, ne, E, st.SK, st.info, work)
     torch.cuda.synchronize()
     assert not st.info.any().item() and torch.equal(st.SK, ref)
+
+
+@pytest.mark.parametrize("n,p,m", [((2, 2, 2), 1, 1), ((2, 2, 2), 1, 200), ((4, 4, 4), 2, 200), ((8, 8, 8), 2, 30)])
+def test_gmres_keeps_to_its_workspace(n, p, m):
+    """A cycle from a guess (the longest, and slices on every CU) writes nothing past the
+    size it asks for, and that is two parts per slice and vector beside its vectors."""
+    import torch
+    st = _step(n, p, m=m)
+    ctx = st.ctx
+    print(f"[workspace] GMRES({m}), {n} p={p}", flush=True)
+    st.run()
+    N, nz = ctx.N_uh, int(ctx.layout["elem_f"].sum())
+    size = ctx.workspace_size(4, 0, 0, m)
+    need = (m + 3) * N + nz + (m + 1) * m + 4 * m + 1 + 2 * 256 * (m + 2)
+    assert 8 * need <= size <= 8 * (need + 11 * 32)
+    guard = 1 << 20
+    work = torch.full((size + guard,), 0x5A, dtype=torch.uint8, device="cuda")
+    x0 = st.dUhat.clone()
+    rc = ctx.L.hdg_gmres_x0(ctx.h, 0, st.S.data_ptr(), st.Sinv.data_ptr(), st.g.data_ptr(), x0.data_ptr(), m,
+                            st.dUhat.data_ptr(), st.hist.data_ptr(), work.data_ptr(), size, None)
+    torch.cuda.synchronize()
+    assert rc == 0 and bool((work[size:] == 0x5A).all())
