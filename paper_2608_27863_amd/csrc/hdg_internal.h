@@ -29,16 +29,15 @@ __host__ __device__ inline int tbl_W(int nq, int g) { return kTblW + (nq - 3) * 
 // Per-element quadrature-point data written by the point kernels (doubles):
 //   volume  vjac [c 5][s 20][d 4][g]   coefficient of phi_k and of the reference
 //                                      derivatives of phi_i in row u_c, column field s
-//           vres [r 20][d 4][g]        residual coefficients of row field r
+//           vres [c 5][d 4][g]         residual coefficients of row u_c
 //   face lf (lf = 0..5, points of that face)
 //           fjac [c 5][slot 25][s]     d(fh_c dS)/d(u 0..4, q 5..19, uh 20..24), weights included
 //           fres [c 5][s]              fh_c dS
 //           bres [c 5][s]              boundary residual w |N| b^_c (boundary faces)
-//           fuh  [c 5][s]              uh_c
 //           bjac [c 5][slot 25][s]     d(b^_c)/d(u, q, uh), weights included (boundary faces)
 //   then the scalar blocks M, G_j, H_j of the gradient rows (scal_size)
 __host__ __device__ inline int64_t scal_size(int Np, int p1, int w) { return (int64_t)4 * Np * Np + 3 * p1 * p1 * w; }
-constexpr int kVJac = 400, kVRes = 80, kFJac = 125, kFPer = 265;
+constexpr int kVJac = 400, kVRes = 20, kFRes = 125, kFBRes = 130, kFBJac = 135, kFPer = 260;
 
 // Device view of a context, passed by value to kernels.
 struct DevMesh {

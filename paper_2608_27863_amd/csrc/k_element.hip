@@ -208,19 +208,12 @@ __global__ void __launch_bounds__(256) k_qp_volume(DevMesh dm, Phys P, int e0, c
         double F[5][3];
         total_flux(u, q, nu, P, s, F);
         double *vres = out + (int64_t)kVJac * Nq;
-        // residual coefficients: gradient rows
-        for (int c = 0; c < 5; ++c)
-            for (int j = 0; j < 3; ++j) {
-                const int r = 3 * c + j;
-                vres[(4 * r + 0) * Nq + g] = W * q[r];
-                for (int d = 0; d < 3; ++d) vres[(4 * r + 1 + d) * Nq + g] = W * u[c] * G[d][j];
-            }
-        // residual coefficients: conservation rows
+        // residual coefficients of the conservation rows (the gradient rows' residuals are
+        // formed from their blocks, k_grad_rows)
         for (int c = 0; c < 5; ++c) {
-            const int r = 15 + c;
-            vres[(4 * r + 0) * Nq + g] = P.alpha * W * (u[c] - un[c]);
+            vres[(4 * c + 0) * Nq + g] = P.alpha * W * (u[c] - un[c]);
             for (int d = 0; d < 3; ++d)
-                vres[(4 * r + 1 + d) * Nq + g] = -P.dt * W * (G[d][0] * F[c][0] + G[d][1] * F[c][1] + G[d][2] * F[c][2]);
+                vres[(4 * c + 1 + d) * Nq + g] = -P.dt * W * (G[d][0] * F[c][0] + G[d][1] * F[c][1] + G[d][2] * F[c][2]);
         }
         // Jacobian coefficients of the conservation rows
         for (int cp = 0; cp < 5; ++cp) {
@@ -294,11 +287,8 @@ __global__ void __launch_bounds__(64) k_qp_face(DevMesh dm, Phys P, int e0, cons
         pstate(uh, q, P, st);
         double Fl[5][3];
         total_flux(uh, q, nu, P, st, Fl);
-        for (int c = 0; c < 5; ++c) {
-            out[(125 + c) * Nqf + s] = Fl[c][0] * wN[0] + Fl[c][1] * wN[1] + Fl[c][2] * wN[2] + P.tau * wA * (u[c] - uh[c]);
-            out[(130 + c) * Nqf + s] = 0.0;
-            out[(135 + c) * Nqf + s] = uh[c];
-        }
+        for (int c = 0; c < 5; ++c)
+            out[(kFRes + c) * Nqf + s] = Fl[c][0] * wN[0] + Fl[c][1] * wN[1] + Fl[c][2] * wN[2] + P.tau * wA * (u[c] - uh[c]);
         // d fh / d u (element trace): tau |N| I
         for (int c = 0; c < 5; ++c)
             for (int cp = 0; cp < 5; ++cp) out[(25 * c + cp) * Nqf + s] = (c == cp) ? P.tau * wA : 0.0;
@@ -318,14 +308,14 @@ __global__ void __launch_bounds__(64) k_qp_face(DevMesh dm, Phys P, int e0, cons
                     dF[c][0] * wN[0] + dF[c][1] * wN[1] + dF[c][2] * wN[2] - ((c == cp) ? P.tau * wA : 0.0);
         }
         if (bc) {
-            // boundary residual b^ of eq. hdg-trace (weighted by w |N|) into slots 130+c, its
-            // derivatives d b^_c / d(u 0..4, q 5..19, uh 20..24) into 140 + 25 c + slot:
+            // boundary residual b^ of eq. hdg-trace (weighted by w |N|) into slots kFBRes + c, its
+            // derivatives d b^_c / d(u 0..4, q 5..19, uh 20..24) into kFBJac + 25 c + slot:
             //  1 prescribed state uh - ub; 2 extrapolated state uh - u;
             //  3 no-slip isothermal wall (rho^ - rho, m^, rho^E^ - rho^ e_w), e_w the internal
             //    energy of the prescribed state; 4 no-slip adiabatic wall (rho^ - rho, m^, the
             //    energy component of the numerical flux); 5 symmetry (rho^ - rho,
             //    m^ - (I - n n^T) m, rho^E^ - rhoE)
-            double *bj = out + (int64_t)140 * Nqf + s;
+            double *bj = out + (int64_t)kFBJac * Nqf + s;
             for (int k = 0; k < 125; ++k) bj[(int64_t)k * Nqf] = 0.0;
             auto J = [&](int c, int slot) -> double & { return bj[(int64_t)(25 * c + slot) * Nqf]; };
             double br[5];
@@ -349,7 +339,7 @@ __global__ void __launch_bounds__(64) k_qp_face(DevMesh dm, Phys P, int e0, cons
                     J(4, 24) = wA;
                     J(4, 20) = -wA * ew;
                 } else {
-                    br[4] = out[(125 + 4) * Nqf + s];
+                    br[4] = out[(kFRes + 4) * Nqf + s];
                     for (int k = 0; k < 25; ++k) J(4, k) = out[(25 * 4 + k) * Nqf + s];
                 }
             } else {
@@ -371,7 +361,7 @@ __global__ void __launch_bounds__(64) k_qp_face(DevMesh dm, Phys P, int e0, cons
                 J(4, 24) = wA;
                 J(4, 4) = -wA;
             }
-            for (int c = 0; c < 5; ++c) out[(130 + c) * Nqf + s] = br[c];
+            for (int c = 0; c < 5; ++c) out[(kFBRes + c) * Nqf + s] = br[c];
         }
     }
 }
@@ -923,7 +913,7 @@ __global__ void __launch_bounds__(256) k_conserved_trace(DevMesh dm, Phys P, int
     // ---- residual column and padding: the residual's point coefficients in LDS,
     // the sum over the Gauss points split over two halves of the threads
     {
-        const double *rc = qpe + (int64_t)kVJac * Nq + (int64_t)(4 * r) * Nq;
+        const double *rc = qpe + (int64_t)kVJac * Nq + (int64_t)(4 * c) * Nq;
         for (int t = tid; t < 4 * Nq; t += NT) sC[t / Nq][t % Nq] = rc[t];
     }
     __syncthreads();
@@ -949,7 +939,7 @@ __global__ void __launch_bounds__(256) k_conserved_trace(DevMesh dm, Phys P, int
             const int Nqf = sNqf[lf], nqf1 = sPf[lf] + 2;
             const double *fb = qpe + sFbase[lf];
             for (int s = 0; s < Nqf; ++s)
-                v += P.dt * fb[(125 + c) * Nqf + s] * sLf[lf][a0 * nqf1 + s % nqf1] * sLf[lf][a1 * nqf1 + s / nqf1];
+                v += P.dt * fb[(kFRes + c) * Nqf + s] * sLf[lf][a0 * nqf1 + s % nqf1] * sLf[lf][a1 * nqf1 + s / nqf1];
         }
         Er[(int64_t)i * ld + n + f] = v;
         for (int64_t col = n + f + 1; col < ld; ++col) Er[(int64_t)i * ld + col] = 0.0;
@@ -1032,8 +1022,8 @@ __global__ void __launch_bounds__(256) k_trace_rows(DevMesh dm, int e0, const do
         __syncthreads();
         for (int t = tid; t < 26 * Nqf; t += 256) {
             const int slot = t / Nqf, sq = t % Nqf;
-            sK[slot][sq] = (slot == 25) ? fb[(int64_t)((bc ? 130 : 125) + c) * Nqf + sq]
-                                        : fb[(int64_t)((bc ? 140 : 0) + 25 * c + slot) * Nqf + sq];
+            sK[slot][sq] = (slot == 25) ? fb[(int64_t)((bc ? kFBRes : kFRes) + c) * Nqf + sq]
+                                        : fb[(int64_t)((bc ? kFBJac : 0) + 25 * c + slot) * Nqf + sq];
         }
         __syncthreads();
         for (int t = tid; t < 26 * pf1 * nqf1; t += 256) {

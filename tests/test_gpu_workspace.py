@@ -65,3 +65,26 @@ def test_gmres_keeps_to_its_workspace(n, p, m):
                             st.dUhat.data_ptr(), st.hist.data_ptr(), work.data_ptr(), size, None)
     torch.cuda.synchronize()
     assert rc == 0 and bool((work[size:] == 0x5A).all())
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+def test_point_workspace_holds_what_is_read(p):
+    """Per element: Jacobian and residual coefficients of the five conserved rows at the volume
+    points (420), of a face's rows, residual and boundary terms at its points (260), and
+    the scalar blocks of the gradient rows; every entry of the systems is still written."""
+    import torch
+    st = _step((2, 2, 2), p)
+    ctx = st.ctx
+    print(f"[workspace] point coefficients, p={p}", flush=True)
+    nq, p1 = p + 2, p + 1
+    per = 420 * nq ** 3 + 6 * 260 * nq ** 2 + 4 * p1 ** 6 + 3 * p1 ** 2 * 6 * p1 ** 2
+    for ne in (1, 8):
+        assert ctx.workspace_size(0, 0, 0, ne) == (8 * ne * per + 255) // 256 * 256
+    st.residual_jacobian()
+    torch.cuda.synchronize()
+    ref = st.E.clone()
+    st.E.fill_(float("nan"))
+    st.qp_work.fill_(0xFF)  # NaN wherever nothing is written
+    st.residual_jacobian()
+    torch.cuda.synchronize()
+    assert torch.equal(st.E, ref)
