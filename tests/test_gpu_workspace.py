@@ -88,3 +88,31 @@ def test_point_workspace_holds_what_is_read(p):
     st.residual_jacobian()
     torch.cuda.synchronize()
     assert torch.equal(st.E, ref)
+
+
+def test_pieces_equal_chunks():
+    """More elements than one piece holds (290 of degree 4 are 4.5 GiB), degrees 2 and 4 mixed, from
+    an element that is not the first: the systems, S^K and info of one call are bit for bit
+    those of calls of 100 elements, each of one piece."""
+    import torch
+    st = _step((8, 7, 7), (4, 4, 4, 4, 2))
+    ctx = st.ctx
+    e0, ne = 3, ctx.n_elem - 3
+    n4 = int((ctx.layout["elem_n"][e0:] == 2500).sum())
+    print(f"[workspace] pieces: {ne} elements, {n4} of degree 4", flush=True)
+    assert n4 > 290 and ctx.workspace_size(1, 0, e0, ne) < (9 << 29) + 4096
+    st.residual_jacobian()
+    o = ctx.layout["E_off"]
+    E0 = st.E.clone()
+    one, many = (torch.zeros_like(st.SK) for _ in range(2))
+    info = torch.full((2, ctx.n_elem), -1, dtype=torch.int32, device="cuda")
+    ctx.hdg_condense(0, 1, e0, ne, st.E[int(o[e0]):], one, info[0], st.cond_work)
+    torch.cuda.synchronize()
+    work = torch.empty(ctx.workspace_size(1, 0, 0, 100), dtype=torch.uint8, device="cuda")
+    for a in range(e0, ctx.n_elem, 100):
+        k = min(100, ctx.n_elem - a)
+        ctx.hdg_condense(0, 1, a, k, E0[int(o[a]):int(o[a + k])], many, info[1], work)
+    torch.cuda.synchronize()
+    assert torch.equal(info[0], info[1]) and not info[0, e0:].any().item() and bool((info[:, :e0] == -1).all())
+    assert torch.equal(one, many)
+    assert torch.equal(st.E, E0)
