@@ -264,7 +264,9 @@ int hdg_get_update_tile(const hdg_ctx *ctx, int n);
  *    triangle of the n x n block) and L^{-1} P [B | R_qu]; rows n.. hold
  *    [S^K | -g^K].  Where an element's gradient rows have the structure of
  *    eq. hdg-grad (one mass matrix M in every field, the same coupling to u_c and
- *    uh_c for every component, checked entry by entry), the gradient is
+ *    uh_c for every component, checked entry by entry) and M is as well conditioned
+ *    as that of an element (|M| |M^{-1}| up to 16 times an affine element's, in
+ *    Frobenius norms; not asked of systems formed in the same call), the gradient is
  *    eliminated with M itself as the block factor: U's first 15 N_p rows are then
  *    scaled so that their diagonal blocks are identities (L holds M there), and
  *    the pivots of the remaining 5 N_p columns are chosen among the conserved

@@ -17,8 +17,8 @@
 // remain), and a trace row meets only the nodes of its own face.
 //
 // None of this is assumed of a system that a caller hands in: k_check compares
-// every entry of E that the elimination relies on, and an element that differs
-// in one of them takes the dense LU of all its n columns.  The one-call Newton
+// every entry of E that the elimination relies on, k_minv looks at how well M is
+// conditioned, and an element that fails either takes the dense LU of all its n columns.  The one-call Newton
 // step forms the systems itself in the same call and does without the check.
 #include <hip/hip_runtime.h>
 
@@ -193,9 +193,18 @@ __global__ void __launch_bounds__(256) k_check(DevMesh dm, int e0, int ne, int n
 // dependent steps (two barriers, the search by every wave, one division).  256 elements
 // at p = 4: 347 us (70 elements: 199); with the matrix in LDS, read and written in
 // every step, 584 (438).  A zero or non-finite k-th pivot sends the element to the dense LU (sel = 0), or is
-// reported as info[e] = k+1 in a call that runs without it (checked).  With `unit` the 15 diagonal
-// blocks of the gradient rows of E become identities (the block factor M is
-// divided out of those rows).
+// reported as info[e] = k+1 in a call that runs without it (checked).  A matrix whose
+// |M| |M^{-1}| (Frobenius norms) is over kMassCond goes there too: the elimination through
+// M cannot pivot out of it, and loses up to the cube of that factor in systems where the LU
+// of all columns loses none (random couplings of order 1 at p = 2: S within 1e-12 at a factor
+// of 7e2, within 6e-7 at 2e4).  The bound is 16 times an affine element's 37, 536, 2112, 5831;
+// vertices moved by 0.4 of the spacing give at most 1.6 times those, a Jacobian that varies a
+// hundredfold in an element ten times.  In systems that the same call forms (checked) the
+// couplings are graded as M is, and this route is the more accurate one (a Jacobian varying
+// 10^4-fold, p = 3: S within 1e-15 to 2e-13, by all columns 1e-15 to 1e-10).
+// With `unit` the 15 diagonal blocks of the gradient rows of E become identities (the block
+// factor M is divided out of those rows).
+template <int P> constexpr double kMassCond = 16 * (P == 1 ? 37 : P == 2 ? 536 : P == 3 ? 2112 : 5831);
 template <int P>
 __global__ void __launch_bounds__(512) k_minv(DevMesh dm, RedBuf rb, int e0, int checked, int unit,
                                               double *__restrict__ Ebase, int *__restrict__ info) {
@@ -208,6 +217,7 @@ __global__ void __launch_bounds__(512) k_minv(DevMesh dm, RedBuf rb, int e0, int
     const Aux ax = aux_of(rb, e, e0, Np, f / 5);
     __shared__ double sfac[2][128], srow[16 * CJ];  // the step's column; its scaled pivot row
     __shared__ int sstep[128], spiv[16 * CJ];       // step of a pivot row; pivot row of a step
+    __shared__ double snorm[2][NT / 64];            // squares of M's and of the inverse's entries, by wave
     const int tid = threadIdx.x, lane = tid & 63, cg = tid & 15, rg = tid >> 4;
     double a[RI][CJ];
 #pragma unroll
@@ -217,6 +227,16 @@ __global__ void __launch_bounds__(512) k_minv(DevMesh dm, RedBuf rb, int e0, int
             const int r = rg + 32 * i, c = cg + 16 * j;
             a[i][j] = (r < Np && c < Np) ? E[(int64_t)r * ld + c] : 0.0;
         }
+    auto squares = [&](double *out) {
+        double v = 0.0;
+#pragma unroll
+        for (int i = 0; i < RI; ++i)
+#pragma unroll
+            for (int j = 0; j < CJ; ++j) v += a[i][j] * a[i][j];
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if (lane == 0) out[tid >> 6] = v;
+    };
+    if (!checked) squares(snorm[0]);
     if (tid < 256) sfac[tid >> 7][tid & 127] = 0.0;
     __syncthreads();
     if (cg == 0)
@@ -297,7 +317,19 @@ __global__ void __launch_bounds__(512) k_minv(DevMesh dm, RedBuf rb, int e0, int
         }
         if (!checked) return;
     }
+    if (!checked) squares(snorm[1]);
     __syncthreads();
+    if (!checked) {
+        double m = 0.0, v = 0.0;
+        for (int q = 0; q < NT / 64; ++q) {
+            m += snorm[0][q];
+            v += snorm[1][q];
+        }
+        if (!(m * v <= kMassCond<P> * kMassCond<P>)) {  // uniform; also where a square leaves the range
+            if (tid == 0) rb.sel[blockIdx.x] = 0;
+            return;
+        }
+    }
     // entry (p_k, j) of the result is entry (k, p_j) of the inverse
 #pragma unroll
     for (int i = 0; i < RI; ++i) {

@@ -164,3 +164,47 @@ def test_mass_matrix_without_an_inverse(systems):
         print(f"  element {e}: |S| {np.linalg.norm(R[:, :-1]):.2e}, tolerance {tol:.2e}")
         assert tol <= 1e-3 * np.linalg.norm(R[:, :-1])
         assert np.linalg.norm(S - R[:, :-1]) <= tol and np.linalg.norm(g + R[:, -1]) <= tol, e
+
+
+@pytest.mark.parametrize("kind,eps", [("row", 1e-2), ("row", 1e-4), ("row", 1e-8), ("row", 1e-12), ("column", 1e-8),
+                                      ("near", 1e-3), ("near", 1e-6), ("near", 1e-9), ("near", 1e-12)])
+def test_ill_conditioned_mass_matrix(systems, kind, eps):
+    """Gradient rows with the structure, A well conditioned and M less and less so (a row or a
+    column scaled by eps, or a row that differs from another by eps): S^K and g^K within
+    what a solve with pivoting over all of A allows, 8 cond(A) u |C| |A^{-1} B|."""
+    import torch
+    wl, st0, E0 = systems
+    ctx, Np, n = st0.ctx, 27, 540
+    r = np.random.default_rng(9)
+    M = np.eye(Np) + 0.1 * r.standard_normal((Np, Np))
+    if kind == "row":
+        M[4] *= eps
+    elif kind == "column":
+        M[:, 4] *= eps
+    else:
+        M[4] = M[9] + eps * r.standard_normal(Np)
+    E = E0.clone()
+    print(f"[reduced failure] mass matrix, {kind} {eps}: cond {np.linalg.cond(M):.1e}", flush=True)
+    for e in (5, 60):
+        s = _sys(ctx, E, e)
+        new = _random_structured(tuple(s.shape), Np, int(ctx.layout["elem_f"][e]), 4, r)
+        for k in range(15):
+            new[k * Np:(k + 1) * Np, k * Np:(k + 1) * Np] = M
+        s.copy_(torch.as_tensor(new))
+        assert _keeps_structure(s, Np)
+    host = E.cpu().numpy()
+    st0.E.copy_(E)
+    st0.condense()
+    torch.cuda.synchronize()
+    assert not st0.info.any().item()
+    SK = st0.SK.cpu().numpy()
+    for e in (5, 60):
+        Ev, _ = e_view(ctx, host, e)
+        X = np.linalg.solve(Ev[:n, :n], Ev[:n, n:])
+        R = Ev[n:, n:] - Ev[n:, :n] @ X
+        S, g = sk_view(ctx, SK, e)
+        tol = 8 * np.linalg.cond(Ev[:n, :n], 1) * U64 * np.linalg.norm(np.abs(Ev[n:, :n]) @ np.abs(X))
+        err = np.linalg.norm(S - R[:, :-1])
+        print(f"  element {e}: |S| {np.linalg.norm(R[:, :-1]):.2e}, error {err:.2e}, tolerance {tol:.2e}")
+        assert tol <= 1e-3 * np.linalg.norm(R[:, :-1])
+        assert err <= tol and np.linalg.norm(g + R[:, -1]) <= tol, e
