@@ -1188,10 +1188,11 @@ static void launch_asm_local(const hdg_ctx *ctx, int prec, const void *Sinv, con
     // One workgroup per element, unless the columns are whole lines and the elements too few
     // to keep the chip reading with a workgroup each: at p = 3, 252 elements 86 us by rows
     // against 92 (FP64) and 392 66 against 68 (FP32); 294 elements 114 against 102 and
-    // 448 79 against 71; 512 elements 172 against 147 and 87 against 80.
-    const bool aligned = prec == HDG_FP64 ? ctx->asm_cols_aligned64 : ctx->asm_cols_aligned32;
+    // 448 79 against 71; 512 elements 172 against 147 and 87 against 80.  k_asm_local_elem
+    // loads 16 bytes at a time: inverses that do not start on 16 go by rows where they can.
+    const bool lines = prec == HDG_FP64 ? ctx->asm_cols_aligned64 : ctx->asm_cols_aligned32;
     const bool per_elem = ctx->max_f <= kAsmRowsPerThread * 256 &&
-                          (!aligned || ctx->n_elem >= (prec == HDG_FP64 ? 288 : 400));
+                          (!lines || (ctx->n_elem >= (prec == HDG_FP64 ? 288 : 400) && (uintptr_t)Sinv % 16 == 0));
     // fewer workgroups than CUs in the kernels below: 27 elements at p = 2 (FP64) 48 -> 14 us,
     // 216 at p = 4 368 -> 189 us; from there on they read the inverses better (252 elements
     // at p = 4 212 against 215 us, 512 340 against 439)

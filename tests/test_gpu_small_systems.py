@@ -147,3 +147,27 @@ def test_gradient_rows_by_several_nodes(n, p):
         got.append(st.E.clone())
         del st
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("prec", ["FP64", "MIXED"])
+def test_schwarz_apply_off_16_bytes(prec):
+    """480-row inverses (columns of whole lines) that start one entry off a 16-byte boundary,
+    from as many elements on as take the kernel of 16-byte loads: the same product."""
+    import torch
+    from paper_2608_27863_amd import hdg
+    ctx, mesh = _context((8, 8, 7), 3)
+    pc = getattr(hdg, "HDG_" + prec)
+    print(f"[small] Schwarz apply {prec}, inverses off 16 bytes, {ctx.n_elem} elements", flush=True)
+    dt = torch.float64 if prec == "FP64" else torch.float32
+    g = torch.Generator("cuda").manual_seed(3)
+    n = int(ctx.layout["asm_off"][-1])
+    buf = torch.randn(n + 1, dtype=dt, device="cuda", generator=g)
+    x = torch.randn(ctx.N_uh, dtype=torch.float64, device="cuda", generator=g)
+    work = torch.empty(ctx.workspace_size(3, pc), dtype=torch.uint8, device="cuda")
+    out = []
+    for M in (buf[1:], buf[1:].clone()):
+        z = torch.empty_like(x)
+        ctx.hdg_asm_block_apply(pc, M, x, z, work)
+        out.append(z)
+    # both sum the columns in increasing order, row by row
+    assert buf[1:].data_ptr() % 16 != 0 and torch.equal(out[0], out[1])
