@@ -452,8 +452,9 @@ def main():
             "frac": achieved / PEAK_FP64_TFLOPS,
             "peak_measured": peaks["fp64_mfma_tflops"], "frac_of_measured_peak": achieved / peaks["fp64_mfma_tflops"],
             "traffic": measured_traffic(f"condense_fp64_{tag}_hbm"),
-            "kernel": "hdg_condense (all chunks; k_check, k_minv, k_ysolve, k_reduce; per pair of 128-column blocks "
-                      "k_panel, k_half, k_crows, k_rowperm, k_inv128, k_blocku, k_update; then k_wb_rows, k_wb_trace)",
+            "kernel": "hdg_condense (all chunks; k_check, k_minv, k_ysolve, k_reduce, k_rescol; per pair of 128-column "
+                      "blocks k_panel_reg, k_half, k_crows, k_rowperm, k_inv128, k_blocku, k_update; then k_wb_rows, "
+                      "k_wb_trace)",
             "algorithmic": f"{fl:.4e} flop over {ne} elements (elimination of the gradient, then LU 2u^3/3 + solve "
                            f"2u^2(f+1) + Schur 2fu(f+1), u = n/4, per element), median hdg_condense time "
                            f"{r64['condense_ms']:.2f} ms"}

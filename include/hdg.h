@@ -245,12 +245,14 @@ int hdg_local_residual_jacobian(hdg_ctx *ctx, int e0, int ne,
 
 /*
  * Tile shape of the trailing update of the blocked LU (the dominant kernel of
- * hdg_condense and of the Schwarz inversion), per size of system: systems with
- * n pivot columns (n = 20 N_p for element systems; n = 0 sets the default for
- * every size) use tiles of tile_rows x 128 (tile_rows 128 or 256; default
- * 128).  Chosen by measurement (the Python pipeline's autotuner times both on
- * the device).  A chunk mixing sizes uses the setting of its largest n.
- * hdg_get_update_tile returns the rows in effect for n.
+ * hdg_condense and of the Schwarz inversion), per size of system: n = 20 N_p for
+ * element systems, f rounded up to a multiple of 4 for Schwarz systems, 0 for the
+ * default of every size.  They use tiles of tile_rows x 128 (tile_rows 128 or 256;
+ * default 128).  An element system's setting serves its LU of 5 N_p columns, with
+ * the gradient eliminated first, and its LU of all n alike.  Chosen by measurement
+ * (the Python pipeline's autotuner times both on the device).  A chunk mixing sizes
+ * uses the setting of its largest n.  hdg_get_update_tile returns the rows in
+ * effect for n.
  */
 int hdg_set_update_tile(hdg_ctx *ctx, int n, int tile_rows);
 int hdg_get_update_tile(const hdg_ctx *ctx, int n);
@@ -270,10 +272,17 @@ int hdg_get_update_tile(const hdg_ctx *ctx, int n);
  *    eliminated with M itself as the block factor: U's first 15 N_p rows are then
  *    scaled so that their diagonal blocks are identities (L holds M there), and
  *    the pivots of the remaining 5 N_p columns are chosen among the conserved
- *    rows.  Any other system takes the LU of all n columns.
+ *    rows.  Four doubles at the start of such an element's first trace row (columns
+ *    0..3 of row n, whatever they held before) then say so to hdg_recover_interior;
+ *    without them it back-substitutes with all of U, to the same result but for
+ *    rounding.  Any other system takes the LU of all n columns (5 to 6 times longer at
+ *    p = 4), after the check and launches that find nothing to do: about 50 us a
+ *    call, and the time to read the system up to its first difference.
  *  HDG_MIXED_FAST: as HDG_FP64 but in FP32 (an FP32 copy of the systems in the
- *    workspace); S^K and g^K carry the FP32 rounding; rows 0..n-1 of E are then
- *    overwritten with the FP32 factors converted to FP64 (for the recovery).
+ *    workspace) and always by the LU of all n columns, which makes it slower than
+ *    the other two where those eliminate the gradient first (4 times at p = 4); S^K and
+ *    g^K carry the FP32 rounding; rows 0..n-1 of E are then overwritten with the FP32
+ *    factors converted to FP64 (for the recovery).
  *  HDG_MIXED: A is factorised in FP32 in the workspace, X = A^{-1}[B | R_qu] is
  *    refined `refine_steps` (>= 1) times with FP64 residuals [B|R_qu] - A X, S^K
  *    and g^K are formed with FP64 products; X is then stored in place of
