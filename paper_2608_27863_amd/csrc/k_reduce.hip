@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(256) k_check(DevMesh dm, int e0, int ne, int n
 // step's column is in register 0.  Rows are not exchanged; the inverse's rows and
 // columns are put in place when it is written.  Bound by the latency of its N_p
 // dependent steps (two barriers, the search by every wave, one division).  256 elements
-// at p = 4: 347 us (70 elements: 199); with the matrix in LDS, read and written in
+// at p = 4: 277 us (70 elements: 199); with the matrix in LDS, read and written in
 // every step, 584 (438).  A zero or non-finite k-th pivot sends the element to the dense LU (sel = 0), or is
 // reported as info[e] = k+1 in a call that runs without it (checked).  A matrix whose
 // |M| |M^{-1}| (Frobenius norms) is over kMassCond goes there too: the elimination through
